@@ -35,7 +35,7 @@ struct SplatLayout {
   uint32_t units, chunks;            // binning units (waves), 64 per chunk
   uint64_t max_points, max_pairs, max_slices;
   bool aux;                          // an attribute channel is drawn
-  size_t tile_count, tile_off, ucount, pchunk, slice_off, scan_tmp, counters;
+  size_t tile_count, tile_off, ucount, pchunk, slice_off, counters;
   size_t rec, partial, partial_aux, slice_table;   // rec: float32 records of the (point, tile) pairs
   size_t total;
 };
@@ -54,7 +54,7 @@ inline float blob_max_radius(const splat_params &sp) {
 }
 
 lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_params &sp,
-                        SplatLayout &L, bool aux);
+                        SplatLayout &L, bool aux, bool few_units = false);
 lod_status launch_splat(const float *x, const float *y, const float *z, const float *m, const float *aux,
                         uint64_t count, const lod_camera &cam, const splat_params &sp, void *ws, const SplatLayout &L,
                         float *image, float *image_aux, hipStream_t st);
@@ -75,7 +75,7 @@ lod_status launch_splat_backward(const float *x, const float *y, const float *z,
 // LOD render: the chosen nodes' stored points, decoded inside the binning.
 struct LodDrawLayout {
   uint64_t max_ids, max_points;
-  size_t offs, scan_tmp, count;
+  size_t offs, bsum, count;
   size_t total;
 };
 LodDrawLayout lod_draw_layout(uint64_t node_capacity, uint64_t max_points);

@@ -126,19 +126,28 @@ __device__ __forceinline__ bool axis_range(const Cam &c, float t, uint32_t size,
 //
 // Points are binned to 16x16 pixel tiles by a stable counting sort, so that
 // every tile's pair list -- and with it the image -- is a function of the
-// input alone.  The points are cut into U = 64 C contiguous ranges ("units"),
-// one wave each.  Pass 1 counts each unit's pairs per tile into row u of a
-// [U][tiles] table; two column scans (within chunks of 64 units, then over the
-// C chunks) and a scan over tiles give every (tile, unit) its slot range.
-// Pass 2 re-derives the pairs in the same order (64-point rounds, then a
-// point's tiles row by row, then lane) and ranks equal tiles inside the wave
-// with ballots, so the list of a tile is ordered by (unit, round, tile index
-// within the point, lane).
+// input alone.  The points are cut into rounds of 64 consecutive ones and the
+// rounds into U = 64 C contiguous ranges ("units"), one wave each.  Pass 1
+// counts each unit's pairs per tile into row u of a [U][tiles] table; two
+// column scans (within chunks of 64 units, then over the C chunks) and a scan
+// over tiles give every (tile, unit) its slot range.  Pass 2 re-derives the
+// pairs in the same order, so a tile's list is ordered by round and, inside
+// a round, by lane (rounds that spread too far: by the tile's index within
+// the point, then by lane).  Rounds start at multiples of 64, so the lists do
+// not depend on how many units there are.
+//
+// What bounds both passes is instruction issue, and the chain from one round's
+// counters to the next one's.  A wave therefore keeps the counters of an 8x8
+// tile window in its 64 lanes (lane l: tile column l % 8, row l / 8).  A round
+// whose points all fall in the window (nearly all rounds of points in Morton
+// order) turns every point's tile rectangle into a 64-bit cell mask, ORs the
+// masks over the wave, and visits each set cell once: one ballot gives the
+// cell's points, their number and their ranks, with no table access.
 
 constexpr int BW = 64;              // binning block: one wave, one unit
 constexpr int BR = 8;               // rounds of 64 points loaded together by the count pass
-constexpr int BR_FILL = 16;         // and by the fill pass (measured: 1.67 vs 1.78 ms at 150 M points;
-                                    // sixteen in the count pass cost it 0.3 ms)
+constexpr int BR_FILL = 8;          // and by the fill pass
+constexpr int WINT = 8;             // window edge in tiles: WINT * WINT == WAVE
 
 // decoded float32 coordinate of a stored point (cell coordinate c at depth d,
 // 16-bit offset q): centre of the quantisation cell, exact in float32
@@ -155,6 +164,12 @@ __device__ __forceinline__ float decode_motion(uint32_t c, uint32_t q, int dq, i
 
 // fl(a + fl(t fl(b - a))): the value at frame time t in [0, 1] between a and b
 __device__ __forceinline__ float lerp_t(float a, float b, float t) { return a + t * (b - a); }
+
+// offset of listed node k (k_lod_offsets)
+constexpr int LOFF = 1024;
+__device__ __forceinline__ uint64_t lod_off(const uint64_t *offs, const uint64_t *bsum, uint64_t k) {
+  return offs[k] + bsum[k / LOFF];
+}
 
 // Point sources.  A wave first resolves the addresses of its next BR rounds of
 // points (resolve + end_round, in round order), then issues all their loads
@@ -230,10 +245,11 @@ template <bool MOTION>
 struct TreeSrcT {
   lod_tree t;
   const uint32_t *ids;
-  const uint64_t *offs;
+  const uint64_t *offs, *bsum;   // offset of node k: lod_off
   const uint64_t *n_ids;
   uint64_t max_ids;
   const uint64_t *total;     // points to draw (device)
+  __device__ __forceinline__ uint64_t off(uint64_t k) const { return lod_off(offs, bsum, k); }
   struct Addr {
     uint64_t sidx;
     uint32_t cx, cy, cz;
@@ -246,7 +262,7 @@ struct TreeSrcT {
     __device__ __forceinline__ void set(const TreeSrcT &s, uint64_t cc) {
       c = cc;
       const uint32_t v = s.ids[cc];
-      ob = s.offs[cc]; oe = s.offs[cc + 1];
+      ob = s.off(cc); oe = s.off(cc + 1);
       d = s.t.depth[v];
       const uint64_t pfx = s.t.prefix[v];
       const uint32_t cell = d ? (uint32_t)(pfx & ((1ull << (3 * d)) - 1)) : 0u;
@@ -259,7 +275,7 @@ struct TreeSrcT {
       uint64_t lo = 0, hi = min(*s.n_ids, s.max_ids);
       while (hi - lo > 1) {
         const uint64_t mid = (lo + hi) >> 1;
-        if (s.offs[mid] <= b) lo = mid; else hi = mid;
+        if (s.off(mid) <= b) lo = mid; else hi = mid;
       }
       set(s, lo);
     }
@@ -272,15 +288,57 @@ struct TreeSrcT {
         return a;
       }
       uint64_t cl = c + 1;
-      while (s.offs[cl + 1] <= k) ++cl;
+      while (s.off(cl + 1) <= k) ++cl;
       far_c = max(far_c, cl);
       const uint32_t v = s.ids[cl];
       a.d = s.t.depth[v];
       const uint64_t pfx = s.t.prefix[v];
       const uint32_t cell = a.d ? (uint32_t)(pfx & ((1ull << (3 * a.d)) - 1)) : 0u;
       a.cx = compact3(cell); a.cy = compact3(cell >> 1); a.cz = compact3(cell >> 2);
-      a.sidx = s.t.pt_begin[v] + (k - s.offs[cl]);
+      a.sidx = s.t.pt_begin[v] + (k - s.off(cl));
       return a;
+    }
+    // Whether points [k0, k1) all lie in the cached node: then the addresses
+    // and the cell are the same for every lane (scalar registers, one vector
+    // offset) and fetch_run reads the whole batch with fetch's results.
+    __device__ __forceinline__ bool run_inside(uint64_t k0, uint64_t k1) const {
+      const uint64_t end = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(oe >> 32)) << 32) |
+                           __builtin_amdgcn_readfirstlane((uint32_t)oe);
+      return k1 <= end;
+    }
+    template <int R>
+    __device__ __forceinline__ void fetch_run(const TreeSrcT &s, uint64_t k0, float (&px)[R], float (&py)[R],
+                                              float (&pz)[R], float (&pm)[R]) const {
+      const uint32_t lane = threadIdx.x & (WAVE - 1);
+      const uint64_t first = pb + (k0 - ob);
+      const uint64_t base = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(first >> 32)) << 32) |
+                            __builtin_amdgcn_readfirstlane((uint32_t)first);
+      const int du = __builtin_amdgcn_readfirstlane(d);
+      const uint32_t ux = __builtin_amdgcn_readfirstlane(cx), uy = __builtin_amdgcn_readfirstlane(cy),
+                     uz = __builtin_amdgcn_readfirstlane(cz);
+      const uint16_t *ax = s.t.qx + base, *ay = s.t.qy + base, *az = s.t.qz + base;
+      const float *am = s.t.pt_mass + base;
+      uint32_t qx[R], qy[R], qz[R];
+      int dx[R], dy[R], dz[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t o = (uint32_t)r * WAVE + lane;
+        qx[r] = ax[o]; qy[r] = ay[o]; qz[r] = az[o]; pm[r] = am[o];
+        if constexpr (MOTION) {
+          dx[r] = (s.dqx + base)[o]; dy[r] = (s.dqy + base)[o]; dz[r] = (s.dqz + base)[o];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        px[r] = decode_coord(ux, qx[r], du);
+        py[r] = decode_coord(uy, qy[r], du);
+        pz[r] = decode_coord(uz, qz[r], du);
+        if constexpr (MOTION) {
+          px[r] = lerp_t(px[r], decode_motion(ux, qx[r], dx[r], du), s.t_frame);
+          py[r] = lerp_t(py[r], decode_motion(uy, qy[r], dy[r], du), s.t_frame);
+          pz[r] = lerp_t(pz[r], decode_motion(uz, qz[r], dz[r], du), s.t_frame);
+        }
+      }
     }
     // move the cached node to the furthest node any lane reached
     __device__ void end_round(const TreeSrcT &s) {
@@ -360,11 +418,14 @@ template <> struct RecInfo<RecCA> { static constexpr bool aux = true; static con
 // of 1/100 pixel makes the range conservative.  A tile this admits without a
 // covered pixel only adds a pair whose rows are zero in the accumulation.
 __device__ __forceinline__ bool cover_range(float R, float t, uint32_t size, int &lo, int &hi) {
-  const float lim = R + 4.0f;
-  if (!(t > -lim && t < (float)size + lim)) return false;
-  lo = max((int)ceilf(t - 0.5f - R - 0.01f), 0);
-  hi = min((int)floorf(t - 0.5f + R + 0.01f), (int)size - 1);
-  return lo <= hi;
+  const float reach = R + 0.01f;
+  const float a = fmaxf(ceilf(t - 0.5f - reach), 0.0f);
+  const float b = fminf(floorf(t - 0.5f + reach), (float)(int)(size - 1));
+  // clamped first: a coordinate far outside gives a > b (a NaN fails t == t)
+  if (!(a <= b && t == t)) return false;
+  lo = (int)a;
+  hi = (int)b;
+  return true;
 }
 
 // Pixel radius of a cubic blob at camera depth zc: the fixed radius, or the
@@ -392,61 +453,178 @@ __device__ __forceinline__ Blob make_blob(const Cam &c, bool valid, float px, fl
   return b;
 }
 
-__device__ __forceinline__ void lds_count_add(uint32_t *lc, uint32_t t, uint32_t cnt) { atomicAdd(&lc[t], cnt); }
-__device__ __forceinline__ void lds_count_add(uint16_t *lc, uint32_t t, uint32_t cnt) {
-  atomicAdd(reinterpret_cast<uint32_t *>(lc) + (t >> 1), cnt << (16 * (t & 1u)));
+// OR of a value over the wave's 64 lanes.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast 15, 31
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
 }
 
-// One tile of every lane with `has` (tile t): lanes holding the same tile form
-// a group and rank by lane index inside it; a group adds its size to the
-// tile's counter and, with FILL, writes its records at the counter's old
-// value plus the rank.  Spatially coherent points share few tiles, so groups
-// are peeled off by their lowest lane first, with the group mask in scalar
-// registers; after four groups the rest is matched bit by bit.  The grouping,
-// not the method, decides the ranks.  Counting adds to LDS without reading
-// back (16-bit counters are added in their 32-bit word; a unit's counts stay
-// below 2^16, so no carry crosses the halves).
-template <bool FILL, class CT, class RecT>
-__device__ __forceinline__ void emit_tile(uint32_t t, bool has, int nbits, CT *lc, RecT *__restrict__ rec,
-                                          const Blob &bl) {
+// Largest value over the wave's 64 lanes.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, WAVE - 1);
+}
+
+__device__ __forceinline__ uint32_t rank_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// One lane's writes to a table that another lane of the same wave reads.
+__device__ __forceinline__ void wave_sync_mem() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A unit's per-tile counters (pass 1) or list cursors (pass 2), private to its
+// wave.  LdsTab: in LDS, for rounds that touch tiles all over the image (every
+// round of points in random order).  RowTab: the unit's own row of the count
+// table in global memory, touched when a window is opened or closed; no LDS,
+// so as many waves run as registers allow, and no row-sized initialisation of
+// LDS.  get / put are a lane's own element.
+template <class CT>
+struct LdsTab {
+  static constexpr bool adds = true;
+  CT *lc;
+  __device__ __forceinline__ uint32_t get(uint32_t t) const { return (uint32_t)lc[t]; }
+  __device__ __forceinline__ void put(uint32_t t, uint32_t v) const { lc[t] = (CT)v; }
+  // counts only: lanes may add to one tile at a time (16-bit counters are
+  // added in their 32-bit word; a unit's counts stay below 2^16, so no carry
+  // crosses the halves)
+  __device__ __forceinline__ void add(uint32_t t) const {
+    if constexpr (sizeof(CT) == 2) atomicAdd(reinterpret_cast<uint32_t *>(lc) + (t >> 1), 1u << (16 * (t & 1u)));
+    else atomicAdd(&lc[t], 1u);
+  }
+};
+struct RowTab {
+  static constexpr bool adds = false;
+  uint32_t *row;
+  const uint32_t *off, *pre;     // added to what is read (list starts of the tile and the chunk), or null
+  __device__ __forceinline__ uint32_t base(uint32_t t) const { return (off ? off[t] : 0u) + (pre ? pre[t] : 0u); }
+  __device__ __forceinline__ uint32_t get(uint32_t t) const { return row[t] + base(t); }
+  __device__ __forceinline__ void put(uint32_t t, uint32_t v) const { row[t] = v - base(t); }
+};
+
+// The counters of an 8x8 tile window, one per lane.
+template <class Tab>
+struct TileWin {
+  int wx = -(1 << 20), wy = 0;   // closed: no point lies in it
+  uint32_t cur = 0, tile = 0;
+  bool inside = false;           // this lane's tile lies in the image
+  __device__ __forceinline__ bool open() const { return wx >= 0; }
+  __device__ __forceinline__ void load(const Tab &tab, const Cam &c, int x, int y) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    wx = x; wy = y;
+    const int tx = wx + lane % WINT, ty = wy + lane / WINT;
+    inside = tx < (int)c.tiles_x && ty < (int)c.tiles_y;
+    tile = inside ? (uint32_t)(ty * (int)c.tiles_x + tx) : 0u;
+    cur = inside ? tab.get(tile) : 0u;
+  }
+  __device__ __forceinline__ void close(const Tab &tab) {
+    if (!open()) return;
+    if (inside) tab.put(tile, cur);
+    wx = -(1 << 20);
+    wave_sync_mem();
+  }
+};
+
+// The pairs of one round whose points do not fit one window, tile index by
+// tile index within the point.  Counting in LDS adds lane by lane.  Otherwise
+// a ballot per tile bit groups and ranks the lanes of one tile, and the
+// lowest of them moves the tile's counter.
+template <bool FILL, class Tab, class RecT>
+__device__ __forceinline__ void emit_spread(const Blob &bl, const Cam &c, int nbits, const Tab &tab,
+                                            RecT *__restrict__ rec) {
   const int lane = threadIdx.x & (WAVE - 1);
-  uint64_t pending = __ballot(has);
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    if (!pending) return;
-    const int leader = __ffsll((unsigned long long)pending) - 1;
-    const uint32_t tl = __builtin_amdgcn_readlane(t, leader);
-    const bool mine = has && t == tl;
-    const uint64_t grp = __ballot(mine);
-    const uint32_t cnt = (uint32_t)__popcll(grp);
-    if (FILL) {
-      const uint32_t old = (uint32_t)lc[tl];
-      const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(grp >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)grp, 0u));
-      if (mine) rec_put(rec, old + rank, bl);
-      if (lane == leader) lc[tl] = (CT)(old + cnt);
-    } else {
-      if (lane == leader) lds_count_add(lc, t, cnt);   // the leader's own tile (t == tl)
+  for (int dy = 0; __ballot(dy < bl.nty); ++dy) {
+    for (int dx = 0; __ballot(dy < bl.nty && dx < bl.ntx); ++dx) {
+      const bool has = dy < bl.nty && dx < bl.ntx;
+      const uint32_t t = has ? (uint32_t)((bl.ty0 + dy) * (int)c.tiles_x + bl.tx0 + dx) : 0u;
+      if constexpr (!FILL && Tab::adds) {
+        if (has) tab.add(t);
+      } else {
+        uint64_t peers = __ballot(has);
+        for (int b = 0; b < nbits; ++b) {
+          const uint64_t bal = __ballot((t >> b) & 1u);
+          peers &= ((t >> b) & 1u) ? bal : ~bal;
+        }
+        const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (WAVE - lane));
+        const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
+        const uint32_t old = has ? tab.get(t) : 0u;
+        wave_sync_mem();
+        if (has && below == 0) tab.put(t, old + (uint32_t)__popcll(peers));
+        wave_sync_mem();
+        if (FILL && has) rec_put(rec, old + below, bl);
+      }
     }
-    pending &= ~grp;
   }
-  if (!pending) return;
-  const bool rest = ((pending >> lane) & 1ull) != 0;
-  uint64_t peers = pending;
-  for (int b = 0; b < nbits; ++b) {
-    const uint64_t bal = __ballot((t >> b) & 1u);
-    peers &= ((t >> b) & 1u) ? bal : ~bal;
+  wave_sync_mem();
+}
+
+// The pairs of one round of 64 points (each at most 8 tiles wide and high).
+template <bool FILL, class Tab, class RecT>
+__device__ __forceinline__ void emit_round(const Blob &bl, const Cam &c, int nbits, const Tab &tab,
+                                           TileWin<Tab> &win, RecT *__restrict__ rec) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const bool drawn = bl.ntx > 0;
+  const uint64_t live = __ballot(drawn);
+  if (!live) return;
+  auto fits = [&]() {
+    return drawn && (uint32_t)(bl.tx0 - win.wx) <= (uint32_t)(WINT - bl.ntx) &&
+           (uint32_t)(bl.ty0 - win.wy) <= (uint32_t)(WINT - bl.nty);
+  };
+  if (__ballot(fits()) != live) {
+    // a new window around the round's tiles, if one holds them all (a
+    // property of the round alone, and with it the order of its pairs)
+    win.close(tab);
+    const uint32_t big = 1u << 20;
+    const int x1 = (int)wave_max(drawn ? (uint32_t)(bl.tx0 + bl.ntx) : 0u);
+    const int y1 = (int)wave_max(drawn ? (uint32_t)(bl.ty0 + bl.nty) : 0u);
+    const int x0 = (int)(big - wave_max(drawn ? big - (uint32_t)bl.tx0 : 0u));
+    const int y0 = (int)(big - wave_max(drawn ? big - (uint32_t)bl.ty0 : 0u));
+    if (x1 - x0 > WINT || y1 - y0 > WINT) {
+      emit_spread<FILL, Tab, RecT>(bl, c, nbits, tab, rec);
+      return;
+    }
+    // the round's tiles in the middle of it
+    const int x = max(x0 - (WINT - (x1 - x0)) / 2, 0), y = max(y0 - (WINT - (y1 - y0)) / 2, 0);
+    win.load(tab, c, x, y);
   }
-  const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (WAVE - lane));
-  const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
-  const uint32_t cnt = (uint32_t)__popcll(peers);
-  if (FILL) {
-    const uint32_t old = rest ? (uint32_t)lc[t] : 0u;
-    if (rest && below == 0) lc[t] = (CT)(old + cnt);
-    if (rest) rec_put(rec, old + below, bl);
-  } else if (rest && below == 0) {
-    lds_count_add(lc, t, cnt);
+  // the point's cells: its columns in every row, its rows
+  uint32_t mlo = 0, mhi = 0;
+  if (drawn) {
+    const uint32_t cols = ((1u << bl.ntx) - 1u) << (bl.tx0 - win.wx);
+    const uint32_t cols4 = __builtin_amdgcn_perm(cols, cols, 0u);   // byte 0 in all four bytes
+    const uint64_t rows = (~0ull >> (64 - 8 * bl.nty)) << (8 * (bl.ty0 - win.wy));
+    mlo = cols4 & (uint32_t)rows;
+    mhi = cols4 & (uint32_t)(rows >> 32);
   }
+  auto cells_of = [&](uint32_t word, uint32_t m, int first) {
+    while (word) {
+      const int b = __builtin_ctz(word);
+      word &= word - 1u;
+      const bool mine = (m & (1u << b)) != 0u;
+      const uint64_t grp = __ballot(mine);
+      const int cell = first + b;
+      if constexpr (FILL) {
+        const uint32_t old = (uint32_t)__builtin_amdgcn_readlane((int)win.cur, cell);
+        if (mine) rec_put(rec, old + rank_below(grp), bl);
+      }
+      if (lane == cell) win.cur += (uint32_t)__popcll(grp);
+    }
+  };
+  cells_of(wave_or(mlo), mlo, 0);
+  cells_of(wave_or(mhi), mhi, 32);
 }
 
 // Highlight staging: the count pass writes the decoded points whose id is
@@ -457,96 +635,115 @@ struct HlStage {
   uint64_t *count, *scan;   // per unit (scan: a copy, scanned afterwards)
 };
 
-// Points [u0 per, min(n, (u0 + g) per)) with per = ceil(n / units): g
-// consecutive units of the partition.  Returns the points staged (HL).
-template <class Src, bool FILL, class CT, class RecT, bool HL = false>
+// Points per unit of a partition of n points: whole rounds.
+__device__ __forceinline__ uint64_t unit_points(uint64_t n, uint32_t units) {
+  const uint64_t rounds = (n + WAVE - 1) / WAVE;
+  return (rounds + units - 1) / units * WAVE;
+}
+
+// The pairs of points [u0 per, min(n, (u0 + g) per)): g consecutive units.
+// Returns the points staged (HL).
+template <class Src, bool FILL, class Tab, class RecT, bool HL = false>
 __device__ __forceinline__ uint32_t bin_unit(const Src &src, const Cam &c, uint32_t units, uint32_t u0, uint32_t g,
-                                             int nbits, CT *lc, RecT *__restrict__ rec, HlStage hs = HlStage{}) {
+                                             int nbits, const Tab &tab, RecT *__restrict__ rec,
+                                             HlStage hs = HlStage{}) {
   const int lane = threadIdx.x;
   const uint64_t n = src.count();
-  const uint64_t per = (n + units - 1) / units;
+  const uint64_t per = unit_points(n, units);
   const uint64_t b = (uint64_t)u0 * per, e = min(n, b + (uint64_t)g * per);
   uint32_t staged = 0;
   if (b >= e) return 0;
   typename Src::Cursor cur;
   cur.begin(src, b, e);
+  TileWin<Tab> win;
   constexpr int R = FILL ? BR_FILL : BR;
   for (uint64_t k0 = b; k0 < e; k0 += (uint64_t)R * WAVE) {
-    typename Src::Addr ad[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint64_t k = k0 + (uint64_t)r * WAVE + lane;
-      ad[r] = cur.resolve(src, k, k < e);
-      cur.end_round(src);
-    }
     float px[R], py[R], pz[R], pm[R], pa[R], ph[R];
+    uint64_t pid[HL ? R : 1];
+    bool whole = false;
+    if constexpr (IsTree<Src>::value) {
+      whole = k0 + (uint64_t)R * WAVE <= e && cur.run_inside(k0, k0 + (uint64_t)R * WAVE);
+      if (whole) {
+        cur.template fetch_run<R>(src, k0, px, py, pz, pm);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint64_t k = k0 + (uint64_t)r * WAVE + lane;
-      cur.fetch(src, ad[r], k < e, px[r], py[r], pz[r], pm[r]);
-      pa[r] = (FILL && RecInfo<RecT>::aux) ? cur.attr(src, ad[r]) : 0.0f;
-      ph[r] = c.blob == LOD_BLOB_CUBIC ? cur.wradius(src, ad[r]) : 0.0f;
+        for (int r = 0; r < R; ++r) {
+          pa[r] = ph[r] = 0.0f;
+          if (HL) pid[r] = cur.pb + (k0 + (uint64_t)r * WAVE + lane - cur.ob);
+        }
+      }
+    }
+    if (!whole) {
+      typename Src::Addr ad[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t k = k0 + (uint64_t)r * WAVE + lane;
+        ad[r] = cur.resolve(src, k, k < e);
+        cur.end_round(src);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t k = k0 + (uint64_t)r * WAVE + lane;
+        cur.fetch(src, ad[r], k < e, px[r], py[r], pz[r], pm[r]);
+        pa[r] = (FILL && RecInfo<RecT>::aux) ? cur.attr(src, ad[r]) : 0.0f;
+        ph[r] = c.blob == LOD_BLOB_CUBIC ? cur.wradius(src, ad[r]) : 0.0f;
+        if constexpr (HL) pid[r] = cur.point_index(src, ad[r]);
+      }
     }
     if constexpr (HL) {
       // ID highlighting: the flag test of every drawn point, and the
       // flagged ones staged in sequence order (wave ballot ranks).  A wave's
       // points are mostly consecutive stored points, so its flag loads fall
       // on one or two words.
-      uint64_t pid[R];
       uint32_t word[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) pid[r] = cur.point_index(src, ad[r]);
 #pragma unroll
       for (int r = 0; r < R; ++r) word[r] = src.hl_word(pid[r]);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const bool in = k0 + (uint64_t)r * WAVE + lane < e && src.hl_test(pid[r], word[r]);
         const uint64_t mask = __ballot(in);
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
         if (in) {
-          const uint64_t o = b + staged + rank;
+          const uint64_t o = b + staged + rank_below(mask);
           hs.x[o] = px[r]; hs.y[o] = py[r]; hs.z[o] = pz[r]; hs.m[o] = pm[r];
         }
         staged += (uint32_t)__popcll(mask);
       }
     }
-    Blob blobs[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      blobs[r] = make_blob(c, k0 + (uint64_t)r * WAVE + lane < e, px[r], py[r], pz[r], pm[r], pa[r], ph[r]);
-    // pairs in the order (round, tile row, tile column, lane)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const Blob &bl = blobs[r];
-      for (int dy = 0; __ballot(dy < bl.nty); ++dy) {
-        for (int dx = 0; __ballot(dy < bl.nty && dx < bl.ntx); ++dx) {
-          const bool has = dy < bl.nty && dx < bl.ntx;
-          const uint32_t t = has ? (uint32_t)((bl.ty0 + dy) * (int)c.tiles_x + bl.tx0 + dx) : 0u;
-          emit_tile<FILL, CT, RecT>(t, has, nbits, lc, rec, bl);
-        }
-      }
+      const Blob bl = make_blob(c, k0 + (uint64_t)r * WAVE + lane < e, px[r], py[r], pz[r], pm[r], pa[r], ph[r]);
+      emit_round<FILL, Tab, RecT>(bl, c, nbits, tab, win, rec);
     }
   }
+  win.close(tab);
   return staged;
 }
 
 // Pass 1: row u of the [U][tiles] count table.  CT = uint16_t when a unit
 // holds at most 65535 points (a point adds at most one pair per tile), which
-// halves the LDS per wave and doubles the resident waves.
+// halves the LDS per wave and doubles the resident waves; CT = void: counted
+// in the row itself.
 template <class Src, class CT, bool HL = false>
-__global__ __launch_bounds__(BW) void k_bin_count(Src src, Cam c, uint32_t units, int nbits,
-                                                  uint32_t *__restrict__ ucount, HlStage hs = HlStage{}) {
+__global__ __launch_bounds__(BW) void k_bin_count(Src src, Cam c, uint32_t units, int nbits, uint32_t *ucount,
+                                                  HlStage hs = HlStage{}) {
   extern __shared__ uint32_t lds_raw[];
-  CT *lc = reinterpret_cast<CT *>(lds_raw);
   const uint32_t nt = c.tiles_x * c.tiles_y;
-  for (uint32_t i = threadIdx.x; i < nt; i += BW) lc[i] = 0;
-  __syncthreads();
-  const uint32_t staged =
-      bin_unit<Src, false, CT, float3, HL>(src, c, units, blockIdx.x, 1, nbits, lc, (float3 *)nullptr, hs);
+  uint32_t *row = ucount + (uint64_t)blockIdx.x * nt;
+  uint32_t staged;
+  if constexpr (std::is_void<CT>::value) {
+    for (uint32_t i = threadIdx.x; i < nt; i += BW) row[i] = 0u;
+    wave_sync_mem();
+    staged = bin_unit<Src, false, RowTab, float3, HL>(src, c, units, blockIdx.x, 1, nbits,
+                                                      RowTab{row, nullptr, nullptr}, (float3 *)nullptr, hs);
+  } else {
+    CT *lc = reinterpret_cast<CT *>(lds_raw);
+    for (uint32_t i = threadIdx.x; i < nt; i += BW) lc[i] = 0;
+    __syncthreads();
+    staged = bin_unit<Src, false, LdsTab<CT>, float3, HL>(src, c, units, blockIdx.x, 1, nbits, LdsTab<CT>{lc},
+                                                          (float3 *)nullptr, hs);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < nt; i += BW) row[i] = lc[i];
+  }
   if (HL && threadIdx.x == 0) { hs.count[blockIdx.x] = staged; hs.scan[blockIdx.x] = staged; }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < nt; i += BW) ucount[(uint64_t)blockIdx.x * nt + i] = lc[i];
 }
 
 // Gather the staged highlighted points into one array in unit order: unit u
@@ -558,7 +755,7 @@ __global__ void k_hl_gather(HlStage hs, const uint64_t *__restrict__ off, const 
                             float *__restrict__ z, float *__restrict__ m, uint64_t cap,
                             uint64_t *__restrict__ total, uint64_t *status) {
   const uint64_t n = min(*n_points, max_points);
-  const uint64_t per = (n + units - 1) / units;
+  const uint64_t per = unit_points(n, units);
   const uint32_t u = blockIdx.x;
   const uint64_t b = (uint64_t)u * per, o = off[u], k = hs.count[u];
   for (uint64_t j = threadIdx.x; j < k && o + j < cap; j += blockDim.x) {
@@ -595,17 +792,22 @@ __global__ void k_hl_flags(const lod_tree t, const uint32_t *__restrict__ bits, 
 }
 
 // Column scans of the count table: exclusive prefix over the 64 units of each
-// chunk (in place) and the chunk totals.
+// chunk (in place) and the chunk totals.  A column is a chain of dependent
+// adds but not of loads: sixteen rows are loaded together.
 __global__ void k_bin_colscan(uint32_t *__restrict__ ucount, uint32_t nt, uint32_t *__restrict__ pchunk) {
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t ch = blockIdx.y;
   if (t >= nt) return;
   uint32_t run = 0;
-  for (uint32_t u = ch * 64; u < ch * 64 + 64; ++u) {
-    const uint64_t i = (uint64_t)u * nt + t;
-    const uint32_t v = ucount[i];
-    ucount[i] = run;
-    run += v;
+  for (uint32_t u = ch * 64; u < ch * 64 + 64; u += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = ucount[(uint64_t)(u + k) * nt + t];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      ucount[(uint64_t)(u + k) * nt + t] = run;
+      run += v[k];
+    }
   }
   pchunk[(uint64_t)ch * nt + t] = run;
 }
@@ -616,58 +818,94 @@ __global__ void k_bin_chunkscan(uint32_t *__restrict__ pchunk, uint32_t nt, uint
   const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nt) return;
   uint32_t run = 0;
-  for (uint32_t ch = 0; ch < chunks; ++ch) {
-    const uint64_t i = (uint64_t)ch * nt + t;
-    const uint32_t v = pchunk[i];
-    pchunk[i] = run;
-    run += v;
+  for (uint32_t c0 = 0; c0 < chunks; c0 += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = pchunk[(uint64_t)min(c0 + k, chunks - 1) * nt + t];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (c0 + k < chunks) {
+        pchunk[(uint64_t)(c0 + k) * nt + t] = run;
+        run += v[k];
+      }
   }
   tile_count[t] = run;
 }
 
-// Pass 2: write the (u, v, m) records.  Block f covers the g consecutive
-// units f g .. f g + g - 1 (a tile's list holds their pairs in unit order, so
-// one cursor per tile carries over from one unit to the next); its cursor for
-// tile t starts at tile_off[t] + (pairs of earlier chunks) + (pairs of earlier
-// units in its chunk).  The pair count (tile_off[nt]) is checked against the
+// Offsets of the tiles' pair lists and of their slices (exclusive, with the
+// totals at [nt]), and a cleared status word: one block, since there are at
+// most 8192 tiles.  tile_count null: no points.
+constexpr int PLAN_T = 1024;
+constexpr int PLAN_ITEMS = lodh::SPLAT_MAX_TILES / PLAN_T;
+__global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict__ tile_count, uint32_t nt,
+                                                      uint32_t *__restrict__ tile_off,
+                                                      uint32_t *__restrict__ slice_off, uint64_t *clear_status) {
+  __shared__ uint32_t tmp[PLAN_T / WAVE + 1];
+  const uint32_t per = (nt + PLAN_T - 1) / PLAN_T;   // tiles per thread (at most PLAN_ITEMS)
+  const uint32_t t0 = threadIdx.x * per;
+  uint32_t cnt[PLAN_ITEMS], pairs = 0, slices = 0;
+#pragma unroll
+  for (int k = 0; k < PLAN_ITEMS; ++k)
+    cnt[k] = (tile_count && (uint32_t)k < per && t0 + k < nt) ? tile_count[t0 + k] : 0u;
+#pragma unroll
+  for (int k = 0; k < PLAN_ITEMS; ++k) {
+    pairs += cnt[k];
+    slices += (cnt[k] + lodh::SPLAT_SLICE - 1) / lodh::SPLAT_SLICE;
+  }
+  uint32_t tp, ts;
+  uint32_t p = block_excl_scan<uint32_t>(pairs, tmp, tp);
+  uint32_t q = block_excl_scan<uint32_t>(slices, tmp, ts);
+#pragma unroll
+  for (int k = 0; k < PLAN_ITEMS; ++k) {
+    if ((uint32_t)k < per && t0 + k < nt) { tile_off[t0 + k] = p; slice_off[t0 + k] = q; }
+    p += cnt[k];
+    q += (cnt[k] + lodh::SPLAT_SLICE - 1) / lodh::SPLAT_SLICE;
+  }
+  if (threadIdx.x == 0) {
+    tile_off[nt] = tp;
+    slice_off[nt] = ts;
+    if (clear_status) *clear_status = 0;
+  }
+}
+
+// Pass 2: write the records.  Block f covers the g consecutive units f g ..
+// f g + g - 1 (a tile's list holds their pairs in unit order, so one cursor per
+// tile carries over from one unit to the next); its cursor for tile t starts
+// at tile_off[t] + (pairs of earlier chunks) + (pairs of earlier units in its
+// chunk).  LDS: the cursors are kept in LDS, else in the unit's row of the
+// count table (g = 1).  The pair count (tile_off[nt]) is checked against the
 // record capacity once: past it nothing is written and the status word says
-// so.
-template <class Src, class RecT>
+// so.  The blocks also write the slice descriptors, (first pair,
+// tile | pairs << 16), one per slice, a lane per tile.
+template <class Src, class RecT, bool LDS>
 __global__ __launch_bounds__(BW) void k_bin_fill(Src src, Cam c, uint32_t units, uint32_t g, int nbits,
-                                                 const uint32_t *__restrict__ ucount,
-                                                 const uint32_t *__restrict__ pchunk,
+                                                 uint32_t *ucount, const uint32_t *__restrict__ pchunk,
                                                  const uint32_t *__restrict__ tile_off,
-                                                 RecT *__restrict__ rec, uint64_t max_pairs, uint64_t *status) {
+                                                 const uint32_t *__restrict__ slice_off, uint2 *__restrict__ table,
+                                                 uint64_t max_slices, RecT *__restrict__ rec, uint64_t max_pairs,
+                                                 uint64_t *status) {
   extern __shared__ uint32_t lc[];
   const uint32_t nt = c.tiles_x * c.tiles_y;
+  for (uint32_t t = blockIdx.x * BW + threadIdx.x; t < nt; t += gridDim.x * BW) {
+    const uint32_t b = slice_off[t], e = slice_off[t + 1];
+    const uint32_t p = tile_off[t], cnt = tile_off[t + 1] - p;
+    for (uint32_t k = 0; b + k < e && b + k < max_slices; ++k)
+      table[b + k] = make_uint2(p + k * lodh::SPLAT_SLICE,
+                                t | (min(cnt - k * lodh::SPLAT_SLICE, lodh::SPLAT_SLICE) << 16));
+  }
   if (tile_off[nt] > max_pairs) {
     if (threadIdx.x == 0) atomicOr((unsigned long long *)status, (unsigned long long)LOD_STATUS_CAPACITY);
     return;
   }
   const uint32_t u0 = blockIdx.x * g;
-  const uint32_t ch = u0 / 64;
-  for (uint32_t i = threadIdx.x; i < nt; i += BW)
-    lc[i] = tile_off[i] + pchunk[(uint64_t)ch * nt + i] + ucount[(uint64_t)u0 * nt + i];
-  __syncthreads();
-  bin_unit<Src, true, uint32_t, RecT>(src, c, units, u0, g, nbits, lc, rec);
-}
-
-// slices per tile
-__global__ void k_slice_count(const uint32_t *__restrict__ tile_count, uint32_t nt, uint32_t *__restrict__ ns) {
-  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += gridDim.x * blockDim.x)
-    ns[t] = (tile_count[t] + lodh::SPLAT_SLICE - 1) / lodh::SPLAT_SLICE;
-}
-
-// Slice descriptors: (first pair, tile | pairs << 16), one per slice.
-__global__ void k_slice_table(const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ tile_count,
-                              const uint32_t *__restrict__ slice_off, uint32_t nt, uint2 *__restrict__ table,
-                              uint64_t max_slices) {
-  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += gridDim.x * blockDim.x) {
-    const uint32_t b = slice_off[t], e = slice_off[t + 1], c = tile_count[t];
-    for (uint32_t k = 0; b + k < e && b + k < max_slices; ++k) {
-      const uint32_t n = min(c - k * lodh::SPLAT_SLICE, lodh::SPLAT_SLICE);
-      table[b + k] = make_uint2(tile_off[t] + k * lodh::SPLAT_SLICE, t | (n << 16));
-    }
+  const uint32_t *pre = pchunk ? pchunk + (uint64_t)(u0 / 64) * nt : nullptr;   // null: one chunk
+  uint32_t *row = ucount + (uint64_t)u0 * nt;
+  if constexpr (LDS) {
+    for (uint32_t i = threadIdx.x; i < nt; i += BW) lc[i] = tile_off[i] + (pre ? pre[i] : 0u) + row[i];
+    __syncthreads();
+    bin_unit<Src, true, LdsTab<uint32_t>, RecT>(src, c, units, u0, g, nbits, LdsTab<uint32_t>{lc}, rec);
+  } else {
+    bin_unit<Src, true, RowTab, RecT>(src, c, units, u0, g, nbits, RowTab{row, tile_off, pre}, rec);
   }
 }
 
@@ -898,7 +1136,16 @@ __global__ __launch_bounds__(PT) void k_finalize(const uint32_t *__restrict__ sl
   for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
     const uint32_t b = slice_off[t], e = slice_off[t + 1];
     float s = 0.0f, cc = 0.0f;
-    for (uint32_t sl = b; sl < e && sl < max_slices; ++sl) neumaier(s, cc, partial[(uint64_t)sl * (TS * TS) + threadIdx.x]);
+    // (a tile in front of a dense clump has a thousand slices: eight are loaded together)
+    const uint32_t e1 = (uint32_t)min((uint64_t)e, max_slices);
+    for (uint32_t sl = b; sl < e1; sl += 8) {
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = partial[(uint64_t)min(sl + k, e1 - 1) * (TS * TS) + threadIdx.x];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (sl + k < e1) neumaier(s, cc, v[k]);
+    }
     const int i = (int)(t % c.tiles_x) * TS + (threadIdx.x % TS);
     const int j = (int)(t / c.tiles_x) * TS + (threadIdx.x / TS);
     if (i < (int)c.W && j < (int)c.H) image[(uint64_t)j * c.W + i] = s + cc;
@@ -1316,32 +1563,55 @@ __global__ void k_set_points(const lod_tree t, uint32_t v, const float *__restri
 
 // --- LOD decode ----------------------------------------------------------------
 
-__global__ void k_lod_counts(const lod_tree t, const uint32_t *__restrict__ ids, const uint64_t *__restrict__ n_ids,
-                             uint64_t max_ids, uint64_t *__restrict__ offs) {
-  const uint64_t nn = t.counts[0];
+// Exclusive offsets of the listed nodes' points: block b scans ids
+// [LOFF b, LOFF (b + 1)), one id past the last one included, and the scan of
+// the blocks' totals (k_lod_total) is added where an offset is read (lod_off).
+// Ids past the node count hold no points; blocks past the list write nothing.
+// (One block walking the whole list took 56 us for the 33 k nodes of a 150 M
+// particle cut; these two launches take 9.)
+__global__ __launch_bounds__(LOFF) void k_lod_offsets(const lod_tree t, const uint32_t *__restrict__ ids,
+                                                      const uint64_t *__restrict__ n_ids, uint64_t max_ids,
+                                                      uint64_t *__restrict__ offs, uint64_t *__restrict__ bsum) {
+  __shared__ uint64_t tmp[LOFF / WAVE + 1];
   const uint64_t ni = min(*n_ids, max_ids);
-  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k <= max_ids;
-       k += (uint64_t)gridDim.x * blockDim.x) {
-    uint64_t c = 0;
-    if (k < ni) {
-      const uint32_t v = ids[k];
-      if (v < nn) c = t.pt_count[v];
-    }
-    offs[k] = c;
+  const uint64_t k = (uint64_t)blockIdx.x * LOFF + threadIdx.x;
+  if ((uint64_t)blockIdx.x * LOFF > ni) return;
+  uint64_t c = 0;
+  if (k < ni) {
+    const uint32_t v = ids[k];
+    if (v < t.counts[0]) c = t.pt_count[v];
   }
+  uint64_t total;
+  const uint64_t o = block_excl_scan<uint64_t>(c, tmp, total);
+  if (k <= ni) offs[k] = o;
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-// offs[max_ids] holds the total after the scan.
-__global__ void k_lod_total(const lod_tree t, const uint64_t *__restrict__ offs, uint64_t max_ids,
-                            uint64_t max_points, uint64_t *__restrict__ total) {
-  const uint64_t tot = offs[max_ids];
-  *total = min(tot, max_points);
-  if (tot > max_points) atomicOr((unsigned long long *)&t.counts[2], (unsigned long long)LOD_STATUS_CAPACITY);
+// scan of the block totals (in place) and the number of points drawn (one block)
+__global__ __launch_bounds__(LOFF) void k_lod_total(const lod_tree t, const uint64_t *__restrict__ n_ids,
+                                                    uint64_t max_ids, uint64_t *__restrict__ bsum,
+                                                    uint64_t max_points, uint64_t *__restrict__ total) {
+  __shared__ uint64_t tmp[LOFF / WAVE + 1];
+  const uint64_t nb = min(*n_ids, max_ids) / LOFF + 1;
+  uint64_t run = 0;
+  for (uint64_t b0 = 0; b0 < nb; b0 += LOFF) {
+    const uint64_t b = b0 + threadIdx.x;
+    uint64_t step;
+    const uint64_t o = block_excl_scan<uint64_t>(b < nb ? bsum[b] : 0ull, tmp, step);
+    if (b < nb) bsum[b] = run + o;
+    run += step;
+  }
+  if (threadIdx.x == 0) {
+    *total = min(run, max_points);
+    if (run > max_points)
+      atomicOr((unsigned long long *)&t.counts[2], (unsigned long long)LOD_STATUS_CAPACITY);
+  }
 }
 
 __global__ __launch_bounds__(PT) void k_lod_decode(const lod_tree t, const uint32_t *__restrict__ ids,
                                                    const uint64_t *__restrict__ n_ids, uint64_t max_ids,
-                                                   const uint64_t *__restrict__ offs, uint64_t max_points,
+                                                   const uint64_t *__restrict__ offs,
+                                                   const uint64_t *__restrict__ bsum, uint64_t max_points,
                                                    float *__restrict__ x, float *__restrict__ y,
                                                    float *__restrict__ z, float *__restrict__ m) {
   const uint64_t nn = t.counts[0];
@@ -1355,7 +1625,7 @@ __global__ __launch_bounds__(PT) void k_lod_decode(const lod_tree t, const uint3
     const uint32_t cx = compact3(cell), cy = compact3(cell >> 1), cz = compact3(cell >> 2);
     const uint64_t pb = t.pt_begin[v];
     const uint32_t pc = t.pt_count[v];
-    const uint64_t ob = offs[k];
+    const uint64_t ob = lod_off(offs, bsum, k);
     for (uint32_t j = threadIdx.x; j < pc; j += PT) {
       const uint64_t o = ob + j;
       if (o >= max_points) break;
@@ -1396,43 +1666,60 @@ __device__ __forceinline__ bool descends(const lod_tree &t, uint32_t v, const Cu
   return c.F * side > c.tau_cbrt * dist;
 }
 
-__global__ void k_cut_flags(const lod_tree t, CutArgs c, uint64_t cap_nodes, uint32_t *__restrict__ flag) {
+// Drawn nodes of one block of CUT_T nodes: keep[v] = 1 + rank among the block's
+// drawn nodes, or 0, and the block's number of drawn nodes.
+constexpr int CUT_T = 1024;
+__global__ __launch_bounds__(CUT_T) void k_cut_flags(const lod_tree t, CutArgs c, uint64_t cap_nodes,
+                                                     uint32_t *__restrict__ keep, uint32_t *__restrict__ sums) {
+  __shared__ uint32_t tmp[CUT_T / WAVE + 1];
   const uint64_t nn = min(t.counts[0], cap_nodes);
-  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v <= cap_nodes;
-       v += (uint64_t)gridDim.x * blockDim.x) {
-    uint32_t f = 0;
-    if (v < nn && !descends(t, (uint32_t)v, c)) {
-      f = 1;
-      uint32_t u = t.parent[v];
-      while (u != NONE) {
-        if (!descends(t, u, c)) { f = 0; break; }
-        u = t.parent[u];
-      }
-    }
-    flag[v] = f;
-  }
-}
-
-__global__ void k_cut_write(const lod_tree t, uint64_t cap_nodes, const uint32_t *__restrict__ keep,
-                            const uint32_t *__restrict__ scan, uint32_t *__restrict__ ids, uint64_t cap,
-                            uint64_t *__restrict__ n_sel) {
-  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < cap_nodes;
-       v += (uint64_t)gridDim.x * blockDim.x) {
-    if (keep[v]) {
-      const uint32_t o = scan[v];
-      if (o < cap) ids[o] = (uint32_t)v;
+  const uint64_t v = (uint64_t)blockIdx.x * CUT_T + threadIdx.x;
+  if ((uint64_t)blockIdx.x * CUT_T >= nn) return;   // uniform; k_cut_write reads no further than nn
+  uint32_t f = 0;
+  if (v < nn && !descends(t, (uint32_t)v, c)) {
+    f = 1;
+    uint32_t u = t.parent[v];
+    while (u != NONE) {
+      if (!descends(t, u, c)) { f = 0; break; }
+      u = t.parent[u];
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const uint64_t tot = scan[cap_nodes];
-    *n_sel = min(tot, cap);
-    if (tot > cap) atomicOr((unsigned long long *)&t.counts[2], (unsigned long long)LOD_STATUS_CAPACITY);
-  }
+  uint32_t total;
+  const uint32_t rank = block_excl_scan<uint32_t>(f, tmp, total);
+  if (v < nn) keep[v] = f ? rank + 1u : 0u;
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-__global__ void k_copy_u32(const uint32_t *__restrict__ a, uint32_t *__restrict__ b, uint64_t n) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    b[i] = a[i];
+// The drawn nodes in node order: a block adds up the blocks before it itself
+// (at most some hundreds), which saves the launches of a scan.
+__global__ __launch_bounds__(CUT_T) void k_cut_write(const lod_tree t, uint64_t cap_nodes,
+                                                     const uint32_t *__restrict__ keep,
+                                                     const uint32_t *__restrict__ sums, uint32_t *__restrict__ ids,
+                                                     uint64_t cap, uint64_t *__restrict__ n_sel) {
+  __shared__ uint64_t tmp[CUT_T / WAVE + 1];
+  const uint64_t nn = min(t.counts[0], cap_nodes);
+  const uint32_t nb = (uint32_t)((nn + CUT_T - 1) / CUT_T);   // blocks that hold nodes
+  if (blockIdx.x >= max(nb, 1u)) return;
+  uint64_t before = 0, all = 0;
+  for (uint32_t b = threadIdx.x; b < nb; b += CUT_T) {
+    const uint32_t s = sums[b];
+    if (b < blockIdx.x) before += s;
+    all += s;
+  }
+  before = block_reduce_sum<uint64_t>(before, tmp);
+  const uint64_t v = (uint64_t)blockIdx.x * CUT_T + threadIdx.x;
+  const uint32_t k = v < nn ? keep[v] : 0u;
+  if (k) {
+    const uint64_t o = before + k - 1u;
+    if (o < cap) ids[o] = (uint32_t)v;
+  }
+  if (blockIdx.x == 0) {
+    all = block_reduce_sum<uint64_t>(all, tmp);
+    if (threadIdx.x == 0) {
+      *n_sel = min(all, cap);
+      if (all > cap) atomicOr((unsigned long long *)&t.counts[2], (unsigned long long)LOD_STATUS_CAPACITY);
+    }
+  }
 }
 
 }  // namespace
@@ -1451,7 +1738,7 @@ static size_t rec_bytes(const splat_params &sp, bool aux) {
 }
 
 lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_params &sp, SplatLayout &L,
-                        bool aux) {
+                        bool aux, bool few_units) {
   L = SplatLayout{};
   L.tiles_x = (cam.W + TS - 1) / TS;
   L.tiles_y = (cam.H + TS - 1) / TS;
@@ -1470,17 +1757,21 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   L.aux = aux;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-  // units: 64 per chunk, one chunk per 2^17 points (units of at most 2048
-  // points until the 64-chunk cap: a million points are binned by 512
-  // waves; 150 M by 4096 units of at most 36.6 k points)
-  L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (max_points + (1u << 17) - 1) >> 17));
+  // Units: 64 per chunk.  A unit's row of the count table is written, scanned
+  // and read, so a unit holds at least half as many points as there are tiles
+  // (8 bytes of table per point), but no more than 2048 while there are fewer
+  // than 4096 units (150 M points: 4096 units of 36.6 k points; a 256x256
+  // image of 262 k points: 2048 units of 128, where units of 2048 left 128
+  // waves on the chip).  few_units (a workspace of fixed size): 2048 always.
+  const uint64_t unit = few_units ? 2048 : std::min<uint64_t>(2048, std::max<uint64_t>(128, nt / 2));
+  L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS,
+                                          std::max<uint64_t>(1, (max_points + 64 * unit - 1) / (64 * unit)));
   L.units = 64 * L.chunks;
   L.tile_count = take(4 * (nt + 1));
   L.tile_off = take(4 * (nt + 1));
   L.ucount = take(4 * (size_t)L.units * nt);
   L.pchunk = take(4 * (size_t)L.chunks * nt);
   L.slice_off = take(4 * (nt + 1));
-  L.scan_tmp = take(4 * scan_tmp_elems<uint32_t>(nt + 1));
   L.counters = take(64);
   L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
   L.partial = take(4 * (size_t)TS * TS * L.max_slices);
@@ -1509,57 +1800,57 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
   uint32_t *ucount = (uint32_t *)(W + L.ucount);
   uint32_t *pchunk = (uint32_t *)(W + L.pchunk);
   uint32_t *soff = (uint32_t *)(W + L.slice_off);
-  uint32_t *stmp = (uint32_t *)(W + L.scan_tmp);
   uint64_t *ctr = (uint64_t *)(W + L.counters);
   uint64_t *status = status_word ? status_word : ctr;
   RecT *rec = (RecT *)(W + L.rec);
   float *partial = (float *)(W + L.partial);
   float *partial_aux = (float *)(W + L.partial_aux);
+  uint2 *stab = (uint2 *)(W + L.slice_table);
   int nbits = 0;
   while ((1u << nbits) < nt) ++nbits;
-  fill_u32(tcount, nt + 1, 0, st);
-  if (!status_word) fill_u64(ctr, 1, 0, st);
   const size_t lds = 4 * (size_t)nt;
+  // Counters and cursors in the rows of the count table for points in Morton
+  // order (a tree's): their rounds stay in one window for long, and the waves
+  // per CU are not limited by LDS.  In LDS for arrays in the caller's order,
+  // which may be random, once a unit's points outnumber the initialisation of
+  // its LDS row.
+  const uint64_t per = (L.max_points + L.units - 1) / L.units;
+  const bool rows = IsTree<Src>::value || per < nt / 8;
+  const uint32_t *pre = L.chunks > 1 ? pchunk : nullptr;
   if (any) {
-    const bool narrow_counts = (L.max_points + L.units - 1) / L.units <= 65535;
-    bool staged = false;
+    const bool narrow_counts = per + WAVE <= 65535;
+    auto count = [&](auto kernel, size_t bytes, const HlStage &h) {
+      LOD_LAUNCH_NAMED("k_bin_count", kernel, dim3(L.units), dim3(BW), bytes, st, src, c, L.units, nbits, ucount, h);
+    };
     if constexpr (IsTree<Src>::value) {
-      if (hs) {
-        staged = true;
-        if (narrow_counts)
-          LOD_LAUNCH((k_bin_count<Src, uint16_t, true>), dim3(L.units), dim3(BW), 2 * (size_t)nt, st, src, c,
-                     L.units, nbits, ucount, *hs);
-        else
-          LOD_LAUNCH((k_bin_count<Src, uint32_t, true>), dim3(L.units), dim3(BW), lds, st, src, c, L.units, nbits,
-                     ucount, *hs);
-      }
+      if (hs) count(k_bin_count<Src, void, true>, 0, *hs);
+      else count(k_bin_count<Src, void>, 0, HlStage{});
+    } else {
+      if (rows) count(k_bin_count<Src, void>, 0, HlStage{});
+      else if (narrow_counts) count(k_bin_count<Src, uint16_t>, 2 * (size_t)(nt + 1), HlStage{});
+      else count(k_bin_count<Src, uint32_t>, lds, HlStage{});
     }
-    if (!staged) {
-      if (narrow_counts)
-        LOD_LAUNCH((k_bin_count<Src, uint16_t>), dim3(L.units), dim3(BW), 2 * (size_t)nt, st, src, c, L.units,
-                   nbits, ucount, HlStage{});
-      else
-        LOD_LAUNCH((k_bin_count<Src, uint32_t>), dim3(L.units), dim3(BW), lds, st, src, c, L.units, nbits, ucount,
-                   HlStage{});
-    }
-    LOD_LAUNCH(k_bin_colscan, dim3((nt + 255) / 256, L.chunks), dim3(256), 0, st, ucount, nt, pchunk);
-    LOD_LAUNCH(k_bin_chunkscan, dim3((nt + 255) / 256), dim3(256), 0, st, pchunk, nt, L.chunks, tcount);
+    LOD_LAUNCH(k_bin_colscan, dim3((nt + 255) / 256, L.chunks), dim3(256), 0, st, ucount, nt,
+               L.chunks > 1 ? pchunk : tcount);
+    if (L.chunks > 1)
+      LOD_LAUNCH(k_bin_chunkscan, dim3((nt + 255) / 256), dim3(256), 0, st, pchunk, nt, L.chunks, tcount);
   }
-  // tile offsets (exclusive; toff[nt] = pairs), slices
-  LOD_LAUNCH(k_copy_u32, dim3((nt + 256) / 256), dim3(256), 0, st, tcount, toff, (uint64_t)nt + 1);
-  device_scan<uint32_t>(toff, nt + 1, stmp, st);
+  LOD_LAUNCH(k_tile_plan, dim3(1), dim3(PLAN_T), 0, st, any ? tcount : (uint32_t *)nullptr, nt, toff, soff,
+             status_word ? (uint64_t *)nullptr : ctr);
   if (any) {
-    // fill blocks of two units when there are many (32-bit cursors take twice
-    // the LDS of the 16-bit counts: fewer resident waves)
-    const uint32_t g = L.units >= 4096 ? 2u : 1u;
-    LOD_LAUNCH((k_bin_fill<Src, RecT>), dim3(L.units / g), dim3(BW), lds, st, src, c, L.units, g, nbits, ucount,
-               pchunk, toff, rec, L.max_pairs, status);
+    auto fill = [&](auto kernel, uint32_t g, size_t bytes) {
+      LOD_LAUNCH_NAMED("k_bin_fill", kernel, dim3(L.units / g), dim3(BW), bytes, st, src, c, L.units, g, nbits,
+                       ucount, pre, toff, soff, stab, L.max_slices, rec, L.max_pairs, status);
+    };
+    // with cursors in LDS, blocks of two units when there are many (32-bit
+    // cursors take twice the LDS of the 16-bit counts: fewer resident waves)
+    if constexpr (IsTree<Src>::value) {
+      fill(k_bin_fill<Src, RecT, false>, 1u, 0);
+    } else {
+      if (rows) fill(k_bin_fill<Src, RecT, false>, 1u, 0);
+      else fill(k_bin_fill<Src, RecT, true>, L.units >= 4096 ? 2u : 1u, lds);
+    }
   }
-  LOD_LAUNCH(k_slice_count, dim3((nt + 255) / 256), dim3(256), 0, st, tcount, nt, soff);
-  fill_u32(soff + nt, 1, 0, st);
-  device_scan<uint32_t>(soff, nt + 1, stmp, st);
-  uint2 *stab = (uint2 *)(W + L.slice_table);
-  LOD_LAUNCH(k_slice_table, dim3((nt + 255) / 256), dim3(256), 0, st, toff, tcount, soff, nt, stab, L.max_slices);
   const unsigned agrid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(16384, L.max_slices));
   if (any) {
     if constexpr (RecInfo<RecT>::cubic) {
@@ -1616,6 +1907,14 @@ lod_status launch_splat_interp(const InterpArgs &a, const lod_camera &cam, const
   return splat_any(src, a.count > 0, cam, sp, ws, L, image, image_color, nullptr, st);
 }
 
+// Offsets of the listed nodes' points and the number of points drawn.
+static void lod_offsets(const lod_tree &tree, const uint32_t *node_ids, const uint64_t *n_ids, uint64_t max_ids,
+                        uint64_t *offs, uint64_t *bsum, uint64_t max_points, uint64_t *total, hipStream_t st) {
+  LOD_LAUNCH(k_lod_offsets, dim3((unsigned)(max_ids / LOFF + 1)), dim3(LOFF), 0, st, tree, node_ids, n_ids, max_ids,
+             offs, bsum);
+  LOD_LAUNCH(k_lod_total, dim3(1), dim3(LOFF), 0, st, tree, n_ids, max_ids, bsum, max_points, total);
+}
+
 lod_status launch_encode_motion(const lod_tree &tree, const float *xb, const float *yb, const float *zb,
                                 const uint64_t *snap_off, int16_t *dqx, int16_t *dqy, int16_t *dqz,
                                 uint64_t *saturated, hipStream_t st) {
@@ -1633,11 +1932,9 @@ lod_status launch_splat_lod_motion(const lod_tree &tree, const uint32_t *node_id
   char *W = (char *)ws;
   uint64_t *offs = (uint64_t *)(W + D.offs);
   uint64_t *cnt = (uint64_t *)(W + D.count);
-  const unsigned g = (unsigned)std::min<uint64_t>(4096, (D.max_ids + 256) / 256);
-  LOD_LAUNCH(k_lod_counts, dim3(g), dim3(256), 0, st, tree, node_ids, n_ids, D.max_ids, offs);
-  device_scan<uint64_t>(offs, D.max_ids + 1, (uint64_t *)(W + D.scan_tmp), st);
-  LOD_LAUNCH(k_lod_total, dim3(1), dim3(1), 0, st, tree, offs, D.max_ids, D.max_points, cnt);
-  TreeMotionSrc src{tree, node_ids, offs, n_ids, D.max_ids, cnt};
+  uint64_t *bsum = (uint64_t *)(W + D.bsum);
+  lod_offsets(tree, node_ids, n_ids, D.max_ids, offs, bsum, D.max_points, cnt, st);
+  TreeMotionSrc src{tree, node_ids, offs, bsum, n_ids, D.max_ids, cnt};
   src.dqx = dqx; src.dqy = dqy; src.dqz = dqz;
   src.t_frame = t;
   return splat_any(src, true, cam, sp, W + D.total, L, image, nullptr, tree.counts + 2, st);
@@ -1671,7 +1968,7 @@ LodDrawLayout lod_draw_layout(uint64_t node_capacity, uint64_t max_points) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   L.offs = take(8 * (L.max_ids + 1));
-  L.scan_tmp = take(8 * scan_tmp_elems<uint64_t>(L.max_ids + 1));
+  L.bsum = take(8 * (L.max_ids / LOFF + 1));
   L.count = take(64);
   L.total = off;
   return L;
@@ -1710,11 +2007,9 @@ lod_status launch_splat_lod(const lod_tree &tree, const uint32_t *node_ids, cons
   char *W = (char *)ws;
   uint64_t *offs = (uint64_t *)(W + D.offs);
   uint64_t *cnt = (uint64_t *)(W + D.count);
-  const unsigned g = (unsigned)std::min<uint64_t>(4096, (D.max_ids + 256) / 256);
-  LOD_LAUNCH(k_lod_counts, dim3(g), dim3(256), 0, st, tree, node_ids, n_ids, D.max_ids, offs);
-  device_scan<uint64_t>(offs, D.max_ids + 1, (uint64_t *)(W + D.scan_tmp), st);
-  LOD_LAUNCH(k_lod_total, dim3(1), dim3(1), 0, st, tree, offs, D.max_ids, D.max_points, cnt);
-  TreeSrc src{tree, node_ids, offs, n_ids, D.max_ids, cnt};
+  uint64_t *bsum = (uint64_t *)(W + D.bsum);
+  lod_offsets(tree, node_ids, n_ids, D.max_ids, offs, bsum, D.max_points, cnt, st);
+  TreeSrc src{tree, node_ids, offs, bsum, n_ids, D.max_ids, cnt};
   if (!H) return splat_any(src, true, cam, sp, W + D.total, L, image, nullptr, tree.counts + 2, st);
   // ID highlighting: the count pass of the main render tests every drawn
   // point's flag and stages the flagged ones; they are gathered in unit
@@ -1740,7 +2035,7 @@ lod_status launch_splat_lod(const lod_tree &tree, const uint32_t *node_ids, cons
 
 size_t decode_workspace(uint64_t node_capacity) {
   const uint64_t n = std::max<uint64_t>(1, node_capacity);
-  return align256(8 * (n + 1)) + align256(8 * scan_tmp_elems<uint64_t>(n + 1));
+  return align256(8 * (n + 1)) + align256(8 * (n / LOFF + 1));
 }
 
 lod_status launch_decode(const lod_tree &tree, const uint32_t *node_ids, const uint64_t *n_ids, uint64_t max_points,
@@ -1748,19 +2043,16 @@ lod_status launch_decode(const lod_tree &tree, const uint32_t *node_ids, const u
   const uint64_t max_ids = std::max<uint64_t>(1, tree.node_capacity);
   char *W = (char *)ws;
   uint64_t *offs = (uint64_t *)W;
-  uint64_t *tmp = (uint64_t *)(W + align256(8 * (max_ids + 1)));
-  const unsigned g = (unsigned)std::min<uint64_t>(4096, (max_ids + 256) / 256);
-  LOD_LAUNCH(k_lod_counts, dim3(g), dim3(256), 0, st, tree, node_ids, n_ids, max_ids, offs);
-  device_scan<uint64_t>(offs, max_ids + 1, tmp, st);
-  LOD_LAUNCH(k_lod_total, dim3(1), dim3(1), 0, st, tree, offs, max_ids, max_points, n_points);
+  uint64_t *bsum = (uint64_t *)(W + align256(8 * (max_ids + 1)));
+  lod_offsets(tree, node_ids, n_ids, max_ids, offs, bsum, max_points, n_points, st);
   const unsigned dg = (unsigned)std::min<uint64_t>(16384, max_ids);
-  LOD_LAUNCH(k_lod_decode, dim3(dg), dim3(PT), 0, st, tree, node_ids, n_ids, max_ids, offs, max_points, x, y, z, m);
+  LOD_LAUNCH(k_lod_decode, dim3(dg), dim3(PT), 0, st, tree, node_ids, n_ids, max_ids, offs, bsum, max_points, x, y, z, m);
   return hipGetLastError() == hipSuccess ? LOD_OK : LOD_EDEVICE;
 }
 
 size_t cut_workspace(uint64_t node_capacity) {
   const uint64_t n = std::max<uint64_t>(1, node_capacity) + 1;
-  return align256(4 * n) * 2 + align256(4 * scan_tmp_elems<uint32_t>(n));
+  return align256(4 * n) + align256(4 * ((n + CUT_T - 1) / CUT_T));
 }
 
 lod_status launch_cut(const lod_tree &tree, const lod_camera &cam, float tau_px, uint32_t n, uint32_t *node_ids,
@@ -1768,18 +2060,15 @@ lod_status launch_cut(const lod_tree &tree, const lod_camera &cam, float tau_px,
   const uint64_t nc = std::max<uint64_t>(1, tree.node_capacity);
   char *W = (char *)ws;
   uint32_t *keep = (uint32_t *)W;
-  uint32_t *scan = (uint32_t *)(W + align256(4 * (nc + 1)));
-  uint32_t *tmp = (uint32_t *)(W + 2 * align256(4 * (nc + 1)));
+  uint32_t *sums = (uint32_t *)(W + align256(4 * (nc + 1)));
   CutArgs c{};
   c.proj = cam.projection; c.W = cam.W;
   c.px = (double)cam.pos[0]; c.py = (double)cam.pos[1]; c.pz = (double)cam.pos[2];
   c.F = (double)cam.F;
   c.tau_cbrt = (double)tau_px * std::cbrt((double)n);
-  const unsigned g = (unsigned)std::min<uint64_t>(4096, (nc + 256) / 256);
-  LOD_LAUNCH(k_cut_flags, dim3(g), dim3(256), 0, st, tree, c, nc, keep);
-  LOD_LAUNCH(k_copy_u32, dim3(g), dim3(256), 0, st, keep, scan, nc + 1);
-  device_scan<uint32_t>(scan, nc + 1, tmp, st);
-  LOD_LAUNCH(k_cut_write, dim3(g), dim3(256), 0, st, tree, nc, keep, scan, node_ids, cap, n_selected);
+  const unsigned g = (unsigned)((nc + CUT_T - 1) / CUT_T);
+  LOD_LAUNCH(k_cut_flags, dim3(g), dim3(CUT_T), 0, st, tree, c, nc, keep, sums);
+  LOD_LAUNCH(k_cut_write, dim3(g), dim3(CUT_T), 0, st, tree, nc, keep, sums, node_ids, cap, n_selected);
   return hipGetLastError() == hipSuccess ? LOD_OK : LOD_EDEVICE;
 }
 

@@ -55,6 +55,9 @@ lod_status splat_render_noalloc(const float *x, const float *y, const float *z, 
   lodh::SplatLayout L;
   lod_status s = lodh::splat_layout(count, *cam, *sp, L, false);
   if (s != LOD_OK) return s;
+  // near the limit with fewer, larger binning units: the image is the same
+  if (L.total > (size_t)LOD_NOALLOC_SCRATCH_BYTES) s = lodh::splat_layout(count, *cam, *sp, L, false, true);
+  if (s != LOD_OK) return s;
   if (L.total > (size_t)LOD_NOALLOC_SCRATCH_BYTES) return LOD_ECAPACITY;
   void *ws = nullptr;
   if ((s = scratch_for_current_device(&ws)) != LOD_OK) return s;

@@ -51,3 +51,10 @@ struct TraceScope {
     ::lodh::TraceScope lod_trace_scope_(#kernel, (stream));               \
     hipLaunchKernelGGL(kernel, grid, block, shmem, stream, __VA_ARGS__);  \
   } while (0)
+
+// The same for a kernel chosen by value, under the name given.
+#define LOD_LAUNCH_NAMED(name, kernel, grid, block, shmem, stream, ...)   \
+  do {                                                                    \
+    ::lodh::TraceScope lod_trace_scope_(name, (stream));                  \
+    hipLaunchKernelGGL(kernel, grid, block, shmem, stream, __VA_ARGS__);  \
+  } while (0)

@@ -510,7 +510,7 @@ def select_nodes(tree: Tree, cam: Camera, tau_px: float, n: int, cap: int | None
     if workspace is None or workspace.numel() < ws.value:
         workspace = torch.empty(max(ws.value, 256), dtype=torch.uint8, device=dev)
     ids = torch.empty(max(cap, 1), dtype=torch.uint32, device=dev)
-    nsel = torch.zeros(1, dtype=torch.uint64, device=dev)
+    nsel = torch.empty(1, dtype=torch.uint64, device=dev)      # written by the call
     camc = cam.c()
     _check(lib.lod_select(C.byref(tree.c()), C.byref(camc), float(tau_px), int(n), _ptr(ids), cap,
                           _ptr(nsel), _ptr(workspace), ws.value, _stream()), "lod_select")

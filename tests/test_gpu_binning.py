@@ -1,0 +1,73 @@
+"""The binning of points to tiles at its edges: rounds of 64 points that lie in
+one 8x8 tile window, rounds that change windows, rounds spread over the image,
+blobs several tiles wide; cuts and draw lists at the edges of their blocks.
+Images against the float64 oracle within 1e-5 per pixel."""
+import numpy as np
+import pytest
+
+from gpu_util import image_rel_err, to_dev
+from oracle import cubic as ocubic
+from oracle import cut as ocut
+from oracle import lod as olod
+from oracle import splat as osplat
+from paper_0811_2055_amd import lib
+import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _points(order, n, seed):
+    s = synth.small_clustered(n, seed)
+    if order == "morton":
+        key = olod.interleave(*(olod.cell_coords(a, 10) for a in (s.x, s.y, s.z)), 10)
+        o = np.argsort(key, kind="stable")
+    elif order == "corners":          # every round holds points of all four corners
+        o = np.arange(n)
+        s.x[:] = np.where(o & 1, 0.02, 0.98) + (s.x - 0.5) * 0.03
+        s.y[:] = np.where(o & 2, 0.02, 0.98) + (s.y - 0.5) * 0.03
+    elif order == "jumps":            # a window holds one round and not the next
+        o = np.arange(n)
+        s.x[:] = np.where((o // 64) & 1, 0.1, 0.9) + (s.x - 0.5) * 0.05
+    else:
+        o = np.arange(n)
+    return [np.ascontiguousarray(a[o]) for a in (s.x, s.y, s.z, s.m)]
+
+
+@pytest.mark.parametrize("order", ["morton", "random", "corners", "jumps"])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 4097, 70001])
+@pytest.mark.parametrize("blob", ["narrow", "wide", "cubic"])
+def test_image_over_orders(order, n, blob):
+    import torch
+    W, H = 200, 136                   # 13 x 9 tiles: windows cut by both edges
+    cam, ocam = lib.Camera.ortho(W, H), osplat.Camera(0, W, H)
+    p = _points(order, n, 11 + n)
+    d = [torch.from_numpy(a).cuda() for a in p]
+    if blob == "cubic":
+        img = lib.splat(*d, cam, blob=lib.Blob.cubic(h_px=16.0 if n < 5000 else 4.5)).cpu().numpy()
+        ref = ocubic.render(ocam, *p, h_px=16.0 if n < 5000 else 4.5)
+    else:
+        sigma, rad = (1.0, 3.0) if blob == "narrow" else (8.0, 6.0 if n < 5000 else 2.0)
+        img = lib.splat(*d, cam, sigma, rad).cpu().numpy()
+        ref = osplat.render(ocam, *p, sigma, rad)
+    err, zeros_ok = image_rel_err(img, ref)
+    assert zeros_ok and err <= TOL, err
+
+
+@pytest.mark.parametrize("n,depth", [(1, 1), (2, 6), (1, 7)])
+def test_cut_and_draw_list_over_block_edges(n, depth):
+    """Trees of a few nodes and of several 1024-node cut blocks and 1024-id
+    offset blocks: the cut equals the oracle's, the render its points' render."""
+    s = synth.small_clustered(60000, 5)
+    ref = olod.lod_build(s.x, s.y, s.z, s.m, n=n, D=depth, seed=1)
+    tree = lib.build(*to_dev(s), lib.BuildParams(n=n, max_depth=depth, seed=1))
+    cam, ocam = lib.Camera.ortho(128, 128), osplat.Camera(0, 128, 128)
+    for tau in (0.01, 1.0, 60.0):
+        ids, nsel = lib.select_nodes(tree, cam, tau, n)
+        k = int(lib._to_numpy(nsel)[0])
+        want = ocut.select(ref, ocam, tau, n)
+        assert np.array_equal(lib._to_numpy(ids[:k]).astype(np.int64), want), (tau, k, len(want))
+        img = lib.splat_lod(tree, ids, nsel, tree.point_capacity, cam).cpu().numpy()
+        px, py, pz, pm = olod.decoded_points(ref, want)
+        err, zeros_ok = image_rel_err(img, osplat.render(ocam, px, py, pz, pm))
+        assert zeros_ok and err <= TOL, (tau, err)
