@@ -1183,14 +1183,43 @@ __device__ __forceinline__ void load_rec(const RecCA *r, uint64_t q, float &u, f
   u = t.u; v = t.v; m = t.m; h = t.h; a = t.a;
 }
 
-// One block per slice (as the Gaussian accumulation); the spline is not
-// separable, so thread p owns pixel p of the 16x16 tile and gathers.  The
-// slice's records are staged in LDS 256 at a time (u, v, h, m as one 16-byte
-// entry, 1/h in float64 beside it); each wave runs through them in order and
-// skips a record whose blob misses its four pixel rows (a wave-uniform test),
-// so every pixel adds its contributions in record order: the image is
-// bit-reproducible.  Covered pixels form q = r / h from a float64 reciprocal
-// square root with one Newton step (relative error far below 1e-12).
+// One block per slice (as the Gaussian accumulation).  The spline is not
+// separable, so every covered pixel of every record is evaluated: a blob of
+// pixel radius h covers only pixels of the W x W window that starts at its
+// first admitted pixel, W = floor(2 h + 0.05) + 1 (the binning's conservative
+// range starts 1/100 pixel early, and the float32 rounding of the range stays
+// below the rest of the margin).  The lanes of a wave take (record, window
+// pixel) items:
+//   W <= 4   four records of 16 pixels each per step
+//   W == 5   two records of 32 lanes
+//   W == 6   the records' pixels end to end, 64 per step
+//   W <= 8   one record of 8 x 8 pixels per step
+//   larger   one record over all pixels of the tile, four rows per step
+// so that the lanes do the same work wherever the records lie.  A wave sorts
+// its 64 records by these classes in LDS (stable), each with the float64
+// factors every one of its pixels needs, and adds the contributions to tile
+// sums of its own in LDS (float64, one LDS add instruction per step).  Two
+// records that may cover one pixel in the same step go to different sums, or
+// are added by different instructions, and a wave's LDS instructions complete
+// in order: every sum is formed in an order fixed by the records, so the image
+// is bit-reproducible.  What bounds it is the issue of the float64 evaluation,
+// 54 vector instructions per step of 64 items (vector issue busy 68% of the
+// time, LDS 44%).
+//
+// Before, thread p owned pixel p and walked the records of a chunk that cover
+// it (narrow blobs), or all of them (radii that differ or exceed 3.9 pixels):
+// where a dense clump puts a whole chunk on a few pixels (an NFW core, all of
+// a Morton run), a few lanes walked while the block waited.  Accumulation of
+// 16.7 M NFW particles' cut at 1920x1080, h = 1.5 px: 856 -> 388 us; of 4 M
+// particles with world radii (1.3 to 2.5 px) and a colour channel: 2537 -> 447
+// us; of 1 M at h = 2.5 px: 175 -> 148 us.
+constexpr int CSUM = 2;              // tile sums per wave
+constexpr int CRS = TS + 2;          // their row stride in float64 (36 banks: a window's rows stay apart)
+constexpr int CTILE = TS * CRS;
+constexpr int NCLS = 5;
+
+__device__ __forceinline__ void lds_add_f64(double *p, double v) { unsafeAtomicAdd(p, v); }
+
 template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict__ table,
                                                          const uint32_t *__restrict__ slice_off, uint32_t nt,
@@ -1199,177 +1228,145 @@ __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict
                                                          float *__restrict__ partial_aux, uint64_t max_slices,
                                                          uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
-  __shared__ float4 sr[PT];           // u, v, h, m
-  __shared__ double sih[PT];          // 1 / h
-  __shared__ float sa[AUX ? PT : 1];
+  constexpr int NW = PT / WAVE;
+  constexpr int CH = AUX ? 2 : 1;                        // image channels
+  constexpr int U = AUX ? 2 : 1;                         // two channels leave room for half the waves
+  __shared__ double sum[NW][CSUM][CH][CTILE];
+  // a record: u, v, and either the centre of its window's first pixel or (a
+  // blob over the whole tile) of the tile's; 1 / h^2, m 40 / (7 pi h^2); h^2;
+  // that first pixel within the tile (int16 x, y)
+  __shared__ float4 sgeo[NW][WAVE];
+  __shared__ double2 sfac[NW][WAVE];
+  __shared__ double shh[NW][WAVE];
+  __shared__ uint32_t sorg[NW][WAVE];
+  __shared__ double sfaca[AUX ? NW : 1][AUX ? WAVE : 1]; // the same times the attribute
   const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
   if (blockIdx.x >= total_slices) return;
-  const int px = threadIdx.x % TS, py = threadIdx.x / TS;
-  const int wrow0 = (threadIdx.x / WAVE) * 4;      // a wave's first pixel row within the tile
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
   for (uint32_t sl = blockIdx.x; sl < total_slices; sl += gridDim.x) {
     const uint2 sd = table[sl];
     const uint32_t t = sd.y & 0xFFFFu;
     const uint64_t pb = sd.x;
     const uint64_t pe = min(pb + (sd.y >> 16), max_pairs);
     const int tx0 = (int)(t % c.tiles_x) * TS, ty0 = (int)(t / c.tiles_x) * TS;
-    const float cx = (float)(tx0 + px) + 0.5f, cy = (float)(ty0 + py) + 0.5f;   // exact pixel centres
-    const float rlo = (float)(ty0 + wrow0) + 0.5f, rhi = rlo + 3.0f;
-    float s = 0.0f, cs = 0.0f, s_a = 0.0f, c_a = 0.0f;
-    for (uint64_t c0 = pb; c0 < pe; c0 += PT) {
-      __syncthreads();                               // the previous chunk has been read
-      if (c0 + threadIdx.x < pe) {
-        float u, v, m, h, a;
-        load_rec(rec, c0 + threadIdx.x, u, v, m, h, a);
-        sr[threadIdx.x] = make_float4(u, v, h, m);
-        sih[threadIdx.x] = 1.0 / (double)h;
-        if (AUX) sa[threadIdx.x] = a;
-      }
-      __syncthreads();
-      const int nrec = (int)min((uint64_t)PT, pe - c0);
-      for (int k = 0; k < nrec; ++k) {
-        const float4 r = sr[k];
-        const float u = r.x, v = r.y, h = r.z;
-        // the blob covers |oy| < h: skip when it misses all four row centres
-        if (v + h + 0.01f < rlo || v - h - 0.01f > rhi) continue;
-        const float ox = u - cx, oy = v - cy;
-        const float r2f = ox * ox + oy * oy;
-        if (!(r2f < (h * h) * 1.001f)) continue;   // surely outside (float32 pre-test with margin)
-        const double h64 = (double)h;
-        const double hh = h64 * h64;
-        const double r2 = (double)ox * (double)ox + (double)oy * (double)oy;
-        if (!(r2 < hh)) continue;
-        double q = 0.0;
-        if (r2 > 0.0) {
-          double y = __builtin_amdgcn_rsq(r2);
-          y = y * (1.5 - (0.5 * r2) * (y * y));     // one Newton step
-          q = (r2 * y) * sih[k];
-        }
-        const double val = (double)r.w * (kCubicNorm / hh) * cubic_w(q);
-        neumaier(s, cs, (float)val);
-        if (AUX) neumaier(s_a, c_a, (float)(val * (double)sa[k]));
-      }
-    }
-    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = s + cs;
-    if (AUX) partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = s_a + c_a;
-  }
-}
-
-// The same sums for narrow blobs: every pixel radius below 1.9 (WIN = 4) or
-// 3.9 (WIN = 8) pixels, so that a blob covers only pixels of the WIN x WIN
-// window that starts at its first admitted pixel (the binning's conservative
-// range: its first pixel, and at most WIN - 1 more, since 2 (h + 1/100)
-// plus the float32 rounding of the range stays below WIN).  The gather form
-// spends a wave's 64 lanes on one record, of which a handful are covered;
-// here the work is split in two phases per chunk of CH records:
-//   A: every lane evaluates one record at IPT window pixels (all lanes busy),
-//      leaves the rounded contributions in LDS and, for each covered pixel
-//      of the tile, sets the record's bit in that pixel's mask;
-//   B: thread p owns pixel p of the tile as before and walks the set bits of
-//      its mask in increasing record order, adding those contributions.
-// The contributions are computed by the same float32 / float64 operations as
-// in k_accumulate_cubic and every pixel adds the same ones in the same
-// order: the image is bit-identical to the gather form's.
-template <int WIN> struct CubicWin {
-  static constexpr int WW = WIN * WIN;           // window pixels per record
-  static constexpr int CH = WIN == 4 ? PT : 64;  // records per chunk
-  static constexpr int IPT = WW * CH / PT;       // window pixels per thread in phase A
-  static constexpr int VS = CH + 1;              // LDS stride of one window pixel's row
-  static constexpr int MW = CH / 32;             // mask words per pixel
-};
-
-template <class RecT, int WIN>
-__global__ __launch_bounds__(PT) void k_accumulate_cubic_win(const uint2 *__restrict__ table,
-                                                             const uint32_t *__restrict__ slice_off, uint32_t nt,
-                                                             const RecT *__restrict__ rec, Cam c,
-                                                             float *__restrict__ partial,
-                                                             float *__restrict__ partial_aux, uint64_t max_slices,
-                                                             uint64_t max_pairs) {
-  constexpr bool AUX = RecInfo<RecT>::aux;
-  using CW = CubicWin<WIN>;
-  constexpr int CH = CW::CH, IPT = CW::IPT, VS = CW::VS, MW = CW::MW;
-  static_assert(IPT * PT == CW::WW * CH && CH % 32 == 0 && PT == TS * TS, "phase A covers every window pixel once");
-  __shared__ float val[CW::WW * VS];             // [window pixel][record]
-  __shared__ float vala[AUX ? CW::WW * VS : 1];
-  __shared__ uint32_t org[CH];                   // window origin in the tile: x0 | y0 << 16 (int16 each)
-  __shared__ uint32_t msk[MW * PT];              // [record / 32][pixel]: bit of each covering record
-  const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
-  if (blockIdx.x >= total_slices) return;
-  const int px = threadIdx.x % TS, py = threadIdx.x / TS;
-  const int kA = threadIdx.x % CH;                 // phase A: this thread's record in the chunk
-  const int iA = (threadIdx.x / CH) * IPT;         // and its first window pixel
-  // phase B leaves each pixel's mask words cleared for the next chunk
+    for (int i = threadIdx.x; i < NW * CSUM * CH * CTILE; i += PT) (&sum[0][0][0][0])[i] = 0.0;
+    __syncthreads();
+    // U steps together: item u of this lane is pixel (dx, dy) from the first one
+    // of record slot[u] of this wave; its value is added to sum g by the
+    // instruction of its phase.  The U chains of LDS reads and float64
+    // operations run side by side, without branches.
+    auto items = [&](const bool (&live)[2], const uint32_t (&slot)[2], const int (&dx)[2], const int (&dy)[2],
+                     const int (&g)[2], const int (&phase)[2], int phases) {
+      float4 r[U];
+      double2 f[U];
+      double hh[U], fa[U];
+      uint32_t org[U];
 #pragma unroll
-  for (int wd = 0; wd < MW; ++wd) msk[wd * PT + threadIdx.x] = 0u;
-  __syncthreads();
-  for (uint32_t sl = blockIdx.x; sl < total_slices; sl += gridDim.x) {
-    const uint2 sd = table[sl];
-    const uint32_t t = sd.y & 0xFFFFu;
-    const uint64_t pb = sd.x;
-    const uint64_t pe = min(pb + (sd.y >> 16), max_pairs);
-    const int tx0 = (int)(t % c.tiles_x) * TS, ty0 = (int)(t / c.tiles_x) * TS;
-    float s = 0.0f, cs = 0.0f, s_a = 0.0f, c_a = 0.0f;
-    for (uint64_t c0 = pb; c0 < pe; c0 += CH) {
-      const int nrec = (int)min((uint64_t)CH, pe - c0);
-      // phase A
-      {
-        const bool have = kA < nrec;
-        float u, v, m, h, a;
-        load_rec(rec, have ? c0 + kA : pb, u, v, m, h, a);
-        const int lx = (int)ceilf(u - 0.5f - h - 0.01f), ly = (int)ceilf(v - 0.5f - h - 0.01f);
-        const int x0 = lx - tx0, y0 = ly - ty0;
-        if (iA == 0) org[kA] = ((uint32_t)x0 & 0xFFFFu) | ((uint32_t)y0 << 16);
-        const double h64 = (double)h;
-        const double hh = h64 * h64;
-        const double ih = 1.0 / h64;
-        const float hh32 = (h * h) * 1.001f;
-        const uint32_t bit = 1u << (kA & 31);
+      for (int u = 0; u < U; ++u) {
+        r[u] = sgeo[w][slot[u]];
+        f[u] = sfac[w][slot[u]];
+        hh[u] = shh[w][slot[u]];
+        org[u] = sorg[w][slot[u]];
+        fa[u] = AUX ? sfaca[AUX ? w : 0][AUX ? slot[u] : 0] : 0.0;
+      }
+      bool ok[U];
+      int o[U];
+      double wq[U];
 #pragma unroll
-        for (int e = 0; e < IPT; ++e) {
-          const int wi = iA + e;
-          const int tpx = x0 + wi % WIN, tpy = y0 + wi / WIN;   // the pixel in the tile
-          const float cx = (float)(lx + wi % WIN) + 0.5f, cy = (float)(ly + wi / WIN) + 0.5f;
-          const float ox = u - cx, oy = v - cy;
-          float vf = 0.0f, va = 0.0f;
-          if (have && (ox * ox + oy * oy) < hh32) {
-            const double r2 = (double)ox * (double)ox + (double)oy * (double)oy;
-            if (r2 < hh) {
-              double q = 0.0;
-              if (r2 > 0.0) {
-                double y = __builtin_amdgcn_rsq(r2);
-                y = y * (1.5 - (0.5 * r2) * (y * y));
-                q = (r2 * y) * ih;
-              }
-              const double w = (double)m * (kCubicNorm / hh) * cubic_w(q);
-              vf = (float)w;
-              if (AUX) va = (float)(w * (double)a);
-              if ((unsigned)tpx < (unsigned)TS && (unsigned)tpy < (unsigned)TS)
-                atomicOr(&msk[(kA >> 5) * PT + tpy * TS + tpx], bit);
-            }
+      for (int u = 0; u < U; ++u) {
+        const int px = (int)(int16_t)(org[u] & 0xFFFFu) + dx[u], py = (int)(int16_t)(org[u] >> 16) + dy[u];
+        // pixel centres are half-integers below 2^15: the sums are exact
+        const float ox = r[u].x - (r[u].z + (float)dx[u]), oy = r[u].y - (r[u].w + (float)dy[u]);
+        const double ox64 = (double)ox, oy64 = (double)oy;
+        const double r2 = __builtin_fma(ox64, ox64, oy64 * oy64);   // exact squares, one rounding
+        ok[u] = live[u] && r2 < hh[u] && (unsigned)px < (unsigned)TS && (unsigned)py < (unsigned)TS;
+        // q = sqrt(r2) / h from the hardware reciprocal square root and one
+        // Newton step (relative error far below 1e-12)
+        const double q2 = fmax(r2 * f[u].x, 1e-280);
+        const double y = __builtin_amdgcn_rsq(q2);
+        const double gq = q2 * y;
+        const double q = __builtin_fma(gq, __builtin_fma(-gq, 0.5 * y, 0.5), gq);
+        const double p = 1.0 - q;
+        const double wi = __builtin_fma(-6.0 * q2, p, 1.0), wo = (p * p) * (p + p);
+        wq[u] = q <= 0.5 ? wi : wo;
+        o[u] = py * CRS + px;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        for (int ph = 0; ph < phases; ++ph)
+          if (ok[u] && (phases == 1 || phase[u] == ph)) {
+            lds_add_f64(&sum[w][g[u]][0][o[u]], f[u].y * wq[u]);
+            if constexpr (AUX) lds_add_f64(&sum[w][g[u]][CH - 1][o[u]], fa[u] * wq[u]);
           }
-          val[wi * VS + kA] = vf;
-          if (AUX) vala[wi * VS + kA] = va;
-        }
-      }
-      __syncthreads();
-      // phase B: this pixel's covering records in increasing order
+    };
+    for (uint64_t c0 = pb + (uint64_t)w * WAVE; c0 < pe; c0 += PT) {
+      // the wave's records, sorted by class
+      const bool have = c0 + lane < pe;
+      float u, v, m, h, at;
+      load_rec(rec, have ? c0 + lane : pb, u, v, m, h, at);
+      const int win = (int)floorf(2.0f * h + 0.05f) + 1;
+      const int cls = win <= 4 ? 0 : win <= 6 ? win - 4 : win <= 8 ? 3 : 4;
+      uint32_t slot = 0, first[NCLS + 1];
+      first[0] = 0;
 #pragma unroll
-      for (int wd = 0; wd < MW; ++wd) {
-        uint32_t bits = msk[wd * PT + threadIdx.x];
-        msk[wd * PT + threadIdx.x] = 0u;
-        while (bits) {
-          const int k = wd * 32 + __builtin_ctz(bits);
-          bits &= bits - 1u;
-          const uint32_t o = org[k];
-          const int dx = px - (int)(int16_t)(o & 0xFFFFu), dy = py - (int)(int16_t)(o >> 16);
-          const int vi = (dy * WIN + dx) * VS + k;
-          neumaier(s, cs, val[vi]);
-          if (AUX) neumaier(s_a, c_a, vala[vi]);
-        }
+      for (int k = 0; k < NCLS; ++k) {
+        const uint64_t mask = __ballot(have && cls == k);
+        if (have && cls == k) slot = first[k] + rank_below(mask);
+        first[k + 1] = first[k] + (uint32_t)__popcll(mask);
       }
-      __syncthreads();
+      if (have) {
+        const int x0 = (int)ceilf(u - 0.5f - h - 0.01f) - tx0, y0 = (int)ceilf(v - 0.5f - h - 0.01f) - ty0;
+        const double h2 = (double)h * (double)h, ih2 = 1.0 / h2;
+        const double fm = (double)m * (kCubicNorm * ih2);
+        const int fx = cls == 4 ? 0 : x0, fy = cls == 4 ? 0 : y0;
+        sgeo[w][slot] = make_float4(u, v, (float)(tx0 + fx) + 0.5f, (float)(ty0 + fy) + 0.5f);
+        sfac[w][slot] = make_double2(ih2, fm);
+        shh[w][slot] = h2;
+        sorg[w][slot] = ((uint32_t)fx & 0xFFFFu) | ((uint32_t)fy << 16);
+        if constexpr (AUX) sfaca[w][slot] = fm * (double)at;
+      }
+      wave_sync_mem();
+      const int l16 = lane & 15, l32 = lane & 31;
+      for (uint32_t k = first[0]; k < first[1]; k += 4 * U) {
+        const uint32_t a0 = k + lane / 16, a1 = a0 + 4, last = first[1] - 1;
+        items({a0 <= last, a1 <= last}, {min(a0, last), min(a1, last)}, {l16 & 3, l16 & 3}, {l16 >> 2, l16 >> 2},
+              {(lane >> 4) & 1, (lane >> 4) & 1}, {lane >> 5, lane >> 5}, 2);
+      }
+      for (uint32_t k = first[1]; k < first[2]; k += 2 * U) {
+        const uint32_t a0 = k + lane / 32, a1 = a0 + 2, last = first[2] - 1;
+        items({l32 < 25 && a0 <= last, l32 < 25 && a1 <= last}, {min(a0, last), min(a1, last)}, {l32 % 5, l32 % 5},
+              {l32 / 5, l32 / 5}, {lane >> 5, lane >> 5}, {0, 0}, 1);
+      }
+      const uint32_t n6 = 36 * (first[3] - first[2]);
+      for (uint32_t k = 0; k < n6; k += U * WAVE) {
+        const uint32_t i0 = k + lane, i1 = i0 + WAVE, j0 = min(i0, n6 - 1), j1 = min(i1, n6 - 1);
+        const uint32_t r0 = j0 / 36, r1 = j1 / 36, e0 = j0 % 36, e1 = j1 % 36;
+        items({i0 < n6, i1 < n6}, {first[2] + r0, first[2] + r1}, {(int)(e0 % 6), (int)(e1 % 6)},
+              {(int)(e0 / 6), (int)(e1 / 6)}, {(int)(r0 & 1), (int)(r1 & 1)},
+              {(int)((r0 >> 1) & 1), (int)((r1 >> 1) & 1)}, 2);
+      }
+      for (uint32_t k = first[3]; k < first[4]; k += U) {
+        const uint32_t k1 = min(k + 1, first[4] - 1);
+        items({true, k + 1 < first[4]}, {k, k1}, {lane & 7, lane & 7}, {lane >> 3, lane >> 3}, {0, 0}, {0, 0}, 1);
+      }
+      for (uint32_t k = first[4]; k < first[5]; ++k)
+        for (int y = 0; y < TS; y += U * (WAVE / TS))
+          items({true, true}, {k, k}, {lane % TS, lane % TS}, {y + lane / TS, y + WAVE / TS + lane / TS}, {0, 0},
+                {0, 0}, 1);
+      wave_sync_mem();                                   // the records are rewritten
     }
-    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = s + cs;
-    if (AUX) partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = s_a + c_a;
+    __syncthreads();
+    const int o = (threadIdx.x / TS) * CRS + threadIdx.x % TS;
+    double s[CH];
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) {
+      s[ch] = 0.0;
+#pragma unroll
+      for (int g = 0; g < NW * CSUM; ++g) s[ch] += sum[g / CSUM][g % CSUM][ch][o];
+    }
+    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = (float)s[0];
+    if constexpr (AUX) partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = (float)s[CH - 1];
+    __syncthreads();
   }
 }
 
@@ -1781,11 +1778,6 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   return LOD_OK;
 }
 
-// Whether a source carries per-point world radii (the cubic blob's pixel
-// radius then varies up to the clamp).
-template <class Src> static bool has_point_radii(const Src &) { return false; }
-static bool has_point_radii(const InterpSrc &s) { return s.ha != nullptr; }
-
 // Binning, accumulation and the final slice sums for any point source and
 // record form.  image_aux receives the attribute channel (RecT carrying one).
 template <class Src, class RecT>
@@ -1854,17 +1846,8 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
   const unsigned agrid = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(16384, L.max_slices));
   if (any) {
     if constexpr (RecInfo<RecT>::cubic) {
-      // narrow blobs take the windowed form (same bits, fewer idle lanes)
-      const float hmax = (c.Fhw > 0.0f || has_point_radii(src)) ? lodh::BLOB_H_MAX : c.hpx;
-      if (hmax < 1.9f)
-        LOD_LAUNCH((k_accumulate_cubic_win<RecT, 4>), dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c,
-                   partial, partial_aux, L.max_slices, L.max_pairs);
-      else if (hmax < 3.9f)
-        LOD_LAUNCH((k_accumulate_cubic_win<RecT, 8>), dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c,
-                   partial, partial_aux, L.max_slices, L.max_pairs);
-      else
-        LOD_LAUNCH(k_accumulate_cubic<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
-                   partial_aux, L.max_slices, L.max_pairs);
+      LOD_LAUNCH(k_accumulate_cubic<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
+                 partial_aux, L.max_slices, L.max_pairs);
     } else
       LOD_LAUNCH(k_accumulate<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial, partial_aux,
                  L.max_slices, L.max_pairs);

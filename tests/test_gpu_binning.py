@@ -71,3 +71,33 @@ def test_cut_and_draw_list_over_block_edges(n, depth):
         px, py, pz, pm = olod.decoded_points(ref, want)
         err, zeros_ok = image_rel_err(img, osplat.render(ocam, px, py, pz, pm))
         assert zeros_ok and err <= TOL, (tau, err)
+
+
+@pytest.mark.parametrize("order", ["morton", "random", "clump"])
+@pytest.mark.parametrize("aux", [False, True])
+def test_cubic_window_classes(order, aux):
+    """World radii whose pixel windows span every class of the cubic
+    accumulation (4, 5, 6, 8 pixels and wider) in one render, at chunk
+    remainders, with a clump whose records all cover the same few pixels."""
+    import torch
+    n, W, H = 4096 + 77, 96, 80
+    rng = np.random.default_rng(3)
+    p = _points(order if order != "clump" else "random", n, 21)
+    if order == "clump":
+        p[0][:n // 2] = 0.5 + 0.004 * (p[0][:n // 2] - 0.5)
+        p[1][:n // 2] = 0.5 + 0.004 * (p[1][:n // 2] - 0.5)
+    pos = (0.5, 0.5, -1.0)
+    cam = lib.Camera.look_at(pos, (0.5, 0.5, 0.5), W, H, fov_deg=60.0)
+    ocam = osplat.Camera(1, W, H, cam.pos, cam.right, cam.up, cam.fwd, cam.F, cam.near)
+    # pixel radii from the clamp at 1 to the clamp at 16
+    hw = (np.exp(rng.uniform(np.log(0.8), np.log(20.0), n)) * 1.5 / cam.F).astype(np.float32)
+    col = rng.random(n).astype(np.float32)
+    d = [torch.from_numpy(a).cuda() for a in p]
+    dh, dc = torch.from_numpy(hw).cuda(), torch.from_numpy(col).cuda()
+    got = lib.splat_interp(d, d, 0.5, cam, blob=lib.Blob.cubic(h_world=0.01), hA=dh, hB=dh,
+                           cA=dc if aux else None, cB=dc if aux else None)
+    want = ocubic.render(ocam, *p, h_world=hw, aux=col if aux else None)
+    pairs = zip(got, want) if aux else ((got, want[0] if isinstance(want, tuple) else want),)
+    for g, w in pairs:
+        err, zeros_ok = image_rel_err(g.cpu().numpy(), w)
+        assert zeros_ok and err <= TOL, err
