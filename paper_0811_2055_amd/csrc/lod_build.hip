@@ -861,21 +861,32 @@ __device__ __forceinline__ PointIn read_point(const Sorted &s, uint64_t pos) {
   return PointIn{s.key[pos], s.idx[pos], (uint64_t)s.lo[pos] | ((uint64_t)s.lz[pos] << 32)};
 }
 
-__device__ __forceinline__ void store_point_pos(const BuildArgs &a, const TreeArgs &t, const PointIn &q,
-                                                uint64_t out, int d) {
+// A stored point's id and 16-bit codes (x in the low, y in the high half of xy).
+struct PointOut {
+  uint32_t id, xy, z;
+};
+
+__device__ __forceinline__ PointOut code_point(const BuildArgs &a, const PointIn &q, int d) {
   const int D = a.D;
   const uint32_t kk = D ? (q.k & (uint32_t)((1ull << (3 * D)) - 1)) : 0u;
   const uint32_t cx = compact3(kk), cy = compact3(kk >> 1), cz = compact3(kk >> 2);
   const uint32_t snap = (a.n_snap > 1) ? (uint32_t)((uint64_t)q.k >> (3 * D)) : 0u;
-  t.pt_id[out] = (uint32_t)local_id(a, snap, q.id);
-  t.qx[out] = quant_at(cx, (uint32_t)(q.l & 0xFFFFu), D, d);
-  t.qy[out] = quant_at(cy, (uint32_t)((q.l >> 16) & 0xFFFFu), D, d);
-  t.qz[out] = quant_at(cz, (uint32_t)((q.l >> 32) & 0xFFFFu), D, d);
+  return PointOut{(uint32_t)local_id(a, snap, q.id),
+                  (uint32_t)quant_at(cx, (uint32_t)(q.l & 0xFFFFu), D, d) |
+                      ((uint32_t)quant_at(cy, (uint32_t)((q.l >> 16) & 0xFFFFu), D, d) << 16),
+                  (uint32_t)quant_at(cz, (uint32_t)((q.l >> 32) & 0xFFFFu), D, d)};
+}
+
+__device__ __forceinline__ void store_codes(const TreeArgs &t, const PointOut &o, uint64_t out) {
+  t.pt_id[out] = o.id;
+  t.qx[out] = (uint16_t)(o.xy & 0xFFFFu);
+  t.qy[out] = (uint16_t)(o.xy >> 16);
+  t.qz[out] = (uint16_t)o.z;
 }
 
 __device__ __forceinline__ void store_point(const BuildArgs &a, const TreeArgs &t, const PointIn &q, uint64_t out,
                                             int d, float mass) {
-  store_point_pos(a, t, q, out, d);
+  store_codes(t, code_point(a, q, d), out);
   t.pt_mass[out] = mass;
 }
 
@@ -967,16 +978,19 @@ __global__ __launch_bounds__(TB) void k_leaves(BuildArgs a, TreeArgs t, Sorted s
 
 constexpr int SMALL = 512;
 constexpr int KBINS = 4096;
-constexpr int SILP = 8;       // candidates per lane per wave step
-constexpr int CILP = 8;       // candidates per lane per step of the compaction pass of list nodes
+constexpr int SILP = 8;       // candidates per lane per wave step of the (rare) exact-key rounds
+constexpr int CILP = 8;       // 16-byte chunks of key bins per lane in flight
 constexpr int OILP = 4;       // list entries per thread per step of the output pass
-constexpr int FILP = 2;       // candidates per lane per step of the fused pass of range-only nodes
 constexpr int QCAP = 2048;    // bin-b0 candidates queued in LDS by the collect pass
-constexpr int HT = 2 * SMALL; // slots of the table of ranked candidates (load <= 1/2)
-static_assert(2 * HT <= KBINS, "the table lives in the histogram's storage");
-
-__device__ __forceinline__ uint32_t ht_slot(uint32_t p) { return (p * 2654435761u) >> 22; }   // HT = 2^10
-static_assert(HT == 1024, "ht_slot takes the top 10 bits");
+constexpr int MAXSEG = 9;     // segments of a node's candidates (8 children)
+constexpr uint32_t CHUNK = 8; // key bins per 16-byte chunk
+// chunks whose taken flags (a byte each) fit the histogram's storage: 131072
+// candidates, which holds the eight lists of n <= 16383 points
+constexpr uint32_t FLAG_CHUNKS = 4 * KBINS;
+// Histograms of the lists' key bins (16 bits a bin) are kept for n in
+// [2048, 65534]: below, they would take more memory than the lists (14 n bytes)
+// and the lists are read as fast; above, a bin may not fit.
+__host__ __device__ inline bool keeps_list_hist(uint64_t n) { return n >= 2048 && n < 65535; }
 
 // A list entry is a sorted position, its key bin and the candidate's density
 // weight and mass (so that the parent's output pass reads them in list order
@@ -986,35 +1000,56 @@ struct SelArgs {
   uint16_t *lkb;              // and their key bins (a separate array: the counting passes read only these)
   uint2 *lwm;                 // and (w, mass bits)
   uint32_t n_minus_1;         // N - 1
+  uint16_t *lhist;            // [rank][KBINS] entries of each list by key bin, or null
+  uint32_t *widx;             // [node] the witness's index in the node's list
   double *mhat;               // float64 mass scratch, one row of n per block
-  uint32_t *src;              // source of each list entry, one row of n+1 per block
+  uint32_t *src;              // candidate of each list entry, one row of n+1 per block
 };
 
 // sorted position of list entry i (clamped: the lists are workspace)
 __device__ __forceinline__ uint32_t entry_pos(const SelArgs &sa, uint64_t i) { return min(sa.lpos[i], sa.n_minus_1); }
 
+// A node's candidates: the concatenation of its segments, in sorted position
+// order (runs of leaf children form one range segment).  Their key bins are
+// read in 16-byte chunks, and the chunks of all segments form one sequence
+// (first of segment k: cst[k]).  A candidate is named by 8 times its chunk plus
+// its element in the chunk, its code: ascending codes are the candidate order.
 struct Segs {
   uint32_t nseg;
-  uint64_t base[9];   // start sorted position (range) or list offset (list)
-  uint32_t len[9];
-  uint32_t is_list[9];
-  // list segments: the child's witness position, its first stored point and
-  // its octant (the bit each cell coordinate gains from parent to child)
-  uint32_t cwit[9];
-  uint64_t cob[9];
-  uint32_t coct[9];
+  uint64_t base[MAXSEG];   // start sorted position (range) or list offset (list)
+  uint32_t len[MAXSEG];
+  uint32_t is_list[MAXSEG];
+  uint32_t cst[MAXSEG + 1];      // first chunk; their number at [nseg], then ~0
+  uint64_t adj[MAXSEG];          // sorted position or list offset of code x of segment k: adj[k] + x
+  const uint16_t *kb[MAXSEG];    // key bin of code x of segment k: kb[k][x]
+  uint32_t head[MAXSEG], tail[MAXSEG];         // valid elements (bits) of the first and of the last chunk
+  // list segments: the child's selecting rank, the codes of its first entry and
+  // of its witness, its first stored point and its octant (the bit each cell
+  // coordinate gains from parent to child)
+  uint32_t crank[MAXSEG], cx0[MAXSEG], cwx[MAXSEG];
+  uint64_t cob[MAXSEG];
+  uint32_t coct[MAXSEG];
 };
+
+// Segment of chunk c (entries past the last segment are ~0).
+__device__ __forceinline__ uint32_t seg_of(const Segs &g, uint32_t c) {
+  uint32_t k = 0;
+#pragma unroll
+  for (int i = 1; i < MAXSEG; ++i) k += c >= g.cst[i] ? 1u : 0u;
+  return k;
+}
 
 // A node's children's fields, loaded by one lane each so that the loads of
 // all children are in flight together.
 struct Children {
   uint64_t pc[8], pb[8], ptb[8];
-  uint32_t sel[8], wit[8], oct[8];
+  uint32_t sel[8], widx[8], oct[8];
   double m[8];
 };
 
-__device__ __forceinline__ void build_segments(const BuildArgs &a, const TreeArgs &t, uint32_t v, uint32_t fc,
-                                               int nk, const Children &ch, Segs &g) {
+__device__ __forceinline__ void build_segments(const BuildArgs &a, const TreeArgs &t, const Sorted &s,
+                                               const SelArgs &sa, uint32_t v, uint32_t fc, int nk,
+                                               const Children &ch, Segs &g) {
   const uint32_t n = a.n;
   uint32_t ns = 0;
   if (fc == NONE) {
@@ -1023,7 +1058,7 @@ __device__ __forceinline__ void build_segments(const BuildArgs &a, const TreeArg
     for (int k = 0; k < nk; ++k) {
       if (ch.pc[k] > n) {
         g.base[ns] = (uint64_t)ch.sel[k] * (n + 1); g.len[ns] = n + 1; g.is_list[ns] = 1;
-        g.cwit[ns] = ch.wit[k]; g.cob[ns] = ch.ptb[k]; g.coct[ns] = ch.oct[k];
+        g.crank[ns] = ch.sel[k]; g.cwx[ns] = ch.widx[k]; g.cob[ns] = ch.ptb[k]; g.coct[ns] = ch.oct[k];
         ++ns;
       } else if (ns > 0 && !g.is_list[ns - 1]) {
         g.len[ns - 1] += (uint32_t)ch.pc[k];   // siblings are adjacent in sorted order
@@ -1034,12 +1069,24 @@ __device__ __forceinline__ void build_segments(const BuildArgs &a, const TreeArg
     }
   }
   g.nseg = ns;
+  uint32_t c = 0;
+  for (uint32_t k = 0; k < ns; ++k) {
+    const uint64_t a0 = g.base[k] / CHUNK, a1 = (g.base[k] + g.len[k] - 1) / CHUNK;
+    g.cst[k] = c;
+    g.adj[k] = CHUNK * a0 - CHUNK * (uint64_t)c;
+    g.kb[k] = (g.is_list[k] ? sa.lkb : s.kb) + g.adj[k];
+    g.head[k] = 0xFFu << (g.base[k] % CHUNK);
+    g.tail[k] = 0xFFu >> (CHUNK - 1 - (g.base[k] + g.len[k] - 1) % CHUNK);
+    g.cx0[k] = (uint32_t)(CHUNK * c + g.base[k] % CHUNK);
+    if (g.is_list[k]) g.cwx[k] += g.cx0[k];   // from the list index
+    c += (uint32_t)(a1 - a0 + 1);
+  }
+  g.cst[ns] = c;
+  for (uint32_t k = ns + 1; k <= MAXSEG; ++k) g.cst[k] = 0xFFFFFFFFu;
 }
 
-// The candidates of a node are the concatenation of its segments, in sorted
-// position order (runs of leaf children form one range segment).  Wave w of the block owns the w-th of W equal contiguous
-// parts of every segment, so (segment, wave) parts are in candidate order and
-// a wave streams its part in steps of 64 x SILP without block barriers.
+// Wave w of the block owns the w-th of W equal contiguous parts of a segment
+// (exact-key rounds) or of the chunk sequence.
 __device__ __forceinline__ void wave_part(uint32_t L, uint32_t w, uint32_t W, uint32_t &lo, uint32_t &hi) {
   const uint32_t P = (L + W - 1) / W;
   lo = min(L, w * P);
@@ -1070,46 +1117,71 @@ __device__ __forceinline__ void load_step(const Segs &g, int k, const SelArgs &s
   }
 }
 
-// Calls f(k, p, kb) for every candidate of this wave's parts, in no
-// particular order (f is inlined many times: keep it small), with 16-byte
-// loads of 8 key bins per lane so that many bytes are in flight per wave.  p
-// is the sorted position for a range segment and the index within the list
-// for a list segment (entry_pos gives its position).  Reads may run up to 16
-// bytes past a part; the key-bin arrays are padded for it.
-constexpr int BU = 4;         // 16-byte loads in flight per lane
+// Calls f(c, k, valid, v) for the chunks [lo, hi) of this wave, in order of c
+// within a lane: the chunk's segment, its valid elements (bits) and its eight
+// key bins.  CILP 16-byte loads of a lane are in flight together, across
+// segments, so a pass over a node's lists costs a few memory latencies, not
+// one per list.  (Reads may run up to 16 bytes past a part; the key-bin arrays
+// are padded for it.)
+// A step's segment is found once per wave when all of its chunks lie in one
+// segment (nearly always: a list of 16 k entries is 2 k chunks).
+__device__ __forceinline__ uint32_t step_seg(const Segs &g, uint32_t c0, uint32_t hi) {
+  const uint32_t lane = threadIdx.x & (WAVE - 1);
+  const uint32_t k0 = __builtin_amdgcn_readfirstlane(seg_of(g, c0));
+  if (min(c0 + WAVE, hi) <= g.cst[k0 + 1]) return k0;
+  return seg_of(g, min(c0 + lane, hi - 1));
+}
+
 template <typename F>
-__device__ __forceinline__ void for_parts_bulk(const Segs &g, const SelArgs &sa, const Sorted &s, F f) {
-  const uint32_t W = blockDim.x / WAVE, w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-  for (int k = 0; k < (int)g.nseg; ++k) {
-    uint32_t lo, hi;
-    wave_part(g.len[k], w, W, lo, hi);
-    if (lo >= hi) continue;
-    const uint64_t b = g.base[k] + lo, e = g.base[k] + hi;   // element range [b, e)
-    const uint16_t *kbp = g.is_list[k] ? sa.lkb : s.kb;
-    const uint64_t off = g.is_list[k] ? g.base[k] : 0;
-    const uint64_t a0 = b & ~7ull, last = (e - 1) & ~7ull;
-    for (uint64_t q0 = a0; q0 < e; q0 += 8ull * WAVE * BU) {
-      uint4 v[BU];
+__device__ __forceinline__ void for_chunks(const Segs &g, uint32_t lo, uint32_t hi, F f) {
+  const uint32_t lane = threadIdx.x & (WAVE - 1);
+  for (uint32_t c0 = lo; c0 < hi; c0 += WAVE * CILP) {
+    uint4 v[CILP];
+    uint32_t ks[CILP];
 #pragma unroll
-      for (int u = 0; u < BU; ++u) {
-        const uint64_t i = min(q0 + 8ull * (u * WAVE + lane), last);
-        v[u] = *reinterpret_cast<const uint4 *>(kbp + i);
-      }
+    for (int u = 0; u < CILP; ++u) {
+      ks[u] = step_seg(g, min(c0 + u * WAVE, hi - 1), hi);
+      v[u] = *reinterpret_cast<const uint4 *>(g.kb[ks[u]] + (uint64_t)min(c0 + u * WAVE + lane, hi - 1) * CHUNK);
+    }
 #pragma unroll
-      for (int u = 0; u < BU; ++u) {
-        const uint64_t i = q0 + 8ull * (u * WAVE + lane);
-        const uint32_t wd[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-        for (int h = 0; h < 8; ++h) {
-          const uint64_t ih = i + h;
-          if (ih >= b && ih < e) f(k, (uint32_t)(ih - off), (wd[h >> 1] >> (16 * (h & 1))) & 0xFFFFu);
-        }
+    for (int u = 0; u < CILP; ++u) {
+      const uint32_t c = c0 + u * WAVE + lane, k = ks[u];
+      if (c < hi) {
+        uint32_t valid = 0xFFu;
+        if (c == g.cst[k]) valid &= g.head[k];
+        if (c + 1 == g.cst[k + 1]) valid &= g.tail[k];
+        f(c, k, valid, v[u]);
       }
     }
   }
 }
 
-// Calls f(k, pos, kb) for every candidate of this wave's parts.
+// Sorted position of the candidate of code x in segment k.
+__device__ __forceinline__ uint32_t cand_pos(const Segs &g, const SelArgs &sa, uint32_t k, uint32_t x) {
+  return g.is_list[k] ? entry_pos(sa, g.adj[k] + x) : (uint32_t)(g.adj[k] + x);
+}
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// Of a chunk's key bins: le = those at most b, eq = those equal to b (bits in
+// element order).  A saturating packed subtraction leaves 0 below, 1 at and 2
+// or more above b, for two bins at a time; the two-bit codes of all eight are
+// gathered before the bits are taken apart.
+__device__ __forceinline__ void compare_bins(uint4 v, uint32_t b, uint32_t &le, uint32_t &eq) {
+  const uint32_t b1 = b ? b - 1 : 0u, up = b ? 0u : 0x00010001u;   // (k + 1) - 1 for b = 0: bins stay below 2^12
+  const u16x2 bb = {(unsigned short)b1, (unsigned short)b1};
+  const uint32_t wd[4] = {v.x + up, v.y + up, v.z + up, v.w + up};
+  uint32_t p = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const u16x2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, wd[i]), bb);
+    p |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(d, u16x2{2, 2})) << (2 * i);
+  }
+  const uint32_t above = (p >> 1) & 0x00550055u, at = p & 0x00550055u;
+  le = ((above | (above >> 15)) & 0xFFu) ^ 0xFFu;
+  eq = (at | (at >> 15)) & 0xFFu;
+}
+
+// Calls f(pos, kb) for every candidate of this wave's parts of the segments.
 template <typename F>
 __device__ __forceinline__ void for_parts(const Segs &g, const SelArgs &sa, const Sorted &s, F f) {
   const uint32_t W = blockDim.x / WAVE, w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
@@ -1121,7 +1193,7 @@ __device__ __forceinline__ void for_parts(const Segs &g, const SelArgs &sa, cons
       load_step(g, k, sa, s, j0, hi, pos, kb);
 #pragma unroll 1
       for (int u = 0; u < SILP; ++u)
-        if (j0 + u * WAVE + lane < hi) f(k, pos[u], kb[u]);
+        if (j0 + u * WAVE + lane < hi) f(pos[u], kb[u]);
     }
   }
 }
@@ -1133,66 +1205,76 @@ __device__ __forceinline__ bool taken_exact(const BuildArgs &a, const Sorted &s,
   return K < Kt || (K == Kt && s.idx[p] <= It);
 }
 
+// m / min(1, w^alpha / tau) with one float64 division at most.
+__device__ __forceinline__ double unscaled_mass(float m, uint32_t w, int alpha, double tau) {
+  const double m64 = (double)m;
+  if (alpha > 0) return (double)w >= tau ? m64 : m64 * tau / (double)w;
+  if (alpha == 0) return tau <= 1.0 ? m64 : m64 * tau;
+  return 1.0 >= tau * (double)w ? m64 : m64 * (tau * (double)w);
+}
+
 // Sum of row[0..n) in an order fixed by n alone, so that every block size and
-// schedule stores the same bits: 64-entry chunks summed by a wave's xor
-// butterfly (lane i holds entry 64c + i, absent entries 0; lane 0's value),
-// groups of 64 chunk sums by one more butterfly, and the group sums added in
-// order by thread 0.  Rows of up to RS_CHUNKS chunks take one pass (the waves
-// load their chunks together); longer rows go group by group.  cs: RS_CHUNKS
-// doubles of LDS; the result is returned to every thread (barriers inside).
-constexpr uint32_t RS_CHUNKS = 256;
+// schedule stores the same bits: groups of RS_GROUP entries, lane i of a wave
+// adding entries i, i + 64, ... of its group in order (absent entries 0), then
+// a xor butterfly over the lanes; 64 group sums by one more butterfly, and
+// those added in order by thread 0.  cs: RS_SUMS doubles of LDS; the result is
+// returned to every thread (barriers inside).  (A butterfly per 64 entries was
+// bound by its own instructions: 6.5 us for n = 16000.)
+//
+// The butterfly runs on lane swaps and row rotations instead of LDS permutes:
+// once two halves hold equal sums, a rotation by o brings the value that the
+// xor by o would.
+__device__ __forceinline__ double wave_sum_xor(double x) {
+  auto words = [](double d, uint32_t &lo, uint32_t &hi) {
+    const uint64_t b = (uint64_t)__double_as_longlong(d);
+    lo = (uint32_t)b; hi = (uint32_t)(b >> 32);
+  };
+  auto make = [](uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)); };
+  uint32_t lo, hi;
+  words(x, lo, hi);
+  {
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = make(a[0], b[0]) + make(a[1], b[1]);
+  }
+  words(x, lo, hi);
+  {
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = make(a[0], b[0]) + make(a[1], b[1]);
+  }
+#define LOD_ROR(n)                                                                            \
+  words(x, lo, hi);                                                                           \
+  x += make((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x120 + n, 0xF, 0xF, false),    \
+            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x120 + n, 0xF, 0xF, false));
+  LOD_ROR(8) LOD_ROR(4) LOD_ROR(2) LOD_ROR(1)
+#undef LOD_ROR
+  return x;
+}
+
+constexpr uint32_t RS_ROWS = 16, RS_GROUP = RS_ROWS * WAVE, RS_SUMS = 64;
 __device__ double row_sum_fixed(const double *row, uint32_t n, double *cs, double *res) {
   const uint32_t W = blockDim.x / WAVE, w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-  const uint32_t chunks = (n + WAVE - 1) / WAVE;
+  const uint32_t groups = (n + RS_GROUP - 1) / RS_GROUP;
   double total = 0.0;   // thread 0's
-  auto chunk_sum = [&](uint32_t c) {
-    double x = c * WAVE + lane < n ? row[c * WAVE + lane] : 0.0;
+  for (uint32_t g0 = 0; g0 < groups; g0 += RS_SUMS) {
+    const uint32_t g1 = min(groups, g0 + RS_SUMS);
+    for (uint32_t g = g0 + w; g < g1; g += W) {
+      double x[RS_ROWS];
 #pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, WAVE);
-    return x;
-  };
-  auto group_sum = [&](uint32_t g, uint32_t count) {   // wave 0: chunk sums g*64.. of cs
-    double x = g * WAVE + lane < count ? cs[g * WAVE + lane] : 0.0;
+      for (uint32_t k = 0; k < RS_ROWS; ++k) x[k] = row[min(g * RS_GROUP + k * WAVE + lane, n - 1)];
+      double y = 0.0;
 #pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, WAVE);
-    return x;
-  };
-  if (chunks <= RS_CHUNKS) {
-    constexpr int CU = 4;   // chunks of a wave loaded together
-    for (uint32_t c0 = w; c0 < chunks; c0 += W * CU) {
-      double x[CU];
-#pragma unroll
-      for (int u = 0; u < CU; ++u) {
-        const uint32_t c = c0 + u * W;
-        const uint32_t j = min(c * WAVE + lane, n - 1);
-        x[u] = (c < chunks && c * WAVE + lane < n) ? row[j] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < CU; ++u) {
-#pragma unroll
-        for (int o = WAVE / 2; o > 0; o >>= 1) x[u] += __shfl_xor(x[u], o, WAVE);
-        if (lane == 0 && c0 + u * W < chunks) cs[c0 + u * W] = x[u];
-      }
+      for (uint32_t k = 0; k < RS_ROWS; ++k) y += g * RS_GROUP + k * WAVE + lane < n ? x[k] : 0.0;
+      y = wave_sum_xor(y);
+      if (lane == 0) cs[g - g0] = y;
     }
     __syncthreads();
-    if (w == 0)
-      for (uint32_t g = 0; g * WAVE < chunks; ++g) {
-        const double x = group_sum(g, chunks);
-        if (lane == 0) total += x;
-      }
-  } else {
-    for (uint32_t c0 = 0; c0 < chunks; c0 += WAVE) {
-      for (uint32_t c = c0 + w; c < min(chunks, c0 + WAVE); c += W) {
-        const double x = chunk_sum(c);
-        if (lane == 0) cs[c - c0] = x;
-      }
-      __syncthreads();
-      if (w == 0) {
-        const double x = group_sum(0, min(chunks - c0, (uint32_t)WAVE));
-        if (lane == 0) total += x;
-      }
-      __syncthreads();
+    if (w == 0) {
+      const double x = wave_sum_xor(lane < g1 - g0 ? cs[lane] : 0.0);
+      if (lane == 0) total += x;
     }
+    __syncthreads();
   }
   if (threadIdx.x == 0) *res = total;
   __syncthreads();
@@ -1204,31 +1286,39 @@ __device__ double row_sum_fixed(const double *row, uint32_t n, double *cs, doubl
 // sorted position; the (n+1)-th smallest is the witness.  The other n are
 // its stored points, written with their float64-renormalised masses.
 //
-// Round 0 histograms the 12-bit log-scale bin of K (stored per particle); the
-// exact K is recomputed only in the threshold bin (rare further rounds split
-// it by 8-bit digits of K, then of the id).  The collect pass gathers the
-// threshold bin's candidates and counts, per (segment, wave) part, the
-// candidates below it; after ranking, one scan of those counts gives every
-// part its output offset and the write pass compacts each part with wave
-// ballots.
+// Round 0 histograms the 12-bit log-scale bin of K (stored per particle): the
+// ranges' by reading them, the lists' from the histograms their nodes left.
+// The exact K is recomputed only in the threshold bin b0 (rare further rounds
+// split it by 8-bit digits of K, then of the id).  One pass over the key bins
+// then leaves a flag per candidate (bin at most b0) in LDS, counts per wave
+// those below b0 and queues those in b0, which are keyed and ranked; the flags
+// of the ones not taken are cleared.  The flags are expanded into the list of
+// taken candidates (wave offsets and popcount scans), and the output pass
+// reads each taken candidate's fields, every lane busy.
+//
+// What bounds a node is the chain of memory latencies and barriers, not its
+// bytes: a pass that reads 128 k key bins of eight lists one list after the
+// other took 10-30 us, and there were three, with the 128 k histogram adds and
+// a compaction that also read all 128 k positions.  A node of eight lists (1024
+// threads, n = 16000) took 154 us at 16.7 M particles and takes 78: histogram
+// 17 -> 5, collect 30 -> 12, compaction 43 -> 6, mass sum 11 -> 3; a node of
+// ranges 86 -> 78 (its output pass, 40 us beside 140 others, moves 1.4 MB of
+// fields, lists and points at the memory's rate).
 __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted &s, const SelArgs &sa,
                             uint32_t v) {
   __shared__ Segs g;
   __shared__ Children ch;
-  __shared__ uint32_t hist[KBINS];
+  __shared__ uint32_t hist[KBINS];               // later: a flag byte per chunk
   __shared__ uint64_t ck[SMALL];
-  __shared__ uint32_t cidx[SMALL];
-  __shared__ uint32_t cpos[SMALL];
-  __shared__ uint16_t cpart[SMALL];
-  __shared__ uint32_t pcnt[9 * (1024 / WAVE)];   // per (segment, wave) part: count, then offset
+  __shared__ uint32_t cidx[SMALL], cpos[SMALL], ccode[SMALL], crnk[SMALL];
+  __shared__ uint32_t pcnt[1024 / WAVE];         // per wave: taken candidates, then list offset
   __shared__ uint32_t ccount, sh_total, nq;
-  __shared__ uint32_t qpos[QCAP];
-  __shared__ uint16_t qpart[QCAP];
+  __shared__ uint32_t qcode[QCAP];
   __shared__ uint32_t red32[1024 / WAVE + 1];
-  __shared__ double cs64[RS_CHUNKS];
+  __shared__ double cs64[RS_SUMS];
   __shared__ double sh_mtot;
   __shared__ uint64_t sh_kt;
-  __shared__ uint32_t sh_it, sh_pt;
+  __shared__ uint32_t sh_it, sh_pt, sh_px, sh_wj;
   __shared__ uint32_t sh_b, sh_below, sh_cnt;
   __shared__ double sh_tau;
   const uint32_t n = a.n;
@@ -1241,7 +1331,7 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
       const uint32_t u = fc + threadIdx.x;
       ch.pc[threadIdx.x] = t.part_count[u]; ch.pb[threadIdx.x] = t.part_begin[u];
       ch.ptb[threadIdx.x] = t.pt_begin[u]; ch.sel[threadIdx.x] = t.sel_idx[u];
-      ch.wit[threadIdx.x] = t.wit[u]; ch.oct[threadIdx.x] = (uint32_t)(t.prefix[u] & 7u);
+      ch.widx[threadIdx.x] = sa.widx[u]; ch.oct[threadIdx.x] = (uint32_t)(t.prefix[u] & 7u);
       ch.m[threadIdx.x] = t.node_mass[u];
     }
     // the lanes' LDS writes before lane 0's reads (one wave)
@@ -1249,7 +1339,7 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (threadIdx.x == 0) {
-      build_segments(a, t, v, fc, nk, ch, g);
+      build_segments(a, t, s, sa, v, fc, nk, ch, g);
       // an internal node's float64 mass: its children's, summed in octant
       // order (read back by this block after the barriers below)
       if (fc != NONE) {
@@ -1260,16 +1350,49 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     }
   }
   for (int i = threadIdx.x; i < KBINS; i += BS) hist[i] = 0;
-  for (int i = threadIdx.x; i < 9 * (int)W; i += BS) pcnt[i] = 0;
+  if (threadIdx.x < 1024 / WAVE) pcnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) { sh_b = 0; sh_below = 0; sh_cnt = 0; }
   __syncthreads();
-  for_parts_bulk(g, sa, s, [&](int, uint32_t, uint32_t kb) { atomicAdd(&hist[kb], 1u); });
+  // ranges (and lists without a histogram): segments' chunks split over the waves
+  for (uint32_t k = 0; k < g.nseg; ++k) {
+    if (sa.lhist && g.is_list[k]) continue;
+    uint32_t lo, hi;
+    wave_part(g.cst[k + 1] - g.cst[k], w, W, lo, hi);
+    for_chunks(g, g.cst[k] + lo, g.cst[k] + hi, [&](uint32_t, uint32_t, uint32_t valid, uint4 x) {
+      const uint32_t wd[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int h = 0; h < (int)CHUNK; ++h)
+        if (valid & (1u << h)) atomicAdd(&hist[(wd[h >> 1] >> (16 * (h & 1))) & 0xFFFu], 1u);
+    });
+  }
   __syncthreads();
   uint32_t r = n;                            // 0-based rank of the witness among in-play
   {
-    const int per = KBINS / BS;
+    // a thread's run of bins: the ranges' counts plus the lists' histograms,
+    // four bins (8 bytes) of every list loaded together
+    const int per = KBINS / BS;              // 4 or more
     uint32_t loc = 0;
-    for (int i = 0; i < per; ++i) loc += hist[threadIdx.x * per + i];
+    for (int i0 = 0; i0 < per; i0 += 4) {
+      const int b = threadIdx.x * per + i0;
+      uint32_t h4[4] = {hist[b], hist[b + 1], hist[b + 2], hist[b + 3]};
+      if (sa.lhist) {
+        uint2 q[MAXSEG - 1];
+        // absent segments and ranges read list 0's bins, not added
+#pragma unroll
+        for (int k = 0; k < MAXSEG - 1; ++k) {
+          const bool use = k < (int)g.nseg && g.is_list[k];
+          q[k] = *reinterpret_cast<const uint2 *>(sa.lhist + (uint64_t)(use ? g.crank[k] : 0u) * KBINS + b);
+          if (!use) q[k] = make_uint2(0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < MAXSEG - 1; ++k) {
+          h4[0] += q[k].x & 0xFFFFu; h4[1] += q[k].x >> 16;
+          h4[2] += q[k].y & 0xFFFFu; h4[3] += q[k].y >> 16;
+        }
+        for (int i = 0; i < 4; ++i) hist[b + i] = h4[i];
+      }
+      loc += (h4[0] + h4[1]) + (h4[2] + h4[3]);
+    }
     uint32_t tot;
     const uint32_t ex = block_excl_scan<uint32_t>(loc, red32, tot);
     if (r >= ex && r < ex + loc) {
@@ -1281,6 +1404,18 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
       }
     }
     __syncthreads();
+    // this list's histogram: all of the bins below b0, what is left in b0
+    if (sa.lhist) {
+      const uint32_t b0 = sh_b, rest = n + 1 - sh_below;
+      uint16_t *lh = sa.lhist + (uint64_t)t.sel_idx[v] * KBINS;
+      for (int i0 = 0; i0 < per; i0 += 4) {
+        const uint32_t b = threadIdx.x * per + i0;
+        uint32_t x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = b + i < b0 ? hist[b + i] : b + i == b0 ? rest : 0u;
+        *reinterpret_cast<uint2 *>(lh + b) = make_uint2(x[0] | (x[1] << 16), x[2] | (x[3] << 16));
+      }
+    }
   }
   const uint32_t b0 = sh_b;
   r -= sh_below;
@@ -1305,7 +1440,7 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     const int sft = (phase == 0 ? kshift : ishift) - wb;
     for (int i = threadIdx.x; i < RADIX; i += BS) hist[i] = 0;
     __syncthreads();
-    for_parts(g, sa, s, [&](int, uint32_t p, uint32_t kb) {
+    for_parts(g, sa, s, [&](uint32_t p, uint32_t kb) {
       if (kb != b0) return;
       const uint64_t K = exact_K(a, s, p);
       bool match;
@@ -1337,13 +1472,21 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     else { ip = (ip << wb) | sh_b; ishift = sft; }
     __syncthreads();
   }
-  // collect the in-play candidates; count, per part, the candidates of lower
-  // bins and (once ranked) the in-play ones at or below the witness
+  // One pass over the key bins: per wave, the candidates below b0; the flags;
+  // those in b0 queued.  The flags and the queue have fixed room: a node with
+  // more candidates (an overfull leaf, n above 16383) or more of them in b0
+  // decides b0's candidates by their exact keys, and reads the key bins again
+  // where it would have read the flags.
+  const uint32_t C = g.cst[g.nseg];
+  const bool flagged = C <= FLAG_CHUNKS && sh_cnt0 <= (uint32_t)QCAP;
+  uint8_t *flags = reinterpret_cast<uint8_t *>(hist);
+  const uint32_t part = ((C + W - 1) / W + 3u) & ~3u;   // chunks per wave: whole words of flags
+  const uint32_t lo = min(C, w * part), hi = min(C, lo + part);
   if (threadIdx.x == 0) { ccount = 0; sh_pt = NONE; nq = 0; }
   __syncthreads();
-  // a candidate of bin b0 with exact key K: in play (collected) or, if not,
-  // counted when it lies below the in-play digits
-  auto visit_b0 = [&](uint32_t part, uint32_t p) {
+  // a candidate of bin b0: in play (collected) or, if not, taken when it lies
+  // below the in-play digits.  Returns false when it is surely not taken.
+  auto visit_b0 = [&](uint32_t x, uint32_t p, uint32_t wave) -> bool {
     const uint64_t K = exact_K(a, s, p);
     const uint32_t id = s.idx[p];
     bool inp, lower;
@@ -1356,82 +1499,81 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     }
     if (inp) {
       const uint32_t slot = atomicAdd(&ccount, 1u);
-      if (slot < SMALL) { ck[slot] = K; cidx[slot] = id; cpos[slot] = p; cpart[slot] = (uint16_t)part; }
+      if (slot < SMALL) { ck[slot] = K; cidx[slot] = id; cpos[slot] = p; ccode[slot] = x; crnk[slot] = 0; }
     } else if (lower) {
-      atomicAdd(&pcnt[part], 1u);
+      atomicAdd(&pcnt[wave], 1u);
     }
+    return inp || lower;
   };
+  // the flags as bits: bit x % 32 of word x / 32 is candidate code x
+  auto clear_flag = [&](uint32_t x) { atomicAnd(&hist[x / 32], ~(1u << (x % 32))); };
   {
     uint32_t below_cnt = 0;
-    int cur = -1;
-    if (sh_cnt0 <= QCAP) {
-      // bin-b0 candidates are queued in LDS and keyed afterwards by the whole block
-      for_parts_bulk(g, sa, s, [&](int k, uint32_t p, uint32_t kb) {
-        if (k != cur) {
-          if (cur >= 0 && below_cnt) atomicAdd(&pcnt[cur * W + w], below_cnt);
-          cur = k; below_cnt = 0;
-        }
-        if (kb < b0) ++below_cnt;
-        else if (kb == b0) {
-          const uint32_t q = atomicAdd(&nq, 1u);
-          qpos[q] = p; qpart[q] = (uint16_t)(k * W + w);
-        }
-      });
-      if (cur >= 0 && below_cnt) atomicAdd(&pcnt[cur * W + w], below_cnt);
+    for_chunks(g, lo, hi, [&](uint32_t c, uint32_t k, uint32_t valid, uint4 x) {
+      uint32_t le, eq;
+      compare_bins(x, b0, le, eq);
+      le &= valid; eq &= valid;
+      below_cnt += __popc(le & ~eq);
+      if (flagged) flags[c] = (uint8_t)le;
+      for (; eq; eq &= eq - 1u) {
+        const uint32_t x = c * CHUNK + __builtin_ctz(eq);
+        if (flagged) qcode[atomicAdd(&nq, 1u)] = x;
+        else visit_b0(x, cand_pos(g, sa, k, x), w);
+      }
+    });
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) below_cnt += __shfl_xor(below_cnt, o, WAVE);
+    if (lane == 0 && below_cnt) atomicAdd(&pcnt[w], below_cnt);
+    if (flagged) {
       __syncthreads();
       for (uint32_t q = threadIdx.x; q < nq; q += BS) {
-        // a queued list candidate is its index in the list: look up its position
-        const uint32_t k = qpart[q] / W, p = qpos[q];
-        visit_b0(qpart[q], g.is_list[k] ? entry_pos(sa, g.base[k] + p) : p);
+        const uint32_t x = qcode[q], c = x / CHUNK;
+        if (!visit_b0(x, cand_pos(g, sa, seg_of(g, c), x), c / part)) clear_flag(x);
       }
-    } else {
-      for_parts(g, sa, s, [&](int k, uint32_t p, uint32_t kb) {
-        if (k != cur) {
-          if (cur >= 0 && below_cnt) atomicAdd(&pcnt[cur * W + w], below_cnt);
-          cur = k; below_cnt = 0;
-        }
-        if (kb < b0) ++below_cnt;
-        else if (kb == b0) visit_b0(k * W + w, p);
-      });
-      if (cur >= 0 && below_cnt) atomicAdd(&pcnt[cur * W + w], below_cnt);
     }
   }
   __syncthreads();
   const uint32_t cc = min(ccount, (uint32_t)SMALL);
-  // The ranked candidates go into a hash table (sorted position -> taken),
-  // kept in the histogram's storage (no longer needed), so that the
-  // compaction pass decides them without recomputing their keys.
-  uint32_t *ht_key = hist, *ht_tk = hist + HT;
-  for (int i = threadIdx.x; i < HT; i += BS) ht_key[i] = NONE;
+  {
+    // Ranks of the in-play candidates: thread (f-quarter, pair of entries), so
+    // that every wave of the block compares and each entry read from LDS
+    // serves two.  Eight entries per step, every read issued before any
+    // compare (clamped indices, masked counts), and no branches.
+    const uint32_t half = (cc + 1) / 2, groups = max(1u, (uint32_t)BS / (uint32_t)(SMALL / 2));
+    const uint32_t e0 = threadIdx.x % (SMALL / 2), q = threadIdx.x / (SMALL / 2);
+    const uint32_t flen = (cc + groups - 1) / groups;
+    const uint32_t fb = min(cc, q * flen), fe = min(cc, fb + flen);
+    for (uint32_t e = e0; e < half; e += min((uint32_t)BS, (uint32_t)(SMALL / 2))) {
+      const uint32_t e2 = min(e + half, cc - 1);
+      const uint64_t K0 = ck[e], K1 = ck[e2];
+      const uint32_t I0 = cidx[e], I1 = cidx[e2];
+      uint32_t r0 = 0, r1 = 0;
+      for (uint32_t f0 = fb; f0 < fe; f0 += 8) {
+        uint64_t Kf[8];
+        uint32_t If[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t f = min(f0 + (uint32_t)u, cc - 1);
+          Kf[u] = ck[f];
+          If[u] = cidx[f];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const bool in = f0 + (uint32_t)u < fe;
+          r0 += (in & ((Kf[u] < K0) | ((Kf[u] == K0) & (If[u] < I0)))) ? 1u : 0u;
+          r1 += (in & ((Kf[u] < K1) | ((Kf[u] == K1) & (If[u] < I1)))) ? 1u : 0u;
+        }
+      }
+      if (r0) atomicAdd(&crnk[e], r0);
+      if (r1 && e + half < cc) atomicAdd(&crnk[e2], r1);
+    }
+  }
   __syncthreads();
   for (uint32_t e = threadIdx.x; e < cc; e += BS) {
-    const uint64_t Ke = ck[e];
-    const uint32_t Ie = cidx[e];
-    uint32_t rank = 0;
-    // eight entries per step, every read issued before any compare (clamped
-    // indices, masked counts), and no branches: the loop is bound by LDS
-    // throughput instead of one read's latency per entry
-    for (uint32_t f0 = 0; f0 < cc; f0 += 8) {
-      uint64_t Kf[8];
-      uint32_t If[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t f = min(f0 + (uint32_t)u, cc - 1);
-        Kf[u] = ck[f];
-        If[u] = cidx[f];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool lt = (Kf[u] < Ke) | ((Kf[u] == Ke) & (If[u] < Ie));
-        rank += (lt & (f0 + (uint32_t)u < cc)) ? 1u : 0u;
-      }
-    }
-    if (rank == r) { sh_kt = Ke; sh_it = Ie; sh_pt = cpos[e]; }
-    if (rank <= r) atomicAdd(&pcnt[cpart[e]], 1u);
-    const uint32_t pe = cpos[e];
-    uint32_t h = ht_slot(pe);
-    while (atomicCAS(&ht_key[h], NONE, pe) != NONE) h = (h + 1) & (HT - 1);   // keys are distinct
-    ht_tk[h] = rank <= r ? 1u : 0u;
+    const uint32_t rank = crnk[e], x = ccode[e];
+    if (rank == r) { sh_kt = ck[e]; sh_it = cidx[e]; sh_pt = cpos[e]; sh_px = x; }
+    if (rank <= r) atomicAdd(&pcnt[x / CHUNK / part], 1u);
+    else if (flagged) clear_flag(x);
   }
   __syncthreads();
   if (sh_pt == NONE || ccount > SMALL) {
@@ -1441,17 +1583,15 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
   }
   const uint64_t Kt = sh_kt;
   const uint32_t It = sh_it;
-  const uint32_t pt = sh_pt;
-  {
-    // part offsets (exclusive, candidate order; at most 9 x 16 parts)
-    const uint32_t np = g.nseg * W;
-    const uint32_t c = threadIdx.x < np ? pcnt[threadIdx.x] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan<uint32_t>(c, red32, tot);
-    if (threadIdx.x < np) pcnt[threadIdx.x] = ex;
-    if (threadIdx.x == 0) sh_total = tot;
+  const uint32_t pt = sh_pt, px = sh_px;
+  if (threadIdx.x < WAVE) {
+    // list offsets of the waves' parts (exclusive, candidate order)
+    const uint32_t c = threadIdx.x < W ? pcnt[threadIdx.x] : 0u;
+    const uint32_t inc = wave_incl_scan<uint32_t>(c);
+    if (threadIdx.x < W) pcnt[threadIdx.x] = inc - c;
+    if (threadIdx.x == WAVE - 1) sh_total = inc;
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == (BS > WAVE ? WAVE : 0)) {
     // the witness's tau
     const uint32_t kt = s.key[pt];
     const uint32_t snap_t = (a.n_snap > 1) ? (uint32_t)((uint64_t)kt >> (3 * a.D)) : 0u;
@@ -1464,156 +1604,131 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
     __syncthreads();
     return;
   }
-  // compaction pass: the n+1 list entries, in candidate (= sorted position) order
+  // the taken candidates' codes, in candidate (= sorted position) order: a lane
+  // takes 1, 2 or 4 chunks, so that all lanes have some (few candidates are
+  // mostly taken: eight codes per lane and step; of many, one in eight is)
+  uint32_t *srow = sa.src + (uint64_t)blockIdx.x * (n + 1);
+  {
+    uint32_t run = pcnt[w];
+    const uint32_t q = part > 512 ? 4u : part > 256 ? 2u : 1u;   // part is a multiple of 4
+    for (uint32_t c0 = lo; c0 < hi; c0 += q * WAVE) {
+      const uint32_t c = c0 + q * lane;
+      uint32_t m = 0;
+      if (flagged) {
+        if (c < hi) {
+          const uint32_t nc = min(q, hi - c);
+          m = (hist[c / 4] >> (CHUNK * (c % 4))) & (0xFFFFFFFFu >> (32 - CHUNK * nc));
+        }
+      } else {
+        for (uint32_t i = 0; i < q && c + i < hi; ++i) {
+          const uint32_t ci = c + i, k = seg_of(g, ci);
+          const uint4 x = *reinterpret_cast<const uint4 *>(g.kb[k] + (uint64_t)ci * CHUNK);
+          uint32_t valid = 0xFFu, le, eq;
+          if (ci == g.cst[k]) valid &= g.head[k];
+          if (ci + 1 == g.cst[k + 1]) valid &= g.tail[k];
+          compare_bins(x, b0, le, eq);
+          le &= valid; eq &= valid;
+          for (; eq; eq &= eq - 1u) {
+            const uint32_t h = __builtin_ctz(eq);
+            if (!taken_exact(a, s, cand_pos(g, sa, k, ci * CHUNK + h), Kt, It)) le &= ~(1u << h);
+          }
+          m |= le << (CHUNK * i);
+        }
+      }
+      const uint32_t cnt = __popc(m);
+      const uint32_t inc = wave_incl_scan<uint32_t>(cnt);
+      uint32_t o = run + inc - cnt;
+      run += (uint32_t)__builtin_amdgcn_readlane((int)inc, WAVE - 1);
+      const uint32_t x0 = c * CHUNK;
+      if (px - x0 < q * CHUNK && c < hi) sh_wj = o + __popc(m & ((1u << (px - x0)) - 1u));
+      for (; m; m &= m - 1u, ++o)
+        if (o <= n) srow[o] = x0 + __builtin_ctz(m);
+    }
+  }
+  __syncthreads();
+  // output pass, one taken candidate per lane: the list entry and the stored
+  // point with its unscaled float64 mass, kept in this block's scratch row
   const double tau = sh_tau;
   const bool out_ok = a.counts[1] <= a.point_cap;
-  uint32_t *out_pos = sa.lpos + (uint64_t)t.sel_idx[v] * (n + 1);
-  uint16_t *out_kb = sa.lkb + (uint64_t)t.sel_idx[v] * (n + 1);
-  uint2 *out_wm = sa.lwm + (uint64_t)t.sel_idx[v] * (n + 1);
+  const uint64_t lbase = (uint64_t)t.sel_idx[v] * (n + 1);
+  uint32_t *out_pos = sa.lpos + lbase;
+  uint16_t *out_kb = sa.lkb + lbase;
+  uint2 *out_wm = sa.lwm + lbase;
   double *mrow = sa.mhat + (uint64_t)blockIdx.x * n;
-  uint32_t *srow = sa.src + (uint64_t)blockIdx.x * (n + 1);
   const uint64_t ob = t.pt_begin[v];
   const int d = t.depth[v];
-  const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (WAVE - lane));
-  bool lists = false;
-  for (int k = 0; k < (int)g.nseg; ++k) lists |= g.is_list[k] != 0;
-  // whether a candidate of the threshold bin is taken: ranked above (the
-  // usual case) or decided by its exact key
-  auto taken_b0 = [&](uint32_t p) -> bool {
-    uint32_t h = ht_slot(p), found = 2u;
-    for (int pr = 0; pr < HT; ++pr) {
-      const uint32_t kh = ht_key[h];
-      if (kh == p) { found = ht_tk[h]; break; }
-      if (kh == NONE) break;
-      h = (h + 1) & (HT - 1);
-    }
-    if (found != 2u) return found != 0u;
-    return taken_exact(a, s, p, Kt, It);
-  };
-  if (!lists) {
-    // Only ranges: one pass writes the list and the stored points, the
-    // candidates' data loaded alongside their key bins (contiguous reads).
-    for (int k = 0; k < (int)g.nseg; ++k) {
-      uint32_t lo, hi;
-      wave_part(g.len[k], w, W, lo, hi);
-      uint32_t run = pcnt[k * W + w];
-      const uint64_t base = g.base[k];
-      for (uint32_t j0 = lo; j0 < hi; j0 += WAVE * FILP) {
-        uint32_t pp[FILP], kbv[FILP], wv[FILP];
-        PointIn q[FILP];
-        float mm[FILP];
+  const uint32_t wj = sh_wj;
+  for (uint32_t j0 = threadIdx.x; j0 <= n; j0 += BS * OILP) {
+    // An entry of a child's list takes position, key bin, weight and mass from
+    // that list and, unless it is the child's witness, id and codes from the
+    // child's stored point (each code gains the child's octant bit on top).
+    // The others are read from the sorted arrays.  Every load of a step is
+    // issued before any is used; a wave without entries of one kind skips its
+    // loads.
+    uint32_t cx[OILP], ks[OILP];
+    bool li[OILP];
 #pragma unroll
-        for (int u = 0; u < FILP; ++u) {
-          const uint32_t pu = (uint32_t)(base + min(j0 + u * WAVE + lane, hi - 1));
-          pp[u] = pu;
-          kbv[u] = s.kb[pu];
-          q[u] = read_point(s, pu);
-          wv[u] = s.w[pu];
-          mm[u] = s.m[pu];
-        }
-#pragma unroll
-        for (int u = 0; u < FILP; ++u) {
-          bool tk = j0 + u * WAVE + lane < hi && kbv[u] <= b0;
-          if (tk && kbv[u] == b0) tk = taken_b0(pp[u]);
-          const uint64_t bal = __ballot(tk);
-          const uint32_t o = run + (uint32_t)__popcll(bal & lt_mask);
-          run += (uint32_t)__popcll(bal);
-          if (tk && o <= n) {
-            out_pos[o] = pp[u];
-            out_kb[o] = (uint16_t)kbv[u];
-            out_wm[o] = make_uint2(wv[u], __float_as_uint(mm[u]));
-            if (out_ok && pp[u] != pt) {
-              const uint32_t j = o - (pp[u] > pt ? 1u : 0u);
-              const double mhat = (double)mm[u] / fmin(1.0, weight_pow(wv[u], a.alpha) / tau);
-              store_point_pos(a, t, q[u], ob + j, d);
-              mrow[j] = mhat;
-            }
-          }
-        }
-      }
+    for (int u = 0; u < OILP; ++u) {
+      cx[u] = srow[min(j0 + u * BS, n)];
+      ks[u] = seg_of(g, cx[u] / CHUNK);
+      li[u] = g.is_list[ks[u]] != 0;
     }
-  } else {
-    for (int k = 0; k < (int)g.nseg; ++k) {
-      uint32_t lo, hi;
-      wave_part(g.len[k], w, W, lo, hi);
-      uint32_t run = pcnt[k * W + w];
-      for (uint32_t j0 = lo; j0 < hi; j0 += WAVE * CILP) {
-        uint32_t pos[CILP], kb[CILP];
-        load_step<CILP>(g, k, sa, s, j0, hi, pos, kb);
+    uint32_t pos[OILP], kbv[OILP];
+    uint2 wm[OILP];
+    PointOut pq[OILP];
+    bool any_list = false, any_sorted = false;
 #pragma unroll
-        for (int u = 0; u < CILP; ++u) {
-          bool tk = j0 + u * WAVE + lane < hi && kb[u] <= b0;
-          if (tk && kb[u] == b0) tk = taken_b0(pos[u]);
-          const uint64_t bal = __ballot(tk);
-          const uint32_t o = run + (uint32_t)__popcll(bal & lt_mask);
-          run += (uint32_t)__popcll(bal);
-          if (tk && o <= n) {
-            out_pos[o] = pos[u];
-            out_kb[o] = (uint16_t)kb[u];
-            // an entry of a child's list: record where (segment, index in the
-            // child's list), so that the output pass reads it in list order
-            uint32_t src = NONE;
-            if (g.is_list[k] && n < (1u << 24)) src = ((uint32_t)k << 24) | (j0 + u * WAVE + lane);
-            srow[o] = src;
-          }
-        }
-      }
+    for (int u = 0; u < OILP; ++u) {
+      any_list |= li[u];
+      any_sorted |= !li[u];
     }
-    __syncthreads();
-    // output pass over the list (every lane busy): the list's (w, mass) and
-    // the stored points with their unscaled float64 masses, kept in this
-    // block's scratch row
-    for (uint32_t j0 = threadIdx.x; j0 <= n; j0 += BS * OILP) {
-      uint32_t pos[OILP], src[OILP];
+    if (__ballot(any_list)) {
+      uint32_t cq[OILP][3];
 #pragma unroll
       for (int u = 0; u < OILP; ++u) {
-        const uint32_t jl = min(j0 + u * BS, n);
-        pos[u] = min(out_pos[jl], sa.n_minus_1);
-        src[u] = srow[jl];
-      }
-      // An entry of a child's list takes (w, mass) from that list and, unless
-      // it is the child's witness, id and codes from the child's stored point
-      // (contiguous reads; each code gains the child's octant bit on top).
-      // The others are gathered from the sorted arrays.  Every lane issues
-      // both sets of loads at clamped addresses (the unused set hits one
-      // cached line).
-      PointIn q[OILP];
-      uint32_t cid[OILP], cq[OILP][3];
-      uint2 wm[OILP], lw[OILP];
-      bool cp[OILP];
-#pragma unroll
-      for (int u = 0; u < OILP; ++u) {
-        const bool fl = src[u] != NONE;
-        const uint32_t kk = fl ? src[u] >> 24 : 0u;
-        const uint32_t ic = src[u] & 0xFFFFFFu;
-        cp[u] = fl && pos[u] != g.cwit[kk];
-        const uint64_t ci = cp[u] ? g.cob[kk] + ic - (pos[u] > g.cwit[kk] ? 1u : 0u) : 0u;
-        q[u] = read_point(s, cp[u] ? pt : pos[u]);
-        cid[u] = t.pt_id[ci];
+        const uint32_t k = ks[u];
+        const uint64_t i = li[u] ? g.adj[k] + cx[u] : 0u;
+        // the child's stored point (a witness has none: some point in its place)
+        const uint64_t ci = li[u] ? g.cob[k] + min(cx[u] - g.cx0[k] - (cx[u] > g.cwx[k] ? 1u : 0u), n - 1) : 0u;
+        pos[u] = entry_pos(sa, i);
+        kbv[u] = sa.lkb[i];
+        wm[u] = sa.lwm[i];
+        pq[u].id = t.pt_id[ci];
         cq[u][0] = t.qx[ci]; cq[u][1] = t.qy[ci]; cq[u][2] = t.qz[ci];
-        lw[u] = sa.lwm[fl ? g.base[kk] + ic : 0u];
-        wm[u] = make_uint2(s.w[fl ? pt : pos[u]], __float_as_uint(s.m[fl ? pt : pos[u]]));
       }
 #pragma unroll
       for (int u = 0; u < OILP; ++u) {
-        const uint32_t jl = j0 + u * BS;
-        if (jl > n) continue;
-        const uint2 e = src[u] != NONE ? lw[u] : wm[u];
-        out_wm[jl] = e;
-        if (!out_ok || pos[u] == pt) continue;
-        const uint32_t j = jl - (pos[u] > pt ? 1u : 0u);
-        const double mhat = (double)__uint_as_float(e.y) / fmin(1.0, weight_pow(e.x, a.alpha) / tau);
-        if (cp[u]) {
-          const uint32_t oc = g.coct[src[u] >> 24];
-          t.pt_id[ob + j] = cid[u];
-          t.qx[ob + j] = (uint16_t)((cq[u][0] >> 1) | ((oc & 1u) << 15));
-          t.qy[ob + j] = (uint16_t)((cq[u][1] >> 1) | (((oc >> 1) & 1u) << 15));
-          t.qz[ob + j] = (uint16_t)((cq[u][2] >> 1) | (((oc >> 2) & 1u) << 15));
-        } else {
-          store_point_pos(a, t, q[u], ob + j, d);
-        }
-        mrow[j] = mhat;
+        const uint32_t oc = g.coct[ks[u]];
+        pq[u].xy = ((cq[u][0] >> 1) | ((oc & 1u) << 15)) | (((cq[u][1] >> 1) | (((oc >> 1) & 1u) << 15)) << 16);
+        pq[u].z = (cq[u][2] >> 1) | (((oc >> 2) & 1u) << 15);
+        if (li[u] && cx[u] == g.cwx[ks[u]]) pq[u] = code_point(a, read_point(s, pos[u]), d);   // one per list
       }
+    }
+    if (__ballot(any_sorted)) {
+      PointIn q[OILP];
+      uint32_t kk[OILP], ww[OILP], mm[OILP];
+#pragma unroll
+      for (int u = 0; u < OILP; ++u) {
+        const uint64_t p = li[u] ? (uint64_t)pt : g.adj[ks[u]] + cx[u];
+        kk[u] = s.kb[p]; ww[u] = s.w[p]; mm[u] = __float_as_uint(s.m[p]);
+        q[u] = read_point(s, p);
+        if (!li[u]) pos[u] = (uint32_t)p;
+      }
+#pragma unroll
+      for (int u = 0; u < OILP; ++u)
+        if (!li[u]) { kbv[u] = kk[u]; wm[u] = make_uint2(ww[u], mm[u]); pq[u] = code_point(a, q[u], d); }
+    }
+#pragma unroll
+    for (int u = 0; u < OILP; ++u) {
+      const uint32_t jl = j0 + u * BS;
+      if (jl > n) continue;
+      out_pos[jl] = pos[u];
+      out_kb[jl] = (uint16_t)kbv[u];
+      out_wm[jl] = wm[u];
+      if (!out_ok || jl == wj) continue;
+      const uint32_t j = jl - (jl > wj ? 1u : 0u);
+      store_codes(t, pq[u], ob + j);
+      mrow[j] = unscaled_mass(__uint_as_float(wm[u].y), wm[u].x, a.alpha, tau);
     }
   }
   __syncthreads();
@@ -1629,7 +1744,7 @@ __device__ void select_node(const BuildArgs &a, const TreeArgs &t, const Sorted 
         if (j0 + u * BS < n) t.pt_mass[ob + j0 + u * BS] = (float)(scale * mv[u]);
     }
   }
-  if (threadIdx.x == 0) t.wit[v] = pt;
+  if (threadIdx.x == 0) { t.wit[v] = pt; sa.widx[v] = wj; }
   __syncthreads();
 }
 
@@ -1885,6 +2000,8 @@ BuildLayout build_layout(uint64_t N, const lod_params &p, uint32_t n_snap) {
   L.lpos = take(4 * std::max<uint64_t>(1, max_sel * ((uint64_t)p.n + 1)));
   L.lkb = take(2 * std::max<uint64_t>(1, max_sel * ((uint64_t)p.n + 1)) + 16);
   L.lwm = take(8 * std::max<uint64_t>(1, max_sel * ((uint64_t)p.n + 1)));
+  L.lhist = keeps_list_hist(p.n) ? take(2 * KBINS * max_sel) : 0;
+  L.widx = take(4 * (size_t)L.node_cap);
   L.sel_rows = (uint32_t)std::min<uint64_t>(4096, N / ((uint64_t)p.n + 1) + n_snap + 1);
   L.mhat = take(8 * (size_t)L.sel_rows * p.n);
   L.src = take(4 * (size_t)L.sel_rows * ((uint64_t)p.n + 1));
@@ -2040,8 +2157,8 @@ lod_status launch_build(const lod_input &in, const lod_params &p, void *ws, cons
   if (side && hipStreamWaitEvent(st, side->join, 0) != hipSuccess) return LOD_EDEVICE;
 
   SelArgs sa{(uint32_t *)(W + L.lpos), (uint16_t *)(W + L.lkb), (uint2 *)(W + L.lwm), (uint32_t)(N - 1),
-             (double *)(W + L.mhat),
-             (uint32_t *)(W + L.src)};
+             keeps_list_hist(p.n) ? (uint16_t *)(W + L.lhist) : nullptr, (uint32_t *)(W + L.widx),
+             (double *)(W + L.mhat), (uint32_t *)(W + L.src)};
   const unsigned sel_threads = p.select_threads ? p.select_threads : 1024;
   // one scratch row of float64 masses per block
   const unsigned sel_grid = (unsigned)std::min<uint64_t>(L.sel_rows, per_level + 1);

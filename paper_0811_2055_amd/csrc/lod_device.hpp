@@ -153,15 +153,28 @@ __device__ __forceinline__ uint16_t quant_at(uint32_t cD, uint32_t lo16, int D, 
 // ---------------------------------------------------------------------------
 // Block-wide exclusive scan of one value per thread (LDS, any blockDim that
 // is a multiple of 64 and <= 1024).  `tmp` holds >= blockDim/64 + 1 entries.
+// Inclusive scan over the wave; 32-bit values on the lane-shift network (six
+// instructions) instead of six LDS permutes.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
-  const int lane = threadIdx.x & (WAVE - 1);
+  if constexpr (sizeof(T) == 4) {
+    uint32_t x = (uint32_t)v;
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast 15, 31
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
+    return (T)x;
+  } else {
+    const int lane = threadIdx.x & (WAVE - 1);
 #pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    T t = __shfl_up(v, o, WAVE);
-    if (lane >= o) v += t;
+    for (int o = 1; o < WAVE; o <<= 1) {
+      T t = __shfl_up(v, o, WAVE);
+      if (lane >= o) v += t;
+    }
+    return v;
   }
-  return v;
 }
 
 template <typename T>
