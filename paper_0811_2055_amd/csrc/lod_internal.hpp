@@ -33,6 +33,7 @@ void *workspace_view(void *ws, const BuildLayout &L, uint32_t which, uint64_t N,
 struct SplatLayout {
   uint32_t tiles_x, tiles_y, n_tiles;
   uint32_t units, chunks;            // binning units (waves), 64 per chunk
+  uint32_t slice;                    // pairs per accumulation slice
   uint64_t max_points, max_pairs, max_slices;
   bool aux;                          // an attribute channel is drawn
   size_t tile_count, tile_off, ucount, pchunk, slice_off, counters;
@@ -42,7 +43,7 @@ struct SplatLayout {
 
 constexpr int SPLAT_TS = 16;           // tile edge in pixels
 constexpr uint32_t SPLAT_MAX_TILES = 8192;
-constexpr uint32_t SPLAT_SLICE = 4096; // points per accumulation slice (4096: LOD splat 5.05 vs 5.11 ms at 2048)
+constexpr uint32_t SPLAT_SLICE = 4096; // pairs per accumulation slice of large renders
 constexpr uint32_t SPLAT_MAX_CHUNKS = 64;
 constexpr float BLOB_H_MIN = 1.0f;     // cubic blob: clamp of a projected world radius, pixels
 constexpr float BLOB_H_MAX = 16.0f;

@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 #include <cmath>
 
 #include "lod.h"
@@ -43,7 +44,10 @@ struct Cam {
   float norm;       // 1 / (2 pi sigma^2)
   float inv_s2;     // 1 / sigma^2
   int win;          // candidate half-window, ceil(R) + 2
-  int narrow;       // 1 when a blob covers fewer than 8 pixels per axis (R < 3.98)
+  int nin, nmax;    // pixels at most nin from the one that holds the point are covered, none beyond nmax is
+  float cn[5];      // exp2(kexp2 n^2), n = 0 .. 4
+  float cl[3];      // what float32 leaves of cn[0 .. 2]: the same rounding at every
+  float norm_lo;    // point would not average out; and of norm
   float kexp2;      // -log2(e) / (2 sigma^2): Gaussian factor = exp2(o^2 kexp2)
   uint32_t tiles_x, tiles_y;
   uint32_t blob;    // LOD_BLOB_GAUSSIAN or LOD_BLOB_CUBIC
@@ -67,8 +71,18 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   k.norm = (float)(1.0 / (2.0 * M_PI * s64 * s64));
   k.inv_s2 = (float)(1.0 / (s64 * s64));
   k.win = (int)std::ceil((double)k.R) + 2;
-  k.narrow = (double)k.R < 3.98 ? 1 : 0;
   k.kexp2 = (float)(-1.4426950408889634 / (2.0 * s64 * s64));
+  // the point lies within half a pixel of its pixel's centre; the binning admits
+  // pixels 1/100 further out, and its float32 range and the
+  // offsets are within 1/200 pixel of the exact ones
+  k.nin = (int)std::floor((double)k.R - 0.52);
+  k.nmax = (int)std::floor((double)k.R + 0.52);
+  for (int n = 0; n < 5; ++n) {
+    const double e = std::exp(-(double)(n * n) / (2.0 * s64 * s64));
+    k.cn[n] = (float)e;
+    if (n < 3) k.cl[n] = (float)(e - (double)k.cn[n]);
+  }
+  k.norm_lo = (float)(1.0 / (2.0 * M_PI * s64 * s64) - (double)k.norm);
   if (L) { k.tiles_x = L->tiles_x; k.tiles_y = L->tiles_y; }
   k.blob = sp.blob;
   k.hpx = sp.h_px;
@@ -838,6 +852,7 @@ __global__ void k_bin_chunkscan(uint32_t *__restrict__ pchunk, uint32_t nt, uint
 constexpr int PLAN_T = 1024;
 constexpr int PLAN_ITEMS = lodh::SPLAT_MAX_TILES / PLAN_T;
 __global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict__ tile_count, uint32_t nt,
+                                                      uint32_t slice,
                                                       uint32_t *__restrict__ tile_off,
                                                       uint32_t *__restrict__ slice_off, uint64_t *clear_status) {
   __shared__ uint32_t tmp[PLAN_T / WAVE + 1];
@@ -850,7 +865,7 @@ __global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict
 #pragma unroll
   for (int k = 0; k < PLAN_ITEMS; ++k) {
     pairs += cnt[k];
-    slices += (cnt[k] + lodh::SPLAT_SLICE - 1) / lodh::SPLAT_SLICE;
+    slices += (cnt[k] + slice - 1) / slice;
   }
   uint32_t tp, ts;
   uint32_t p = block_excl_scan<uint32_t>(pairs, tmp, tp);
@@ -859,7 +874,7 @@ __global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict
   for (int k = 0; k < PLAN_ITEMS; ++k) {
     if ((uint32_t)k < per && t0 + k < nt) { tile_off[t0 + k] = p; slice_off[t0 + k] = q; }
     p += cnt[k];
-    q += (cnt[k] + lodh::SPLAT_SLICE - 1) / lodh::SPLAT_SLICE;
+    q += (cnt[k] + slice - 1) / slice;
   }
   if (threadIdx.x == 0) {
     tile_off[nt] = tp;
@@ -881,8 +896,8 @@ template <class Src, class RecT, bool LDS>
 __global__ __launch_bounds__(BW) void k_bin_fill(Src src, Cam c, uint32_t units, uint32_t g, int nbits,
                                                  uint32_t *ucount, const uint32_t *__restrict__ pchunk,
                                                  const uint32_t *__restrict__ tile_off,
-                                                 const uint32_t *__restrict__ slice_off, uint2 *__restrict__ table,
-                                                 uint64_t max_slices, RecT *__restrict__ rec, uint64_t max_pairs,
+                                                 const uint32_t *__restrict__ slice_off, uint32_t slice,
+                                                 uint2 *__restrict__ table, uint64_t max_slices, RecT *__restrict__ rec, uint64_t max_pairs,
                                                  uint64_t *status) {
   extern __shared__ uint32_t lc[];
   const uint32_t nt = c.tiles_x * c.tiles_y;
@@ -890,8 +905,7 @@ __global__ __launch_bounds__(BW) void k_bin_fill(Src src, Cam c, uint32_t units,
     const uint32_t b = slice_off[t], e = slice_off[t + 1];
     const uint32_t p = tile_off[t], cnt = tile_off[t + 1] - p;
     for (uint32_t k = 0; b + k < e && b + k < max_slices; ++k)
-      table[b + k] = make_uint2(p + k * lodh::SPLAT_SLICE,
-                                t | (min(cnt - k * lodh::SPLAT_SLICE, lodh::SPLAT_SLICE) << 16));
+      table[b + k] = make_uint2(p + k * slice, t | (min(cnt - k * slice, slice) << 16));
   }
   if (tile_off[nt] > max_pairs) {
     if (threadIdx.x == 0) atomicOr((unsigned long long *)status, (unsigned long long)LOD_STATUS_CAPACITY);
@@ -918,17 +932,19 @@ __device__ __forceinline__ void neumaier(float &s, float &c, float x) {
 
 // --- accumulation --------------------------------------------------------------
 
-// One block per slice.  The blob is separable, so a chunk of 256 points adds
+// One block per slice.  The blob is separable, so a chunk of 64 points adds
 // Gy^T Gx to the 16x16 tile, with Gx[k][i] = exp(-ox^2/2s^2) and Gy[k][j] =
 // m norm exp(-oy^2/2s^2) inside point k's truncation square and 0 outside.
-// Phase A: thread k fills row k of Gx and Gy in LDS.  Phase B: wave g
-// contracts its own points 64g..64g+63 on the matrix cores (MFMA 16x16x4,
-// float32), each lane ending with 4 pixels of one column, and folds them
-// (at most 64 products each) into its compensated (Neumaier) float32 sums.
-// A wave reads only the rows its own lanes wrote, and LDS operations of one
-// wave complete in order, so the waves of a block run the chunks without
-// block barriers; at the end of the slice the four wave sums of each pixel
-// are folded in wave order.  No atomics: the image is bit-reproducible.
+// A wave forms its points' rows in LDS, one point per lane, reads them back as
+// the operands of 16 MFMA steps (16x16x4, float32) and adds the products (64
+// per pixel) to float64 sums, four pixels per lane; at the end of the slice the
+// four wave sums of each pixel are added in wave order.  A wave reads only rows
+// that its own lanes wrote, and the LDS operations of one wave complete in
+// order, so the waves of a block run their chunks without block barriers.  No
+// atomics: the image is bit-reproducible.
+//
+// Narrow blobs (k_accumulate_narrow) cover at most nine pixels per axis; wider
+// ones fill whole rows (k_accumulate_wide).
 // Pair record loads (the attribute of records that carry none is 0).
 __device__ __forceinline__ void load_rec(const float3 *r, uint64_t q, float &u, float &v, float &m, float &a) {
   const float3 t = r[q];
@@ -939,216 +955,299 @@ __device__ __forceinline__ void load_rec(const RecGA *r, uint64_t q, float &u, f
   u = t.x; v = t.y; m = t.z; a = t.w;
 }
 
-constexpr int GXS = TS + 1;          // padded row: conflict-free phase-A writes
 typedef float float4v __attribute__((ext_vector_type(4)));
+
+// The slices of a block and their records, loaded one chunk ahead across slice
+// boundaries (clamped indices: every load is issued unconditionally).  Pair
+// indices are 32-bit.
 template <class RecT>
-__global__ __launch_bounds__(PT) void k_accumulate(const uint2 *__restrict__ table,
-                                                   const uint32_t *__restrict__ slice_off, uint32_t nt,
-                                                   const RecT *__restrict__ rec, Cam c,
-                                                   float *__restrict__ partial, float *__restrict__ partial_aux,
-                                                   uint64_t max_slices, uint64_t max_pairs) {
-  constexpr bool AUX = RecInfo<RecT>::aux;
-  constexpr int PA = AUX ? PT : 1;
-  __shared__ float gx[PT][GXS];
-  __shared__ float gy[PT][GXS];
-  __shared__ float gya[PA][GXS];        // attribute channel: rows weighted by m a
-  __shared__ float part[4][TS * TS];   // the waves' slice sums
-  __shared__ float parta[AUX ? 4 : 1][AUX ? TS * TS : 1];
-  const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
-  const int grp = threadIdx.x / 64;                 // point group of phase B
-  const int col = threadIdx.x % TS;                 // pixel column of phase B
-  const int row0 = ((threadIdx.x % 64) / TS) * 4;   // first of 4 pixel rows of phase B
-  if (blockIdx.x >= total_slices) return;
-  // Each thread owns rows threadIdx.x of gx and gy for the whole launch.  In
-  // the narrow case they start at zero and each chunk clears only the
-  // previous chunk's 8-wide windows before writing its own.
-  int pwx = 0, pwy = 0;
-  if (c.narrow) {
-#pragma unroll
-    for (int e = 0; e < TS; ++e) {
-      gx[threadIdx.x][e] = 0.0f; gy[threadIdx.x][e] = 0.0f;
-      if (AUX) gya[threadIdx.x][e] = 0.0f;
-    }
-  }
-  // pair records are loaded one chunk ahead, across slice boundaries too
-  // (clamped indices: every load is issued unconditionally)
-  const uint64_t last = max_pairs - 1;
-  uint2 sd = table[blockIdx.x];
+struct SliceWalk {
+  const uint2 *table;
+  const RecT *rec;
+  uint32_t last, total, sl;
+  uint2 sd, nsd;
   float nu, nv, nm, na = 0.0f;
-  {
-    const uint64_t q = min((uint64_t)sd.x + threadIdx.x, last);
-    load_rec(rec, q, nu, nv, nm, na);
+  __device__ __forceinline__ void begin(const uint2 *tb, const RecT *r, uint32_t n, uint64_t max_pairs) {
+    table = tb; rec = r; total = n; last = (uint32_t)(max_pairs - 1);
+    sl = blockIdx.x;
+    sd = table[sl];
+    load_rec(rec, min(sd.x + threadIdx.x, last), nu, nv, nm, na);
+    peek();
   }
-  for (uint32_t sl = blockIdx.x; sl < total_slices; sl += gridDim.x) {
-    const uint32_t t = sd.y & 0xFFFFu;
-    const uint64_t pb = sd.x;
-    const uint64_t pe = min(pb + (sd.y >> 16), max_pairs);
-    const uint32_t nsl = sl + gridDim.x;
-    const uint2 nsd = table[min(nsl, total_slices - 1)];
-    const int tx0 = (int)(t % c.tiles_x) * TS, ty0 = (int)(t / c.tiles_x) * TS;
-    float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, c4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    float s4a[4] = {0.0f, 0.0f, 0.0f, 0.0f}, c4a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (uint64_t c0 = pb; c0 < pe; c0 += PT) {
-      const bool have = c0 + threadIdx.x < pe;
-      // lanes past the slice hold whatever the clamped prefetch read: zero them
-      // so that the 0/1 masking below multiplies finite values only
-      const float u = have ? nu : 0.0f, v = have ? nv : 0.0f, m = have ? nm : 0.0f;
-      const float pa = have ? na : 0.0f;
-      {
-        const uint64_t q = (c0 + PT < pe) ? c0 + PT + threadIdx.x : (uint64_t)nsd.x + threadIdx.x;
-        const uint64_t qc = min(q, last);
-        load_rec(rec, qc, nu, nv, nm, na);
-      }
-      // phase A: rows are zero outside the truncation square.  A pixel is
-      // covered when its float32 offset fl(t - (i + 1/2)) lies in [-R, R],
-      // tested pixel by pixel (the covered pixels of an axis form one run).
-      // Pixels past the image edge are computed and dropped by the final sum.
-      // The Gaussian factor is the hardware exp2 of o^2 (-log2 e / 2 sigma^2)
-      // (relative error ~3e-7, ample for 1e-5); lanes past the slice carry
-      // mass 0.
-      const float R = c.R;
-      const float w = m * c.norm;
-      const float wa = (m * pa) * c.norm;
-      if (c.narrow) {
-        // fewer than 8 covered pixels per axis: clear the previous window,
-        // then write an 8-wide window from a lower bound of the run's first
-        // pixel (float32 offsets are within 1/100 pixel of the exact ones);
-        // the rest of the row is still zero
-        const int lx = (int)ceilf(u - 0.5f - R - 0.01f), ly = (int)ceilf(v - 0.5f - R - 0.01f);
-        const int wx = min(max(lx - tx0, 0), TS - 8), wy = min(max(ly - ty0, 0), TS - 8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          gx[threadIdx.x][pwx + e] = 0.0f; gy[threadIdx.x][pwy + e] = 0.0f;
-          if (AUX) gya[threadIdx.x][pwy + e] = 0.0f;
-        }
-        pwx = wx; pwy = wy;
-        // pixel centres i + 1/2 are small half-integers: adding q to the
-        // first one is exact.  Away from the image's low edges (tile origin
-        // >= 48, so t > 32) t - c0 and then each - q are exact too (all are
-        // multiples of ulp(t) below 16 in magnitude), which saves an add per
-        // pixel and gives the same bits.
-        const float cx0 = (float)(tx0 + wx) + 0.5f, cy0 = (float)(ty0 + wy) + 0.5f;
-        float oxs[8], oys[8];
-        if (tx0 >= 48) {
-          const float dx = u - cx0;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) oxs[q] = dx - (float)q;
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) oxs[q] = u - (cx0 + (float)q);
-        }
-        if (ty0 >= 48) {
-          const float dy = v - cy0;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) oys[q] = dy - (float)q;
-        } else {
-#pragma unroll
-          for (int q = 0; q < 8; ++q) oys[q] = v - (cy0 + (float)q);
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const float ox = oxs[q], oy = oys[q];
-          // exp2 of a non-positive finite argument lies in [0, 1]
-          const float ex = __builtin_amdgcn_exp2f((ox * ox) * c.kexp2);
-          const float ey = __builtin_amdgcn_exp2f((oy * oy) * c.kexp2);
-          gx[threadIdx.x][wx + q] = fabsf(ox) <= R ? ex : 0.0f;
-          gy[threadIdx.x][wy + q] = fabsf(oy) <= R ? w * ey : 0.0f;
-          if (AUX) gya[threadIdx.x][wy + q] = fabsf(oy) <= R ? wa * ey : 0.0f;
-        }
-      } else {
-        const float cx0 = (float)tx0 + 0.5f, cy0 = (float)ty0 + 0.5f;
-#pragma unroll
-        for (int e = 0; e < TS; ++e) {
-          const float ox = u - (cx0 + (float)e);
-          const float oy = v - (cy0 + (float)e);
-          const float ex = __builtin_amdgcn_exp2f((ox * ox) * c.kexp2);
-          const float ey = __builtin_amdgcn_exp2f((oy * oy) * c.kexp2);
-          gx[threadIdx.x][e] = fabsf(ox) <= R ? ex : 0.0f;
-          gy[threadIdx.x][e] = fabsf(oy) <= R ? w * ey : 0.0f;
-          if (AUX) gya[threadIdx.x][e] = fabsf(oy) <= R ? wa * ey : 0.0f;
-        }
-      }
-      // the rows of this wave's points were written by this wave
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // phase B: wave g accumulates points 64g..64g+63 with 16 MFMA steps of
-      // 16x16x4 (float32); lane l feeds A[l%16][l/16] = Gy[k][row] and
-      // B[l/16][l%16] = Gx[k][col] and receives rows 4(l/16)..+3 of column l%16
-      const int kb = grp * 64;
-      const int ln = threadIdx.x % 64;
-      float4v acc4 = {0.0f, 0.0f, 0.0f, 0.0f};
-      float av[16], bv[16];   // all LDS operands first: one wait, not sixteen
-#pragma unroll
-      for (int st = 0; st < 16; ++st) {
-        const int kk = kb + st * 4 + ln / 16;
-        av[st] = gy[kk][ln % 16];
-        bv[st] = gx[kk][ln % 16];
-      }
-      __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the products
-#pragma unroll
-      for (int st = 0; st < 16; ++st) acc4 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv[st], acc4, 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) neumaier(s4[i], c4[i], acc4[i]);
-      if (AUX) {
-        float4v acc4a = {0.0f, 0.0f, 0.0f, 0.0f};
-        float aa[16];
-#pragma unroll
-        for (int st = 0; st < 16; ++st) aa[st] = gya[kb + st * 4 + ln / 16][ln % 16];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-          acc4a = __builtin_amdgcn_mfma_f32_16x16x4f32(aa[st], bv[st], acc4a, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) neumaier(s4a[i], c4a[i], acc4a[i]);
-      }
-      // the next chunk rewrites this wave's rows after its reads above
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) part[grp][(row0 + i) * TS + col] = s4[i] + c4[i];
-    if (AUX) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) parta[grp][(row0 + i) * TS + col] = s4a[i] + c4a[i];
-    }
-    __syncthreads();
-    float s = 0.0f, cc = 0.0f;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) neumaier(s, cc, part[g][threadIdx.x]);
-    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = s + cc;
-    if (AUX) {
-      float sa = 0.0f, ca = 0.0f;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) neumaier(sa, ca, parta[g][threadIdx.x]);
-      partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = sa + ca;
-    }
+  __device__ __forceinline__ void peek() { nsd = table[min(sl + gridDim.x, total - 1)]; }
+  // records of the slice (all inside the record array)
+  __device__ __forceinline__ uint32_t count() const { return min(sd.y >> 16, last - sd.x + 1u); }
+  // this thread's record of the chunk at offset o (0 past the slice's n), and the next load
+  __device__ __forceinline__ void take(uint32_t o, uint32_t n, float &u, float &v, float &m, float &a) {
+    const bool have = o + threadIdx.x < n;
+    u = have ? nu : 0.0f; v = have ? nv : 0.0f; m = have ? nm : 0.0f; a = have ? na : 0.0f;
+    const uint32_t next = o + PT < n ? sd.x + o + PT : nsd.x;
+    load_rec(rec, min(next + threadIdx.x, last), nu, nv, nm, na);
+  }
+  __device__ __forceinline__ void next() {
+    sl += gridDim.x;
     sd = nsd;
-    __syncthreads();
+    peek();
+  }
+};
+
+// Value of lane `from` of each row of 16 lanes, in all lanes of the row.
+template <int FROM>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + FROM, 0xF, 0xF, true);
+}
+
+// Calls f(integral_constant<int, 0>) .. f(integral_constant<int, 15>).
+template <class F, int... T>
+__device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
+  (f(std::integral_constant<int, T>{}), ...);
+}
+
+// Narrow blobs: radius below 3.98 pixels, sigma at least 1/2.  The Gaussian of
+// the pixel n steps from the one that holds the point (offset d - n, |d| <=
+// 1/2) is exp2(k d^2) exp2(-2 k d)^n exp2(k n^2): three hardware exponentials
+// of small arguments per axis and a chain of products, where every pixel took
+// an exponential of its own (whose argument, up to 6.5, carried more rounding
+// than the products do).  Only the pixels between nin and nmax steps away need
+// the truncation test.
+//
+// A point's window of up to nine values goes to the same columns of its row,
+// 0 .. 2 nmax, with at least 15 zeros on either side that nothing overwrites, so
+// that the writes have no bank conflicts and nothing is cleared between
+// chunks; the reader of pixel p of point k starts p - (window origin) further
+// on, an address that one lane-broadcast add gives (lane l holds point l; the
+// points 16 r .. 16 r + 15 are the r-th operands of the 16 steps).  x rows are
+// read before y rows overwrite them, which halves the LDS per wave.
+//
+// Bound by vector issue beside the matrix steps (a chunk of 64 points: about
+// 150 vector instructions and 16 matrix steps of 32 cycles).  150 M points
+// drawn at 1024^2, 285 M pairs: 2.31 -> 1.88 ms against a form that cleared and
+// wrote 8-wide windows at varying columns (LDS bank conflicts half of the LDS
+// time, 16 exponentials per point, four waves per SIMD; now six).  Error of
+// that image against float64 3.5e-8 -> 3.1e-8.
+constexpr int NPAD = TS - 1;
+constexpr int NROW = 9 + TS;                  // odd: lane i's window starts on its own bank
+constexpr int NWAVE = NPAD + WAVE * NROW;     // a wave's rows: the zeros after one row precede the next
+template <class RecT>
+__global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restrict__ table,
+                                                          const uint32_t *__restrict__ slice_off, uint32_t nt,
+                                                          const RecT *__restrict__ rec, Cam c,
+                                                          float *__restrict__ partial,
+                                                          float *__restrict__ partial_aux, uint64_t max_slices,
+                                                          uint64_t max_pairs) {
+  constexpr bool AUX = RecInfo<RecT>::aux;
+  constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
+  __shared__ float rows[NW][NWAVE];
+  const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
+  if (blockIdx.x >= total_slices) return;
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  const int px = lane % TS;                         // operand pixel; column of the sums
+  for (int i = lane; i < NWAVE; i += WAVE) rows[w][i] = 0.0f;
+  float *mine = &rows[w][NPAD + lane * NROW];       // this lane's window
+  const uint32_t pxb = 4u * (uint32_t)(w * NWAVE + px);
+  auto at_byte = [&](uint32_t o) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(rows) + o); };
+  const int nmax = c.nmax, nin = c.nin;
+  SliceWalk<RecT> sw;
+  sw.begin(table, rec, total_slices, max_pairs);
+  for (; sw.sl < total_slices; sw.next()) {
+    const uint32_t t = sw.sd.y & 0xFFFFu;
+    const uint32_t pn = sw.count();
+    const int tx0 = (int)(t % c.tiles_x) * TS, ty0 = (int)(t / c.tiles_x) * TS;
+    double sum[NCH][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[0][i] = sum[NCH - 1][i] = 0.0;
+    for (uint32_t c0 = 0; c0 < pn; c0 += PT) {
+      float u, v, m, at;
+      sw.take(c0, pn, u, v, m, at);
+      // the window of one axis, scaled by w0; returns where its row's pixel 0
+      // lies (in bytes from the wave's rows)
+      auto window = [&](float x, int t0, float w0) -> uint32_t {
+        const float fc = floorf(x);
+        const float d = x - (fc + 0.5f);
+        const float tw = -2.0f * c.kexp2 * d;
+        const float rp = __builtin_amdgcn_exp2f(tw), rm = __builtin_amdgcn_exp2f(-tw);
+        const float e0 = w0 * __builtin_amdgcn_exp2f((d * d) * c.kexp2);
+        const float R = c.R;
+        float ep = e0, em = e0;
+        mine[nmax] = (nin >= 0 || fabsf(d) <= R) ? e0 : 0.0f;
+#pragma unroll
+        for (int n = 1; n <= 4; ++n) {
+          if (n > nmax) break;                                  // uniform
+          ep *= rp;
+          em *= rm;
+          float vp = n < 3 ? __builtin_fmaf(ep, c.cn[n], ep * c.cl[n < 3 ? n : 0]) : ep * c.cn[n];
+          float vm = n < 3 ? __builtin_fmaf(em, c.cn[n], em * c.cl[n < 3 ? n : 0]) : em * c.cn[n];
+          if (n > nin) {
+            vp = fabsf(x - ((fc + (float)n) + 0.5f)) <= R ? vp : 0.0f;
+            vm = fabsf(x - ((fc - (float)n) + 0.5f)) <= R ? vm : 0.0f;
+          }
+          mine[nmax + n] = vp;
+          mine[nmax - n] = vm;
+        }
+        // a pair's window meets the tile: its origin lies in [-2 nmax, 15]
+        // (lanes past the slice: any place inside the row)
+        const int wx = min(max((int)fc - nmax - t0, -2 * nmax), TS - 1);
+        return 4u * (uint32_t)(lane * NROW + NPAD - wx);
+      };
+      float av[16], bv[16];
+      const uint32_t rx = window(u, tx0, 1.0f);
+      wave_sync_mem();
+      for_16([&](auto st) { bv[st] = at_byte(row_bcast<st>(rx) + pxb); }, std::make_integer_sequence<int, 16>{});
+      wave_sync_mem();
+      const uint32_t ry = window(v, ty0, __builtin_fmaf(m, c.norm, m * c.norm_lo));
+      wave_sync_mem();
+      for_16([&](auto st) { av[st] = at_byte(row_bcast<st>(ry) + pxb); }, std::make_integer_sequence<int, 16>{});
+      wave_sync_mem();
+      float4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int st = 0; st < 16; ++st) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv[st], acc, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[0][i] += (double)acc[i];
+      if constexpr (AUX) {
+        // the second channel's rows are the first's times the point's attribute
+        for_16([&](auto st) { av[st] *= __uint_as_float(row_bcast<st>(__float_as_uint(at))); },
+               std::make_integer_sequence<int, 16>{});
+        float4v acc2 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int st = 0; st < 16; ++st) acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv[st], acc2, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[NCH - 1][i] += (double)acc2[i];
+      }
+    }
+    // the wave sums of each pixel, through the first 256 floats of the rows
+    // (lane l holds rows 4 (l / 16) .. + 3 of column l % 16)
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      wave_sync_mem();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rows[w][((lane / TS) * 4 + i) * TS + px] = (float)sum[ch][i];
+      __syncthreads();
+      double s = 0.0;
+#pragma unroll
+      for (int g = 0; g < NW; ++g) s += (double)rows[g][threadIdx.x];
+      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = (float)s;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rows[w][i * WAVE + lane] = 0.0f;
+    wave_sync_mem();
   }
 }
 
-// Sum each tile's slice partials in slice order and write the image.
-__global__ __launch_bounds__(PT) void k_finalize(const uint32_t *__restrict__ slice_off, uint32_t nt,
-                                                 const float *__restrict__ partial, Cam c,
-                                                 float *__restrict__ image, uint64_t max_slices) {
-  for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
-    const uint32_t b = slice_off[t], e = slice_off[t + 1];
-    float s = 0.0f, cc = 0.0f;
-    // (a tile in front of a dense clump has a thousand slices: eight are loaded together)
-    const uint32_t e1 = (uint32_t)min((uint64_t)e, max_slices);
-    for (uint32_t sl = b; sl < e1; sl += 8) {
-      float v[8];
+// Wider blobs: whole rows of 16 values, every pixel with its own exponential
+// (relative error ~3e-7) and truncation test.
+constexpr int GXS = TS + 1;          // padded row: conflict-free writes
+template <class RecT>
+__global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict__ table,
+                                                        const uint32_t *__restrict__ slice_off, uint32_t nt,
+                                                        const RecT *__restrict__ rec, Cam c,
+                                                        float *__restrict__ partial, float *__restrict__ partial_aux,
+                                                        uint64_t max_slices, uint64_t max_pairs) {
+  constexpr bool AUX = RecInfo<RecT>::aux;
+  constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
+  __shared__ float gx[PT][GXS];
+  __shared__ float gy[PT][GXS];
+  __shared__ float part[NW][TS * TS];   // the waves' slice sums
+  const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
+  if (blockIdx.x >= total_slices) return;
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  SliceWalk<RecT> sw;
+  sw.begin(table, rec, total_slices, max_pairs);
+  for (; sw.sl < total_slices; sw.next()) {
+    const uint32_t t = sw.sd.y & 0xFFFFu;
+    const uint32_t pn = sw.count();
+    const int tx0 = (int)(t % c.tiles_x) * TS, ty0 = (int)(t / c.tiles_x) * TS;
+    double sum[NCH][4];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = partial[(uint64_t)min(sl + k, e1 - 1) * (TS * TS) + threadIdx.x];
+    for (int i = 0; i < 4; ++i) sum[0][i] = sum[NCH - 1][i] = 0.0;
+    for (uint32_t c0 = 0; c0 < pn; c0 += PT) {
+      float u, v, m, at;
+      sw.take(c0, pn, u, v, m, at);
+      // A pixel is covered when its float32 offset fl(t - (i + 1/2)) lies in
+      // [-R, R].  Pixels past the image edge are computed and dropped by the
+      // final sum; lanes past the slice carry mass 0.
+      const float R = c.R, w0 = __builtin_fmaf(m, c.norm, m * c.norm_lo);
+      const float cx0 = (float)tx0 + 0.5f, cy0 = (float)ty0 + 0.5f;
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (sl + k < e1) neumaier(s, cc, v[k]);
+      for (int e = 0; e < TS; ++e) {
+        const float ox = u - (cx0 + (float)e), oy = v - (cy0 + (float)e);
+        const float ex = __builtin_amdgcn_exp2f((ox * ox) * c.kexp2);
+        const float ey = __builtin_amdgcn_exp2f((oy * oy) * c.kexp2);
+        gx[threadIdx.x][e] = fabsf(ox) <= R ? ex : 0.0f;
+        gy[threadIdx.x][e] = fabsf(oy) <= R ? w0 * ey : 0.0f;
+      }
+      wave_sync_mem();
+      float av[16], bv[16];   // all LDS operands first: one wait, not sixteen
+#pragma unroll
+      for (int st = 0; st < 16; ++st) {
+        const int kk = w * WAVE + (lane / TS) * 16 + st;
+        av[st] = gy[kk][lane % TS];
+        bv[st] = gx[kk][lane % TS];
+      }
+      wave_sync_mem();        // the next chunk rewrites this wave's rows after its reads
+      float4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int st = 0; st < 16; ++st) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv[st], acc, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[0][i] += (double)acc[i];
+      if constexpr (AUX) {
+        for_16([&](auto st) { av[st] *= __uint_as_float(row_bcast<st>(__float_as_uint(at))); },
+               std::make_integer_sequence<int, 16>{});
+        float4v acc2 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int st = 0; st < 16; ++st) acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv[st], acc2, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[NCH - 1][i] += (double)acc2[i];
+      }
     }
-    const int i = (int)(t % c.tiles_x) * TS + (threadIdx.x % TS);
-    const int j = (int)(t / c.tiles_x) * TS + (threadIdx.x / TS);
-    if (i < (int)c.W && j < (int)c.H) image[(uint64_t)j * c.W + i] = s + cc;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) part[w][((lane / TS) * 4 + i) * TS + lane % TS] = (float)sum[ch][i];
+      __syncthreads();
+      double s = 0.0;
+#pragma unroll
+      for (int g = 0; g < NW; ++g) s += (double)part[g][threadIdx.x];
+      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = (float)s;
+      __syncthreads();
+    }
+  }
+}
+
+// Sum each tile's slice partials and write the image: FIN_G groups of 256
+// threads (a thread per pixel) add a contiguous share of the slices each, in
+// slice order in float64, sixteen loaded together (a tile in front of a dense
+// clump has thousands of slices), and the shares are added in order.
+constexpr int FIN_G = 4;
+__global__ __launch_bounds__(FIN_G * PT) void k_finalize(const uint32_t *__restrict__ slice_off, uint32_t nt,
+                                                         const float *__restrict__ partial, Cam c,
+                                                         float *__restrict__ image, uint64_t max_slices) {
+  __shared__ double share[FIN_G - 1][PT];
+  const uint32_t g = threadIdx.x / PT, p = threadIdx.x % PT;
+  for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
+    const uint32_t b = slice_off[t], e = (uint32_t)min((uint64_t)slice_off[t + 1], max_slices);
+    const uint32_t per = e > b ? (e - b + FIN_G - 1) / FIN_G : 0u;
+    const uint32_t b1 = min(e, b + g * per), e1 = min(e, b1 + per);
+    double s = 0.0;
+    for (uint32_t sl = b1; sl < e1; sl += 16) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = partial[(uint64_t)min(sl + k, e1 - 1) * (TS * TS) + p];
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (sl + k < e1) s += (double)v[k];
+    }
+    if (e > b + 1) {   // uniform: a single slice is its own sum
+      if (g) share[g - 1][p] = s;
+      __syncthreads();
+      if (g == 0)
+        for (int k = 0; k < FIN_G - 1; ++k) s += share[k][p];
+      __syncthreads();
+    }
+    if (g) continue;
+    const int i = (int)(t % c.tiles_x) * TS + (int)(p % TS);
+    const int j = (int)(t / c.tiles_x) * TS + (int)(p / TS);
+    if (i < (int)c.W && j < (int)c.H) image[(uint64_t)j * c.W + i] = (float)s;
   }
 }
 
@@ -1750,10 +1849,7 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   if (max_points >= (1ull << 32)) return LOD_EUNSUPPORTED;
   L.max_pairs = std::max<uint64_t>(1, max_points * tpa * tpa);
   if (L.max_pairs >= (1ull << 32)) return LOD_EUNSUPPORTED;
-  L.max_slices = nt + L.max_pairs / SPLAT_SLICE + 1;
   L.aux = aux;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   // Units: 64 per chunk.  A unit's row of the count table is written, scanned
   // and read, so a unit holds at least half as many points as there are tiles
   // (8 bytes of table per point), but no more than 2048 while there are fewer
@@ -1764,17 +1860,43 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS,
                                           std::max<uint64_t>(1, (max_points + 64 * unit - 1) / (64 * unit)));
   L.units = 64 * L.chunks;
-  L.tile_count = take(4 * (nt + 1));
-  L.tile_off = take(4 * (nt + 1));
-  L.ucount = take(4 * (size_t)L.units * nt);
-  L.pchunk = take(4 * (size_t)L.chunks * nt);
-  L.slice_off = take(4 * (nt + 1));
-  L.counters = take(64);
-  L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
-  L.partial = take(4 * (size_t)TS * TS * L.max_slices);
-  L.partial_aux = aux ? take(4 * (size_t)TS * TS * L.max_slices) : L.partial;
-  L.slice_table = take(8 * (size_t)L.max_slices);
-  L.total = off;
+  auto lay_out = [&](uint32_t units, uint32_t slice) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
+    L.slice = slice;
+    L.max_slices = nt + L.max_pairs / slice + 1;
+    L.tile_count = take(4 * (nt + 1));
+    L.tile_off = take(4 * (nt + 1));
+    L.ucount = take(4 * (size_t)units * nt);
+    L.pchunk = take(4 * (size_t)(units / 64) * nt);
+    L.slice_off = take(4 * (nt + 1));
+    L.counters = take(64);
+    L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
+    L.partial = take(4 * (size_t)TS * TS * L.max_slices);
+    L.partial_aux = aux ? take(4 * (size_t)TS * TS * L.max_slices) : L.partial;
+    L.slice_table = take(8 * (size_t)L.max_slices);
+    return L.total = off;
+  };
+  // Slices: a block's share of a tile's pairs.  Long slices of dense tiles end
+  // last and leave CUs idle (a 262 k point frame is 256 tiles: 20.6 us of
+  // accumulation in slices of 4096, 9.3 in slices of 512; 16 k points 16.7 and
+  // 5.2; the cubic blob's slices take longer: 4 M points 447 us at 4096, 337 at
+  // 1024; 16.7 M at 1024^2, Gaussian 158 and 153 at 2048, cubic 388 and 345);
+  // 150 M points fill the chip either way.  Shorter slices take more
+  // workspace: near the size of the library's fixed one they stay at 4096, so
+  // that it holds the renders that it held.  The image depends on the slice
+  // length, so this depends on the arguments alone, in the workspace's
+  // smallest form.
+  const bool cubic = sp.blob == LOD_BLOB_CUBIC;
+  const uint32_t want = max_points <= (1u << 19)   ? 512u
+                        : max_points <= (1u << 25) ? (cubic ? 1024u : 2048u)
+                                                   : SPLAT_SLICE;
+  const uint32_t few = (uint32_t)std::min<uint64_t>(
+      SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (max_points + (64 * 2048) - 1) / (64 * 2048)));
+  const bool near_fixed = lay_out(64 * few, want) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
+                          lay_out(64 * few, SPLAT_SLICE) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
+  const uint32_t slice = near_fixed ? SPLAT_SLICE : want;
+  lay_out(L.units, slice);
   return LOD_OK;
 }
 
@@ -1827,12 +1949,12 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
     if (L.chunks > 1)
       LOD_LAUNCH(k_bin_chunkscan, dim3((nt + 255) / 256), dim3(256), 0, st, pchunk, nt, L.chunks, tcount);
   }
-  LOD_LAUNCH(k_tile_plan, dim3(1), dim3(PLAN_T), 0, st, any ? tcount : (uint32_t *)nullptr, nt, toff, soff,
+  LOD_LAUNCH(k_tile_plan, dim3(1), dim3(PLAN_T), 0, st, any ? tcount : (uint32_t *)nullptr, nt, L.slice, toff, soff,
              status_word ? (uint64_t *)nullptr : ctr);
   if (any) {
     auto fill = [&](auto kernel, uint32_t g, size_t bytes) {
       LOD_LAUNCH_NAMED("k_bin_fill", kernel, dim3(L.units / g), dim3(BW), bytes, st, src, c, L.units, g, nbits,
-                       ucount, pre, toff, soff, stab, L.max_slices, rec, L.max_pairs, status);
+                       ucount, pre, toff, soff, L.slice, stab, L.max_slices, rec, L.max_pairs, status);
     };
     // with cursors in LDS, blocks of two units when there are many (32-bit
     // cursors take twice the LDS of the 16-bit counts: fewer resident waves)
@@ -1848,14 +1970,22 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
     if constexpr (RecInfo<RecT>::cubic) {
       LOD_LAUNCH(k_accumulate_cubic<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
                  partial_aux, L.max_slices, L.max_pairs);
-    } else
-      LOD_LAUNCH(k_accumulate<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial, partial_aux,
-                 L.max_slices, L.max_pairs);
+    } else {
+      // the narrow form's windows hold nine pixels; below sigma = 1/2 its
+      // products could overflow where the Gaussian itself underflows
+      const bool narrow = c.R < 3.98f && sp.sigma_px >= 0.5f;
+      auto acc = [&](auto kernel) {
+        LOD_LAUNCH_NAMED("k_accumulate", kernel, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
+                         partial_aux, L.max_slices, L.max_pairs);
+      };
+      if (narrow) acc(k_accumulate_narrow<RecT>);
+      else acc(k_accumulate_wide<RecT>);
+    }
   }
-  LOD_LAUNCH(k_finalize, dim3(std::min<uint32_t>(nt, 4096)), dim3(PT), 0, st, soff, nt, partial, c, image,
+  LOD_LAUNCH(k_finalize, dim3(std::min<uint32_t>(nt, 4096)), dim3(FIN_G * PT), 0, st, soff, nt, partial, c, image,
              L.max_slices);
   if constexpr (RecInfo<RecT>::aux)
-    LOD_LAUNCH(k_finalize, dim3(std::min<uint32_t>(nt, 4096)), dim3(PT), 0, st, soff, nt, partial_aux, c,
+    LOD_LAUNCH(k_finalize, dim3(std::min<uint32_t>(nt, 4096)), dim3(FIN_G * PT), 0, st, soff, nt, partial_aux, c,
                image_aux, L.max_slices);
   return hipGetLastError() == hipSuccess ? LOD_OK : LOD_EDEVICE;
 }

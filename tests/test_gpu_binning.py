@@ -101,3 +101,34 @@ def test_cubic_window_classes(order, aux):
     for g, w in pairs:
         err, zeros_ok = image_rel_err(g.cpu().numpy(), w)
         assert zeros_ok and err <= TOL, err
+
+
+@pytest.mark.parametrize("sigma,radius", [(0.3, 1.0), (0.49, 6.0), (0.5, 0.8), (0.5, 1.0), (0.5, 6.0), (0.663, 6.0),
+                                          (1.0, 2.5), (1.0, 3.49), (1.0, 3.5), (1.326, 3.0), (1.327, 3.0)])
+def test_gaussian_window_edges(sigma, radius):
+    """Truncation radii at the edges of the narrow form's windows (one to nine
+    pixels, tests on none, one and two of them) and of its range, both image
+    channels, points on pixel and tile edges and outside the image."""
+    import torch
+    W, H, n = 70, 50, 3000
+    rng = np.random.default_rng(8)
+    x = rng.uniform(-0.1, 1.1, n).astype(np.float32)
+    y = rng.uniform(-0.1, 1.1, n).astype(np.float32)
+    x[:400] = (rng.integers(0, 2 * W + 1, 400) / 2 / W).astype(np.float32)     # pixel edges and centres
+    y[200:600] = (rng.integers(0, 2 * H + 1, 400) / 2 / H).astype(np.float32)
+    x[600:700] = (16 * rng.integers(0, 5, 100) / W).astype(np.float32)          # tile edges
+    z = rng.random(n).astype(np.float32)
+    m = rng.uniform(0.1, 1.0, n).astype(np.float32)
+    a = rng.uniform(0.0, 2.0, n).astype(np.float32)
+    cam, ocam = lib.Camera.ortho(W, H), osplat.Camera(0, W, H)
+    d = [torch.from_numpy(t).cuda() for t in (x, y, z, m)]
+    img = lib.splat(*d, cam, sigma, radius)
+    both, aimg = lib.splat_aux(*d, torch.from_numpy(a).cuda(), cam, sigma, radius)
+    ma = (m.astype(np.float64) * a.astype(np.float64))
+    for got, mass in ((img, m), (both, m)):
+        err, zeros_ok = image_rel_err(got.cpu().numpy(), osplat.render(ocam, x, y, z, mass, sigma, radius))
+        assert zeros_ok and err <= TOL, err
+    # the oracle takes float32 masses: the rounding of m a is within the tolerance
+    err, zeros_ok = image_rel_err(aimg.cpu().numpy(),
+                                  osplat.render(ocam, x, y, z, ma.astype(np.float32), sigma, radius))
+    assert zeros_ok and err <= TOL, err
