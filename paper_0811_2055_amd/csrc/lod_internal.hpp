@@ -34,6 +34,7 @@ struct SplatLayout {
   uint32_t tiles_x, tiles_y, n_tiles;
   uint32_t units, chunks;            // binning units (waves), 64 per chunk
   uint32_t slice;                    // pairs per accumulation slice
+  bool wide;                         // slice partials in float64
   uint64_t max_points, max_pairs, max_slices;
   bool aux;                          // an attribute channel is drawn
   size_t tile_count, tile_off, ucount, pchunk, slice_off, counters;

@@ -957,6 +957,20 @@ __device__ __forceinline__ void load_rec(const RecGA *r, uint64_t q, float &u, f
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
+// Slice partials: float64 (rounded once, in the image), or float32 where the
+// workspace has to stay as small as it was.
+struct Partial {
+  void *p;
+  bool wide;
+  __device__ __forceinline__ void put(uint64_t i, double v) const {
+    if (wide) reinterpret_cast<double *>(p)[i] = v;
+    else reinterpret_cast<float *>(p)[i] = (float)v;
+  }
+  __device__ __forceinline__ double get(uint64_t i) const {
+    return wide ? reinterpret_cast<const double *>(p)[i] : (double)reinterpret_cast<const float *>(p)[i];
+  }
+};
+
 // The slices of a block and their records, loaded one chunk ahead across slice
 // boundaries (clamped indices: every load is issued unconditionally).  Pair
 // indices are 32-bit.
@@ -1012,7 +1026,7 @@ __device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
 // the truncation test.
 //
 // A point's window of up to nine values goes to the same columns of its row,
-// 0 .. 2 nmax, with at least 15 zeros on either side that nothing overwrites, so
+// 0 .. 2 nmax, with 16 zeros on either side that nothing overwrites, so
 // that the writes have no bank conflicts and nothing is cleared between
 // chunks; the reader of pixel p of point k starts p - (window origin) further
 // on, an address that one lane-broadcast add gives (lane l holds point l; the
@@ -1025,19 +1039,19 @@ __device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
 // wrote 8-wide windows at varying columns (LDS bank conflicts half of the LDS
 // time, 16 exponentials per point, four waves per SIMD; now six).  Error of
 // that image against float64 3.5e-8 -> 3.1e-8.
-constexpr int NPAD = TS - 1;
+constexpr int NPAD = TS;
 constexpr int NROW = 9 + TS;                  // odd: lane i's window starts on its own bank
-constexpr int NWAVE = NPAD + WAVE * NROW;     // a wave's rows: the zeros after one row precede the next
+constexpr int NWAVE = TS + WAVE * NROW;       // a wave's rows: the zeros after one row precede the next
+static_assert(NWAVE % 2 == 0, "the wave sums use the rows as float64");
 template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restrict__ table,
                                                           const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                           const RecT *__restrict__ rec, Cam c,
-                                                          float *__restrict__ partial,
-                                                          float *__restrict__ partial_aux, uint64_t max_slices,
+                                                          Partial partial, Partial partial_aux, uint64_t max_slices,
                                                           uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
-  __shared__ float rows[NW][NWAVE];
+  __shared__ __align__(8) float rows[NW][NWAVE];
   const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
   if (blockIdx.x >= total_slices) return;
   const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
@@ -1114,22 +1128,23 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
         for (int i = 0; i < 4; ++i) sum[NCH - 1][i] += (double)acc2[i];
       }
     }
-    // the wave sums of each pixel, through the first 256 floats of the rows
-    // (lane l holds rows 4 (l / 16) .. + 3 of column l % 16)
+    // the wave sums of each pixel, through the start of the rows (lane l holds
+    // rows 4 (l / 16) .. + 3 of column l % 16)
+    double *part = reinterpret_cast<double *>(rows[w]);
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
       wave_sync_mem();
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rows[w][((lane / TS) * 4 + i) * TS + px] = (float)sum[ch][i];
+      for (int i = 0; i < 4; ++i) part[((lane / TS) * 4 + i) * TS + px] = sum[ch][i];
       __syncthreads();
       double s = 0.0;
 #pragma unroll
-      for (int g = 0; g < NW; ++g) s += (double)rows[g][threadIdx.x];
-      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = (float)s;
+      for (int g = 0; g < NW; ++g) s += reinterpret_cast<const double *>(rows[g])[threadIdx.x];
+      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s);
       __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rows[w][i * WAVE + lane] = 0.0f;
+    for (int i = 0; i < 4; ++i) part[i * WAVE + lane] = 0.0;
     wave_sync_mem();
   }
 }
@@ -1141,13 +1156,13 @@ template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict__ table,
                                                         const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                         const RecT *__restrict__ rec, Cam c,
-                                                        float *__restrict__ partial, float *__restrict__ partial_aux,
+                                                        Partial partial, Partial partial_aux,
                                                         uint64_t max_slices, uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
   __shared__ float gx[PT][GXS];
   __shared__ float gy[PT][GXS];
-  __shared__ float part[NW][TS * TS];   // the waves' slice sums
+  __shared__ double part[NW][TS * TS];  // the waves' slice sums
   const uint32_t total_slices = (uint32_t)min((uint64_t)slice_off[nt], max_slices);
   if (blockIdx.x >= total_slices) return;
   const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
@@ -1203,12 +1218,12 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) part[w][((lane / TS) * 4 + i) * TS + lane % TS] = (float)sum[ch][i];
+      for (int i = 0; i < 4; ++i) part[w][((lane / TS) * 4 + i) * TS + lane % TS] = sum[ch][i];
       __syncthreads();
       double s = 0.0;
 #pragma unroll
-      for (int g = 0; g < NW; ++g) s += (double)part[g][threadIdx.x];
-      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = (float)s;
+      for (int g = 0; g < NW; ++g) s += part[g][threadIdx.x];
+      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s);
       __syncthreads();
     }
   }
@@ -1220,7 +1235,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
 // clump has thousands of slices), and the shares are added in order.
 constexpr int FIN_G = 4;
 __global__ __launch_bounds__(FIN_G * PT) void k_finalize(const uint32_t *__restrict__ slice_off, uint32_t nt,
-                                                         const float *__restrict__ partial, Cam c,
+                                                         Partial partial, Cam c,
                                                          float *__restrict__ image, uint64_t max_slices) {
   __shared__ double share[FIN_G - 1][PT];
   const uint32_t g = threadIdx.x / PT, p = threadIdx.x % PT;
@@ -1230,12 +1245,12 @@ __global__ __launch_bounds__(FIN_G * PT) void k_finalize(const uint32_t *__restr
     const uint32_t b1 = min(e, b + g * per), e1 = min(e, b1 + per);
     double s = 0.0;
     for (uint32_t sl = b1; sl < e1; sl += 16) {
-      float v[16];
+      double v[16];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = partial[(uint64_t)min(sl + k, e1 - 1) * (TS * TS) + p];
+      for (int k = 0; k < 16; ++k) v[k] = partial.get((uint64_t)min(sl + k, e1 - 1) * (TS * TS) + p);
 #pragma unroll
       for (int k = 0; k < 16; ++k)
-        if (sl + k < e1) s += (double)v[k];
+        if (sl + k < e1) s += v[k];
     }
     if (e > b + 1) {   // uniform: a single slice is its own sum
       if (g) share[g - 1][p] = s;
@@ -1323,8 +1338,7 @@ template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict__ table,
                                                          const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                          const RecT *__restrict__ rec, Cam c,
-                                                         float *__restrict__ partial,
-                                                         float *__restrict__ partial_aux, uint64_t max_slices,
+                                                         Partial partial, Partial partial_aux, uint64_t max_slices,
                                                          uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE;
@@ -1463,8 +1477,8 @@ __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict
 #pragma unroll
       for (int g = 0; g < NW * CSUM; ++g) s[ch] += sum[g / CSUM][g % CSUM][ch][o];
     }
-    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = (float)s[0];
-    if constexpr (AUX) partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = (float)s[CH - 1];
+    partial.put((uint64_t)sl * (TS * TS) + threadIdx.x, s[0]);
+    if constexpr (AUX) partial_aux.put((uint64_t)sl * (TS * TS) + threadIdx.x, s[CH - 1]);
     __syncthreads();
   }
 }
@@ -1851,19 +1865,21 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   if (L.max_pairs >= (1ull << 32)) return LOD_EUNSUPPORTED;
   L.aux = aux;
   // Units: 64 per chunk.  A unit's row of the count table is written, scanned
-  // and read, so a unit holds at least half as many points as there are tiles
-  // (8 bytes of table per point), but no more than 2048 while there are fewer
-  // than 4096 units (150 M points: 4096 units of 36.6 k points; a 256x256
-  // image of 262 k points: 2048 units of 128, where units of 2048 left 128
-  // waves on the chip).  few_units (a workspace of fixed size): 2048 always.
-  const uint64_t unit = few_units ? 2048 : std::min<uint64_t>(2048, std::max<uint64_t>(128, nt / 2));
+  // and read, so a unit is not much shorter than an eighth of the tiles (32
+  // bytes of table per point), and no longer than 512 points while there are
+  // fewer than 4096 units (a 256x256 image of 262 k points: 2048 units of 128,
+  // where units of 2048 left 128 waves on the chip; 1 M points at 1024^2: see
+  // the rows rule at the launches).  few_units (a workspace of fixed size):
+  // 2048; the image does not depend on it.
+  const uint64_t unit = few_units ? 2048 : std::min<uint64_t>(512, std::max<uint64_t>(128, nt / 2));
   L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS,
                                           std::max<uint64_t>(1, (max_points + 64 * unit - 1) / (64 * unit)));
   L.units = 64 * L.chunks;
-  auto lay_out = [&](uint32_t units, uint32_t slice) {
+  auto lay_out = [&](uint32_t units, uint32_t slice, bool wide) {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
     L.slice = slice;
+    L.wide = wide;
     L.max_slices = nt + L.max_pairs / slice + 1;
     L.tile_count = take(4 * (nt + 1));
     L.tile_off = take(4 * (nt + 1));
@@ -1872,8 +1888,9 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
     L.slice_off = take(4 * (nt + 1));
     L.counters = take(64);
     L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
-    L.partial = take(4 * (size_t)TS * TS * L.max_slices);
-    L.partial_aux = aux ? take(4 * (size_t)TS * TS * L.max_slices) : L.partial;
+    const size_t pb = (wide ? 8 : 4) * (size_t)TS * TS * L.max_slices;
+    L.partial = take(pb);
+    L.partial_aux = aux ? take(pb) : L.partial;
     L.slice_table = take(8 * (size_t)L.max_slices);
     return L.total = off;
   };
@@ -1883,8 +1900,9 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   // 5.2; the cubic blob's slices take longer: 4 M points 447 us at 4096, 337 at
   // 1024; 16.7 M at 1024^2, Gaussian 158 and 153 at 2048, cubic 388 and 345);
   // 150 M points fill the chip either way.  Shorter slices take more
-  // workspace: near the size of the library's fixed one they stay at 4096, so
-  // that it holds the renders that it held.  The image depends on the slice
+  // workspace, as do float64 slice partials: near the size of the library's
+  // fixed one the slices stay at 4096 and the partials at float32, so that it
+  // holds the renders that it held.  The image depends on the slice
   // length, so this depends on the arguments alone, in the workspace's
   // smallest form.
   const bool cubic = sp.blob == LOD_BLOB_CUBIC;
@@ -1893,10 +1911,9 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
                                                    : SPLAT_SLICE;
   const uint32_t few = (uint32_t)std::min<uint64_t>(
       SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (max_points + (64 * 2048) - 1) / (64 * 2048)));
-  const bool near_fixed = lay_out(64 * few, want) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
-                          lay_out(64 * few, SPLAT_SLICE) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
-  const uint32_t slice = near_fixed ? SPLAT_SLICE : want;
-  lay_out(L.units, slice);
+  const bool near_fixed = lay_out(64 * few, want, true) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
+                          lay_out(64 * few, SPLAT_SLICE, false) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
+  lay_out(L.units, near_fixed ? SPLAT_SLICE : want, !near_fixed);
   return LOD_OK;
 }
 
@@ -1917,8 +1934,7 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
   uint64_t *ctr = (uint64_t *)(W + L.counters);
   uint64_t *status = status_word ? status_word : ctr;
   RecT *rec = (RecT *)(W + L.rec);
-  float *partial = (float *)(W + L.partial);
-  float *partial_aux = (float *)(W + L.partial_aux);
+  const Partial partial{W + L.partial, L.wide}, partial_aux{W + L.partial_aux, L.wide};
   uint2 *stab = (uint2 *)(W + L.slice_table);
   int nbits = 0;
   while ((1u << nbits) < nt) ++nbits;
@@ -1926,10 +1942,12 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
   // Counters and cursors in the rows of the count table for points in Morton
   // order (a tree's): their rounds stay in one window for long, and the waves
   // per CU are not limited by LDS.  In LDS for arrays in the caller's order,
-  // which may be random, once a unit's points outnumber the initialisation of
-  // its LDS row.
+  // which may be random, unless a unit's points are too few to pay for the
+  // initialisation of its LDS row and for the waves that its LDS keeps away
+  // (random points, fill + count: 1 M in units of 512, rows 111 us, of 2048 in
+  // LDS 168; 4 M in units of 977, LDS 264, rows 486; 16.7 M 745 and 1890).
   const uint64_t per = (L.max_points + L.units - 1) / L.units;
-  const bool rows = IsTree<Src>::value || per < nt / 8;
+  const bool rows = IsTree<Src>::value || per <= nt / 8;
   const uint32_t *pre = L.chunks > 1 ? pchunk : nullptr;
   if (any) {
     const bool narrow_counts = per + WAVE <= 65535;
