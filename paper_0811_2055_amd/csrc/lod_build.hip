@@ -89,17 +89,26 @@ __device__ __forceinline__ uint64_t local_id(const BuildArgs &a, uint32_t snap, 
 }
 
 // ---------------------------------------------------------------------------
-// snapshot offsets check (one block)
+// Start of a build, one launch: the status and counts cleared (before any kernel
+// that sets a bit), the snapshot offsets checked by the block that cleared
+// them, and the zeroed part of the workspace (levels, leaf-copy cursors,
+// totals of the tree's levels).
 
-__global__ void k_check_offsets(BuildArgs a) {
+__global__ __launch_bounds__(256) void k_build_init(BuildArgs a, uint32_t *__restrict__ zero, uint64_t n_zero) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_zero;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    zero[i] = 0u;
+  if (blockIdx.x) return;
+  if (threadIdx.x < 3) a.counts[threadIdx.x] = 0;
   if (!a.snap_off || a.n_snap <= 1) return;
+  __syncthreads();
   bool bad = false;
   for (uint32_t s = threadIdx.x; s < a.n_snap; s += blockDim.x) {
     uint64_t lo = a.snap_off[s], hi = a.snap_off[s + 1];
     if (hi < lo || hi - lo >= (1ull << 31)) bad = true;
   }
   if (threadIdx.x == 0 && (a.snap_off[0] != 0 || a.snap_off[a.n_snap] != a.N)) bad = true;
-  if (bad) atomicOr((unsigned long long *)&a.counts[2], (unsigned long long)LOD_STATUS_OFFSETS);
+  if (__syncthreads_or(bad) && threadIdx.x == 0) a.counts[2] = LOD_STATUS_OFFSETS;
 }
 
 // ---------------------------------------------------------------------------
@@ -636,8 +645,8 @@ __device__ __forceinline__ void set_status(const BuildArgs &a, uint32_t bits) {
   atomicOr((unsigned long long *)&a.counts[2], (unsigned long long)bits);
 }
 
-// Roots: one per non-empty snapshot (single block).
-__global__ __launch_bounds__(1024) void k_roots(BuildArgs a, TreeArgs t, const uint32_t *__restrict__ skey) {
+// Roots: one per non-empty snapshot (one block of 1024).
+__device__ void make_roots(const BuildArgs &a, const TreeArgs &t, const uint32_t *__restrict__ skey) {
   __shared__ uint32_t tmp[1024 / WAVE + 1];
   __shared__ uint32_t base_nodes, base_sel;
   if (threadIdx.x == 0) { base_nodes = 0; base_sel = 0; t.lvl[0] = 0; t.lsel[0] = 0; }
@@ -679,115 +688,66 @@ __global__ __launch_bounds__(1024) void k_roots(BuildArgs a, TreeArgs t, const u
     __syncthreads();
   }
   if (threadIdx.x == 0) { t.lvl[1] = min((uint64_t)base_nodes, a.node_cap); t.lsel[1] = base_sel; }
+  __syncthreads();
 }
 
-// Octant boundaries of the internal nodes of level d: 8 lanes per node.
-__global__ __launch_bounds__(TB) void k_octants(BuildArgs a, TreeArgs t, const uint32_t *__restrict__ skey, int d) {
-  const uint32_t b = t.lvl[d], e = t.lvl[d + 1];
-  const uint64_t gtid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  const int sh = 3 * (a.D - d - 1);
-  for (uint64_t g = gtid; g < (uint64_t)(e - b) * 8; g += stride) {
-    const uint32_t v = b + (uint32_t)(g >> 3);
-    const uint32_t o = (uint32_t)(g & 7);
-    const uint64_t cnt = t.part_count[v];
-    if (!(cnt > a.n && d < a.D)) continue;
-    const uint64_t lo = t.part_begin[v], hi = lo + cnt;
-    uint64_t start = lo;
-    if (o) {
-      const uint64_t target = ((t.prefix[v] << 3) | o) << sh;
-      uint64_t l = lo, h = hi;
-      while (l < h) { uint64_t mid = l + ((h - l) >> 1); if ((uint64_t)skey[mid] < target) l = mid + 1; else h = mid; }
-      start = l;
+// Octant boundaries of internal node v of level d, by one wave: eight lanes per
+// octant search for its first key, reading eight keys of the remaining range
+// at once (a ninth of it is left: eight dependent reads for 16 M particles,
+// where a binary search takes 24).  Writes the node's nine boundaries and
+// returns, on every lane, the number of non-empty octants and (nsel) of those
+// holding more than n particles.
+__device__ uint32_t search_octants(const BuildArgs &a, const TreeArgs &t, const uint32_t *__restrict__ skey, int d,
+                                   uint32_t v, uint32_t &nsel) {
+  const uint32_t lane = threadIdx.x & (WAVE - 1), o = lane / 8, sub = lane % 8;
+  const uint64_t lo = t.part_begin[v], hi = lo + t.part_count[v];
+  uint64_t l = lo, h = hi;
+  if (o) {
+    const uint64_t target = ((t.prefix[v] << 3) | o) << (3 * (a.D - d - 1));
+    while (h - l > 8) {
+      const uint64_t step = (h - l) / 9;
+      const bool lt = (uint64_t)skey[l + step * (sub + 1)] < target;
+      const uint32_t c = __popc((uint32_t)(__ballot(lt) >> (8 * o)) & 0xFFu);
+      if (c < 8) h = l + step * (c + 1);
+      if (c) l += step * c + 1;
     }
-    t.cs[(uint64_t)v * 9 + o] = (uint32_t)start;
-    if (o == 7) t.cs[(uint64_t)v * 9 + 8] = (uint32_t)hi;
+    const bool lt = l + sub < h && (uint64_t)skey[min(l + sub, hi - 1)] < target;
+    l += __popc((uint32_t)(__ballot(lt) >> (8 * o)) & 0xFFu);
   }
+  const uint32_t start = (uint32_t)l;
+  const uint32_t next = __shfl_down(start, 8, WAVE);
+  const uint32_t cnt = (o == 7 ? (uint32_t)hi : next) - start;
+  if (sub == 0) t.cs[(uint64_t)v * 9 + o] = start;
+  if (lane == WAVE - 1) t.cs[(uint64_t)v * 9 + 8] = (uint32_t)hi;
+  nsel = (uint32_t)__popcll(__ballot(sub == 0 && cnt > a.n));
+  return (uint32_t)__popcll(__ballot(sub == 0 && cnt > 0));
 }
-
-// Emit level d+1 from level d in three launches.  Thread (i, o) of a block
-// of EMIT_BT handles octant o of node i (8 nodes per wave, 32 per block), so
-// a child's index is the node-major, octant-minor count of non-empty octants
-// before it: per-block totals (k_emit_count), one scan of them
-// (k_emit_scan), and the writes (k_emit_write) with a block scan inside.
-// The emission runs beside the density kernel, which fills the CUs: a
-// 256-thread block finds room as soon as one density block ends, a
-// 1024-thread block only when a whole CU drains (the eight levels' chain
-// measured 0.52 against 0.67 ms with 1024-thread blocks).
-constexpr int EMIT_BT = 256;
-constexpr int EMIT_NODES = EMIT_BT / 8;   // nodes per block
 
 struct EmitOct {
   uint32_t v, cnt, begin;
-  bool valid, split;
+  bool valid;
 };
 
-__device__ __forceinline__ EmitOct emit_octant(const BuildArgs &a, const TreeArgs &t, int d) {
-  const uint32_t b = t.lvl[d], e = t.lvl[d + 1];
+// Octant o = threadIdx.x % 8 of node v of level d (valid: the node exists).
+__device__ __forceinline__ EmitOct emit_octant(const BuildArgs &a, const TreeArgs &t, int d, uint64_t v, bool valid) {
   EmitOct r{};
-  const uint64_t v = (uint64_t)b + (uint64_t)blockIdx.x * EMIT_NODES + threadIdx.x / 8;
-  const uint32_t o = threadIdx.x & 7u;
-  r.valid = v < e;
+  r.valid = valid;
   r.v = (uint32_t)v;
-  const uint32_t vc = r.valid ? r.v : b;   // in bounds when the level is not empty
-  r.split = r.valid && t.part_count[vc] > a.n && d < a.D;
-  const uint32_t s0 = t.cs[(uint64_t)vc * 9 + o], s1 = t.cs[(uint64_t)vc * 9 + o + 1];
-  r.cnt = r.split ? s1 - s0 : 0u;
-  r.begin = s0;
+  if (!valid) return r;
+  const uint32_t o = threadIdx.x & 7u;
+  if (t.part_count[v] > a.n && d < a.D) {
+    r.begin = t.cs[v * 9 + o];
+    r.cnt = t.cs[v * 9 + o + 1] - r.begin;
+  }
   return r;
 }
 
-__global__ __launch_bounds__(EMIT_BT) void k_emit_count(BuildArgs a, TreeArgs t, int d, uint32_t *__restrict__ tot) {
-  __shared__ uint32_t tmp[EMIT_BT / WAVE + 1];
-  if (t.lvl[d] + (uint64_t)blockIdx.x * EMIT_NODES >= t.lvl[d + 1]) {
-    if (threadIdx.x == 0) { tot[2 * blockIdx.x] = 0; tot[2 * blockIdx.x + 1] = 0; }
-    return;
-  }
-  const EmitOct x = emit_octant(a, t, d);
-  uint32_t tk, ts;
-  block_excl_scan<uint32_t>(x.cnt > 0 ? 1u : 0u, tmp, tk);
-  block_excl_scan<uint32_t>(x.cnt > a.n ? 1u : 0u, tmp, ts);
-  if (threadIdx.x == 0) { tot[2 * blockIdx.x] = tk; tot[2 * blockIdx.x + 1] = ts; }
-}
-
-// exclusive scan of the (children, selecting children) totals of nb blocks,
-// and the extent of level d+1
-__global__ __launch_bounds__(1024) void k_emit_scan(BuildArgs a, TreeArgs t, int d, uint32_t *__restrict__ tot,
-                                                    uint32_t nb) {
-  __shared__ uint32_t tmp[1024 / WAVE + 1];
-  __shared__ uint32_t run_k, run_s;
-  if (threadIdx.x == 0) { run_k = 0; run_s = 0; }
-  __syncthreads();
-  for (uint32_t j0 = 0; j0 < nb; j0 += blockDim.x) {
-    const uint32_t j = j0 + threadIdx.x;
-    const uint32_t ck = j < nb ? tot[2 * j] : 0u, cs = j < nb ? tot[2 * j + 1] : 0u;
-    uint32_t tk, ts;
-    const uint32_t ek = block_excl_scan<uint32_t>(ck, tmp, tk);
-    const uint32_t es = block_excl_scan<uint32_t>(cs, tmp, ts);
-    if (j < nb) { tot[2 * j] = run_k + ek; tot[2 * j + 1] = run_s + es; }
-    __syncthreads();
-    if (threadIdx.x == 0) { run_k += tk; run_s += ts; }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const uint64_t end = (uint64_t)t.lvl[d + 1] + run_k;
-    t.lvl[d + 2] = (uint32_t)min(end, a.node_cap);
-    t.lsel[d + 2] = t.lsel[d + 1] + run_s;
-  }
-}
-
-__global__ __launch_bounds__(EMIT_BT) void k_emit_write(BuildArgs a, TreeArgs t, int d,
-                                                     const uint32_t *__restrict__ tot) {
-  __shared__ uint32_t tmp[EMIT_BT / WAVE + 1];
-  if (t.lvl[d] + (uint64_t)blockIdx.x * EMIT_NODES >= t.lvl[d + 1]) return;
-  const EmitOct x = emit_octant(a, t, d);
+// The child of one octant, number c of the nodes and sidx of the selecting
+// ones; every thread of the block calls it.
+__device__ __forceinline__ void emit_child(const BuildArgs &a, const TreeArgs &t, int d, const EmitOct &x, uint64_t c,
+                                           uint32_t sidx) {
   const uint32_t o = threadIdx.x & 7u;
   const bool ne = x.cnt > 0, se = x.cnt > a.n;
-  uint32_t tk, ts;
-  const uint32_t ok = block_excl_scan<uint32_t>(ne ? 1u : 0u, tmp, tk);
-  const uint32_t os = block_excl_scan<uint32_t>(se ? 1u : 0u, tmp, ts);
-  const uint64_t c = (uint64_t)t.lvl[d + 1] + tot[2 * blockIdx.x] + ok;   // this octant's child
-  const uint32_t sidx = t.lsel[d + 1] + tot[2 * blockIdx.x + 1] + os;
   // the node's 8 octants are 8 consecutive lanes of one wave
   const int sh = (int)(threadIdx.x & (WAVE - 1) & ~7u);
   const uint32_t mask = (uint32_t)(__ballot(ne) >> sh) & 0xFFu;
@@ -816,25 +776,160 @@ __global__ __launch_bounds__(EMIT_BT) void k_emit_write(BuildArgs a, TreeArgs t,
   t.pend[c] = 0;
 }
 
-// pt_count for every slot < node_cap (0 beyond the node count) and n_nodes.
-__global__ __launch_bounds__(TB) void k_ptcount(BuildArgs a, TreeArgs t, int D) {
-  const uint32_t nn = t.lvl[D + 1];
-  for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < a.node_cap;
-       v += (uint64_t)gridDim.x * blockDim.x) {
-    uint32_t c = 0;
-    if (v < nn) c = (uint32_t)min(t.part_count[v], (uint64_t)a.n);
-    t.pt_count[v] = v < nn ? c : 0u;
-    t.pt_begin[v] = c;
+// The roots and the children of levels 0 .. top - 1 by one block: levels that
+// hold at most TOP_NODES nodes, a wave per node for the boundaries and a thread
+// per octant for the children.  (Below, a level takes two launches; the first
+// levels' few nodes are bound by latency, and each launch costs as much again.)
+// Sixteen nodes: one for each of the block's waves; a second turn would take
+// as long as the level's two launches.  Roots and levels 0 and 1 of 262,144
+// particles take 13 us, of 16.7 M 22 us.
+constexpr uint32_t TOP_NODES = 16;
+__global__ __launch_bounds__(1024) void k_tree_top(BuildArgs a, TreeArgs t, const uint32_t *__restrict__ skey,
+                                                   int top) {
+  __shared__ uint32_t tmp[1024 / WAVE + 1];
+  make_roots(a, t, skey);
+  for (int d = 0; d < top; ++d) {
+    const uint32_t b = t.lvl[d], e = t.lvl[d + 1];
+    for (uint32_t v = b + threadIdx.x / WAVE; v < e; v += blockDim.x / WAVE) {
+      uint32_t nsel;
+      if (t.part_count[v] > a.n) search_octants(a, t, skey, d, v, nsel);
+    }
+    __syncthreads();
+    // at most TOP_NODES nodes: 8 threads each
+    const uint64_t v = (uint64_t)b + threadIdx.x / 8;
+    const EmitOct x = emit_octant(a, t, d, v, v < e);
+    uint32_t tk, ts;
+    const uint32_t ok = block_excl_scan<uint32_t>(x.cnt > 0 ? 1u : 0u, tmp, tk);
+    const uint32_t os = block_excl_scan<uint32_t>(x.cnt > a.n ? 1u : 0u, tmp, ts);
+    emit_child(a, t, d, x, (uint64_t)e + ok, t.lsel[d + 1] + os);
+    if (threadIdx.x == 0) {
+      t.lvl[d + 2] = (uint32_t)min((uint64_t)e + tk, a.node_cap);
+      t.lsel[d + 2] = t.lsel[d + 1] + ts;
+    }
+    __syncthreads();
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[0] = nn;
 }
 
-__global__ void k_ptfinish(BuildArgs a, TreeArgs t) {
-  // total = last exclusive offset + last count (both over node_cap slots)
-  const uint64_t last = a.node_cap - 1;
-  const uint64_t total = t.pt_begin[last] + t.pt_count[last];
-  a.counts[1] = total;
-  if (total > a.point_cap) set_status(a, LOD_STATUS_CAPACITY);
+// A further level in two launches: the boundaries, a wave per node, with the
+// children (and selecting children) of every EMIT_NODES nodes added to their
+// total and to that of GROUP such blocks; then the children, a thread per
+// octant.  A child's index is the node-major, octant-minor count of non-empty
+// octants before it: the totals before the block, which it adds up itself (a
+// scan of them would be a third launch), and a block scan.  The emission runs
+// beside the density kernel, which fills the CUs: a 256-thread block finds room
+// as soon as one density block ends, a 1024-thread block only when a whole CU
+// drains.
+// Roots and four levels of 262,144 particles: 34 us in five launches, against
+// 79 in seventeen (binary search, count, scan, write); the whole build 309
+// against 360 us, of 16.7 M particles 1778 against 1876.
+constexpr int EMIT_BT = 256;
+constexpr int EMIT_NODES = EMIT_BT / 8;   // nodes per block
+constexpr uint32_t GROUP = 64;            // blocks per group of totals
+
+__global__ __launch_bounds__(EMIT_BT) void k_tree_search(BuildArgs a, TreeArgs t, const uint32_t *__restrict__ skey,
+                                                         int d, uint32_t *__restrict__ tot,
+                                                         uint32_t *__restrict__ gtot) {
+  const uint32_t b = t.lvl[d], e = t.lvl[d + 1];
+  const uint32_t lane = threadIdx.x & (WAVE - 1);
+  for (uint64_t i = ((uint64_t)blockIdx.x * EMIT_BT + threadIdx.x) / WAVE; b + i < e;
+       i += (uint64_t)gridDim.x * (EMIT_BT / WAVE)) {
+    const uint32_t v = b + (uint32_t)i;
+    if (t.part_count[v] <= a.n) continue;
+    uint32_t nsel;
+    const uint32_t nk = search_octants(a, t, skey, d, v, nsel);
+    // lanes 0 and 1: children and selecting children
+    const uint32_t c = lane ? nsel : nk;
+    const uint64_t j = i / EMIT_NODES;
+    if (lane < 2 && c) {
+      atomicAdd(&tot[2 * j + lane], c);
+      atomicAdd(&gtot[2 * (j / GROUP) + lane], c);
+    }
+  }
+}
+
+__global__ __launch_bounds__(EMIT_BT) void k_tree_write(BuildArgs a, TreeArgs t, int d,
+                                                        const uint2 *__restrict__ tot,
+                                                        const uint2 *__restrict__ gtot) {
+  __shared__ uint32_t tmp[EMIT_BT / WAVE + 1];
+  const uint32_t b = t.lvl[d], e = t.lvl[d + 1];
+  const uint32_t nb = (e - b + EMIT_NODES - 1) / EMIT_NODES;   // blocks with nodes
+  if (blockIdx.x >= max(nb, 1u)) return;
+  uint32_t bk = 0, bs = 0, ak = 0, as = 0;
+  const uint32_t g = blockIdx.x / GROUP;
+  for (uint32_t j = threadIdx.x; j * GROUP < nb && (j < g || blockIdx.x == 0); j += EMIT_BT) {
+    const uint2 q = gtot[j];
+    if (j < g) { bk += q.x; bs += q.y; }
+    ak += q.x; as += q.y;
+  }
+  for (uint32_t j = g * GROUP + threadIdx.x; j < blockIdx.x; j += EMIT_BT) { bk += tot[j].x; bs += tot[j].y; }
+  bk = block_reduce_sum<uint32_t>(bk, tmp);
+  bs = block_reduce_sum<uint32_t>(bs, tmp);
+  if (blockIdx.x == 0) {
+    ak = block_reduce_sum<uint32_t>(ak, tmp);
+    as = block_reduce_sum<uint32_t>(as, tmp);
+    if (threadIdx.x == 0) {
+      t.lvl[d + 2] = (uint32_t)min((uint64_t)e + ak, a.node_cap);
+      t.lsel[d + 2] = t.lsel[d + 1] + as;
+    }
+  }
+  const uint64_t v = (uint64_t)b + (uint64_t)blockIdx.x * EMIT_NODES + threadIdx.x / 8;
+  const EmitOct x = emit_octant(a, t, d, v, v < e);
+  uint32_t tk, ts;
+  const uint32_t ok = block_excl_scan<uint32_t>(x.cnt > 0 ? 1u : 0u, tmp, tk);
+  const uint32_t os = block_excl_scan<uint32_t>(x.cnt > a.n ? 1u : 0u, tmp, ts);
+  emit_child(a, t, d, x, (uint64_t)e + bk + ok, t.lsel[d + 1] + bs + os);
+}
+
+// Stored point counts and offsets of every slot below node_cap (past the node
+// count: 0 and the total), the node and point counts.  Block b scans PT_NODES
+// nodes and leaves their total; then it adds up the totals before it, whole
+// groups of them first.  gsums: a total per GROUP blocks, zero before.
+constexpr int PT_NODES = 1024;
+__global__ __launch_bounds__(PT_NODES) void k_pt_scan(BuildArgs a, TreeArgs t, int D, uint64_t *__restrict__ sums,
+                                                      unsigned long long *__restrict__ gsums) {
+  __shared__ uint64_t tmp[PT_NODES / WAVE + 1];
+  const uint32_t nn = t.lvl[D + 1];
+  const uint64_t v = (uint64_t)blockIdx.x * PT_NODES + threadIdx.x;
+  uint32_t c = 0;
+  if (v < nn) c = (uint32_t)min(t.part_count[v], (uint64_t)a.n);
+  if (v < a.node_cap) t.pt_count[v] = c;
+  if ((uint64_t)blockIdx.x * PT_NODES >= nn) return;   // uniform
+  uint64_t total;
+  const uint64_t o = block_excl_scan<uint64_t>(c, tmp, total);
+  if (v < nn) t.pt_begin[v] = o;
+  if (threadIdx.x == 0) {
+    sums[blockIdx.x] = total;
+    atomicAdd(&gsums[blockIdx.x / GROUP], (unsigned long long)total);
+  }
+}
+
+__global__ __launch_bounds__(PT_NODES) void k_pt_finish(BuildArgs a, TreeArgs t, int D,
+                                                        const uint64_t *__restrict__ sums,
+                                                        const uint64_t *__restrict__ gsums) {
+  __shared__ uint64_t tmp[PT_NODES / WAVE + 1];
+  const uint32_t nn = t.lvl[D + 1];
+  const uint64_t v = (uint64_t)blockIdx.x * PT_NODES + threadIdx.x;
+  const uint32_t nb = (nn + PT_NODES - 1) / PT_NODES, g = blockIdx.x / GROUP;
+  if (blockIdx.x < nb) {
+    uint64_t before = 0;
+    for (uint32_t j = threadIdx.x; j < g; j += PT_NODES) before += gsums[j];
+    for (uint32_t j = g * GROUP + threadIdx.x; j < blockIdx.x; j += PT_NODES) before += sums[j];
+    before = block_reduce_sum<uint64_t>(before, tmp);
+    if (v < nn) t.pt_begin[v] += before;
+  }
+  // the last block of the grid has the counts to write; it and the blocks with
+  // slots past the nodes need the total
+  const bool last = blockIdx.x == gridDim.x - 1;
+  if (!last && (uint64_t)(blockIdx.x + 1) * PT_NODES <= nn) return;
+  uint64_t total = 0;
+  for (uint32_t j = threadIdx.x; j * GROUP < nb; j += PT_NODES) total += gsums[j];
+  total = block_reduce_sum<uint64_t>(total, tmp);
+  if (last && threadIdx.x == 0) {
+    a.counts[0] = nn;
+    a.counts[1] = total;
+    if (total > a.point_cap) set_status(a, LOD_STATUS_CAPACITY);
+  }
+  if (v >= nn && v < a.node_cap) t.pt_begin[v] = total;
 }
 
 // ---------------------------------------------------------------------------
@@ -1959,6 +2054,9 @@ static unsigned emit_blocks(uint64_t N, uint32_t n, uint32_t n_snap) {
   return (unsigned)std::max<uint64_t>(1, (max_level + EMIT_NODES - 1) / EMIT_NODES);
 }
 
+static uint64_t pt_blocks(uint64_t node_cap) { return (node_cap + PT_NODES - 1) / PT_NODES; }
+static uint64_t groups(uint64_t blocks) { return (blocks + GROUP - 1) / GROUP; }
+
 BuildLayout build_layout(uint64_t N, const lod_params &p, uint32_t n_snap) {
   BuildLayout L{};
   const uint64_t Np = N ? N : 1;
@@ -1981,10 +2079,9 @@ BuildLayout build_layout(uint64_t N, const lod_params &p, uint32_t n_snap) {
   L.thist = take(4 * (size_t)RADIX * tiles);
   L.scan32 = take(4 * std::max(scan_tmp_elems<uint32_t>((uint64_t)RADIX * tiles),
                                scan_tmp_elems<uint32_t>(L.node_cap + 1)));
-  L.scan64 = take(8 * scan_tmp_elems<uint64_t>(L.node_cap));
+  L.pt_sums = take(8 * (size_t)pt_blocks(L.node_cap));
   L.w = take(4 * Np);
   L.kb = take(2 * Np + 16);            // bulk selection reads may overrun by 16 bytes
-  L.lvl = take(4 * (size_t)(p.max_depth + 4));
   L.lsel = take(4 * (size_t)(p.max_depth + 4));
   L.cs = take(4 * 9 * (size_t)L.node_cap);
   L.sel_idx = take(4 * (size_t)L.node_cap);
@@ -2005,8 +2102,14 @@ BuildLayout build_layout(uint64_t N, const lod_params &p, uint32_t n_snap) {
   L.sel_rows = (uint32_t)std::min<uint64_t>(4096, N / ((uint64_t)p.n + 1) + n_snap + 1);
   L.mhat = take(8 * (size_t)L.sel_rows * p.n);
   L.src = take(4 * (size_t)L.sel_rows * ((uint64_t)p.n + 1));
-  L.leafctl = take(4 * ((size_t)L.sel_rows + 2 * (p.max_depth + 1)));   // leaf-copy cursors, level counts
-  L.emit_tot = take(8 * ((size_t)emit_blocks(N, p.n, n_snap) + 1));   // per-block child totals of the emit
+  // zeroed by the build's first launch: level starts, leaf-copy cursors and
+  // level counts, child totals of every level (blocks, groups), point totals
+  L.lvl = take(4 * (size_t)(p.max_depth + 4));
+  L.leafctl = take(4 * ((size_t)L.sel_rows + 2 * (p.max_depth + 1)));
+  const size_t eb = emit_blocks(N, p.n, n_snap);
+  L.emit_tot = take(8 * (eb + groups(eb)) * std::max(1u, p.max_depth));
+  L.pt_gsums = take(8 * (size_t)groups(pt_blocks(L.node_cap)));
+  L.zero_end = off;
   L.total = off;
   return L;
 }
@@ -2065,13 +2168,12 @@ lod_status launch_build(const lod_input &in, const lod_params &p, void *ws, cons
   a.alpha = p.alpha; a.seed = p.seed; a.n_snap = n_snap; a.snap_off = in.snap_offsets;
   a.node_cap = L.node_cap; a.point_cap = out.point_capacity; a.counts = out.counts;
 
-  // fills instead of memsets: the build may be captured into a graph
-  fill_u64(out.counts, 3, 0, st);
+  // a kernel instead of memsets: the build may be captured into a graph
   uint32_t *lvl = (uint32_t *)(W + L.lvl);
-  fill_u32(lvl, p.max_depth + 4, 0, st);
+  const uint64_t n_zero = (L.zero_end - L.lvl) / 4;
+  LOD_LAUNCH(k_build_init, dim3((unsigned)std::min<uint64_t>(1024, (n_zero + 255) / 256)), dim3(256), 0, st, a, lvl,
+             n_zero);
   if (N == 0) return hipGetLastError() == hipSuccess ? LOD_OK : LOD_EDEVICE;
-
-  LOD_LAUNCH(k_check_offsets, dim3(1), dim3(256), 0, st, a);
 
   uint32_t *keyA = (uint32_t *)(W + L.keyA), *keyB = (uint32_t *)(W + L.keyB);
   uint32_t *idxA = (uint32_t *)(W + L.idxA), *idxB = (uint32_t *)(W + L.idxB);
@@ -2126,29 +2228,33 @@ lod_status launch_build(const lod_input &in, const lod_params &p, void *ws, cons
   t.wit = (uint32_t *)(W + L.wit); t.pend = (uint32_t *)(W + L.pend); t.lsel = (uint32_t *)(W + L.lsel);
 
   const int D = (int)p.max_depth;
-  LOD_LAUNCH(k_roots, dim3(1), dim3(1024), 0, st, a, t, ks);
   const uint64_t per_level = N / ((uint64_t)p.n + 1) + n_snap;
-  const unsigned oct_grid = (unsigned)std::min<uint64_t>(4096, (per_level * 8 + TB - 1) / TB + 1);
-  // blocks of the emit kernels: enough for the largest level (every level but
-  // the roots' holds at most 8 children per selecting node of the level above)
+  // nodes of a level: at most 8 per node above, and emit_blocks' bound
   const unsigned emit_grid = emit_blocks(N, p.n, n_snap);
-  uint32_t *emit_tot = (uint32_t *)(W + L.emit_tot);
-  for (int d = 0; d < D; ++d) {
-    LOD_LAUNCH(k_octants, dim3(oct_grid), dim3(TB), 0, st, a, t, ks, d);
-    LOD_LAUNCH(k_emit_count, dim3(emit_grid), dim3(EMIT_BT), 0, st, a, t, d, emit_tot);
-    LOD_LAUNCH(k_emit_scan, dim3(1), dim3(1024), 0, st, a, t, d, emit_tot, emit_grid);
-    LOD_LAUNCH(k_emit_write, dim3(emit_grid), dim3(EMIT_BT), 0, st, a, t, d, emit_tot);
+  auto level_nodes = [&](int d) {
+    return std::min<uint64_t>((uint64_t)n_snap << std::min(3 * d, 32), (uint64_t)emit_grid * EMIT_NODES);
+  };
+  int top = 0;
+  while (top < D && level_nodes(top) <= TOP_NODES) ++top;
+  LOD_LAUNCH(k_tree_top, dim3(1), dim3(1024), 0, st, a, t, ks, top);
+  for (int d = top; d < D; ++d) {
+    uint32_t *tot = (uint32_t *)(W + L.emit_tot) + 2 * (size_t)(emit_grid + groups(emit_grid)) * d;
+    uint32_t *gtot = tot + 2 * (size_t)emit_grid;
+    const uint64_t ln = level_nodes(d);
+    LOD_LAUNCH(k_tree_search, dim3((unsigned)std::min<uint64_t>(4096, (ln * WAVE + EMIT_BT - 1) / EMIT_BT)),
+               dim3(EMIT_BT), 0, st, a, t, ks, d, tot, gtot);
+    LOD_LAUNCH(k_tree_write, dim3((unsigned)((ln + EMIT_NODES - 1) / EMIT_NODES)), dim3(EMIT_BT), 0, st, a, t, d,
+               (const uint2 *)tot, (const uint2 *)gtot);
   }
-  const unsigned cap_grid = (unsigned)std::min<uint64_t>(4096, (L.node_cap + TB - 1) / TB);
-  LOD_LAUNCH(k_ptcount, dim3(cap_grid), dim3(TB), 0, st, a, t, D);
-  device_scan<uint64_t>(out.pt_begin, L.node_cap, (uint64_t *)(W + L.scan64), st);
-  LOD_LAUNCH(k_ptfinish, dim3(1), dim3(1), 0, st, a, t);
+  const unsigned pt_grid = (unsigned)pt_blocks(L.node_cap);
+  uint64_t *pt_sums = (uint64_t *)(W + L.pt_sums), *pt_gsums = (uint64_t *)(W + L.pt_gsums);
+  LOD_LAUNCH(k_pt_scan, dim3(pt_grid), dim3(PT_NODES), 0, st, a, t, D, pt_sums, (unsigned long long *)pt_gsums);
+  LOD_LAUNCH(k_pt_finish, dim3(pt_grid), dim3(PT_NODES), 0, st, a, t, D, pt_sums, pt_gsums);
 
   const unsigned node_grid = (unsigned)std::min<uint64_t>(8192, L.node_cap);
   // the per-level and persistent schedules copy the leaves' points inside
   // their selection launches
   uint32_t *leaf_ctl = p.mode == 1 ? (uint32_t *)(W + L.leafctl) : nullptr;
-  if (leaf_ctl) fill_u32(leaf_ctl, (uint64_t)L.sel_rows + 2 * (p.max_depth + 1), 0, st);
   if (p.mode == 0) {
     LOD_LAUNCH(k_leaves<true>, dim3(node_grid), dim3(TB), 0, st, a, t, s);
   } else {

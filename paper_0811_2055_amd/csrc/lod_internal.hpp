@@ -13,9 +13,9 @@ namespace lodh {
 struct BuildLayout {
   uint64_t tiles, node_cap, point_cap;
   size_t keyA, keyB, idxA, idxB, loA, loB, lzA, lzB, mA, mB;
-  size_t thist, scan32, scan64;
+  size_t thist, scan32, pt_sums;
   size_t w, kb;
-  size_t lvl, lsel, cs, sel_idx, sel_node, wit, pend, bflag, bscan, bottom, ctl, leafctl, emit_tot;
+  size_t lvl, lsel, cs, sel_idx, sel_node, wit, pend, bflag, bscan, bottom, ctl, leafctl, emit_tot, pt_gsums, zero_end;
   size_t lpos, lkb, lwm, lhist, widx;
   uint32_t sel_rows;             // blocks of a selection launch (rows of mhat)
   size_t mhat, src;
