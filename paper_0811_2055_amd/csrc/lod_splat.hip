@@ -1949,7 +1949,7 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS,
                                           std::max<uint64_t>(1, (max_points + 64 * unit - 1) / (64 * unit)));
   L.units = 64 * L.chunks;
-  auto lay_out = [&](uint32_t units, uint32_t slice, bool wide) {
+  auto lay_out = [&](uint32_t units, uint32_t slice, bool wide, bool aux) {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
     L.slice = slice;
@@ -1977,17 +1977,17 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   // workspace, as do float64 slice partials: near the size of the library's
   // fixed one the slices stay at 4096 and the partials at float32, so that it
   // holds the renders that it held.  The image depends on the slice
-  // length, so this depends on the arguments alone, in the workspace's
-  // smallest form.
+  // length, so this depends on the points and the camera alone, not on the
+  // attribute channel or the form of the workspace.
   const bool cubic = sp.blob == LOD_BLOB_CUBIC;
   const uint32_t want = max_points <= (1u << 19)   ? 512u
                         : max_points <= (1u << 25) ? (cubic ? 1024u : 2048u)
                                                    : SPLAT_SLICE;
   const uint32_t few = (uint32_t)std::min<uint64_t>(
       SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (max_points + (64 * 2048) - 1) / (64 * 2048)));
-  const bool near_fixed = lay_out(64 * few, want, true) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
-                          lay_out(64 * few, SPLAT_SLICE, false) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
-  lay_out(L.units, near_fixed ? SPLAT_SLICE : want, !near_fixed);
+  const bool near_fixed = lay_out(64 * few, want, true, false) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
+                          lay_out(64 * few, SPLAT_SLICE, false, false) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
+  lay_out(L.units, near_fixed ? SPLAT_SLICE : want, !near_fixed, aux);
   return LOD_OK;
 }
 

@@ -132,3 +132,19 @@ def test_gaussian_window_edges(sigma, radius):
     err, zeros_ok = image_rel_err(aimg.cpu().numpy(),
                                   osplat.render(ocam, x, y, z, ma.astype(np.float32), sigma, radius))
     assert zeros_ok and err <= TOL, err
+
+
+@pytest.mark.parametrize("blob", [None, "cubic"])
+@pytest.mark.parametrize("N", [400_000, 700_000, 900_000, 1_100_000, 1_400_000])
+def test_first_channel_is_the_plain_render_around_the_fixed_scratch(N, blob):
+    """The form of the slice sums changes where a render nears the fixed
+    scratch's size; the attribute channel's larger records do not move that
+    line, so the image is the plain render's, bit for bit, on both sides."""
+    import torch
+    s = synth.uniform(N, 3)
+    dev = to_dev(s)
+    cam = lib.Camera.ortho(1024, 1024)
+    b = lib.Blob.cubic(h_px=2.5) if blob else None
+    img, _ = lib.splat_aux(*dev, torch.ones_like(dev[0]), cam, blob=b)
+    plain = lib.splat(*dev, cam, blob=b)
+    assert torch.equal(img.view(torch.int32), plain.view(torch.int32))
