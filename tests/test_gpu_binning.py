@@ -148,3 +148,30 @@ def test_first_channel_is_the_plain_render_around_the_fixed_scratch(N, blob):
     img, _ = lib.splat_aux(*dev, torch.ones_like(dev[0]), cam, blob=b)
     plain = lib.splat(*dev, cam, blob=b)
     assert torch.equal(img.view(torch.int32), plain.view(torch.int32))
+
+
+@pytest.mark.parametrize("size", [None, 256, "planned"])
+def test_splat_workspace_forms(size):
+    """A given workspace is tried before the plan is asked: the image is the
+    same with none, one too small and the planned one, on the current stream,
+    and what is refused without one is refused with one."""
+    import torch
+    s = synth.uniform(5000, 9)
+    dev = to_dev(s)
+    cam = lib.Camera.ortho(96, 80)
+    want = lib.splat(*dev, cam)
+    ws = None
+    if size is not None:
+        ws = torch.empty(lib.splat_workspace_bytes(5000, cam) if size == "planned" else size, dtype=torch.uint8,
+                         device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        assert lib._stream().value == side.cuda_stream
+        got = lib.splat(*dev, cam, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    assert torch.equal(got, want)
+    with pytest.raises(lib.LodError):
+        lib.splat(*dev, lib.Camera.ortho(0, 80), workspace=ws, out=want)
+    with pytest.raises(lib.LodError):
+        lib.splat(*dev, cam, sigma=-1.0, workspace=ws)
