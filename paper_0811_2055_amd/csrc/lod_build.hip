@@ -402,28 +402,28 @@ __global__ __launch_bounds__(STB) void k_scatter(BuildArgs a, int shift, const u
 // density (run length of equal depth-L cells) and selection keys
 
 template <bool MAXOP>
-__device__ __forceinline__ uint64_t block_incl_scan_op(uint64_t v, uint64_t *tmp) {
+__device__ __forceinline__ uint32_t block_incl_scan_op(uint32_t v, uint32_t *tmp) {
   // inclusive max- or min-scan over threads in index order
   const int lane = threadIdx.x & (WAVE - 1);
   const int wid = threadIdx.x / WAVE;
   const int nw = blockDim.x / WAVE;
 #pragma unroll
   for (int o = 1; o < WAVE; o <<= 1) {
-    uint64_t t = __shfl_up(v, o, WAVE);
+    uint32_t t = __shfl_up(v, o, WAVE);
     if (lane >= o) v = MAXOP ? max(v, t) : min(v, t);
   }
   if (lane == WAVE - 1) tmp[wid] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint64_t run = MAXOP ? 0ull : ~0ull;
+    uint32_t run = MAXOP ? 0u : ~0u;
     for (int ww = 0; ww < nw; ++ww) {
-      uint64_t t = tmp[ww];
+      uint32_t t = tmp[ww];
       tmp[ww] = run;
       run = MAXOP ? max(run, t) : min(run, t);
     }
   }
   __syncthreads();
-  uint64_t pre = tmp[wid];
+  uint32_t pre = tmp[wid];
   __syncthreads();
   return MAXOP ? max(pre, v) : min(pre, v);
 }
@@ -434,16 +434,23 @@ __device__ __forceinline__ uint64_t block_incl_scan_op(uint64_t v, uint64_t *tmp
 // pass plus a block scan, and runs crossing the tile edge are closed by a
 // binary search over the sorted keys.  The LDS arrays hold word i at
 // i + i/16: blocked accesses (thread t at 16 t + k) would otherwise put a
-// wave's lanes on four banks.
+// wave's lanes on four banks.  Bound by vector issue: the generator's ten
+// rounds are about half of a particle's instructions (14 bytes of traffic take
+// half of the time at the rate of a copy).  Its exclusive ors of three words
+// are single instructions; run starts and ends share a word and scan in 32
+// bits; a batch of snapshots has its own instance: 150 M particles 913 -> 836
+// us, 60 M in 32 snapshots 468 -> 399.  Five waves per SIMD instead of four
+// spill and give nothing (874).
 constexpr int DPAD = (TILE + 2) / 16 + 1;
 __device__ __forceinline__ int dpad(int i) { return i + (i >> 4); }
+template <bool MULTI>
 __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__restrict__ skey,
                                                 const uint32_t *__restrict__ sidx,
                                                 uint32_t *__restrict__ w_out, uint16_t *__restrict__ kb_out) {
   __shared__ uint32_t cell[TILE + 2 + DPAD];   // cell[dpad(i+1)] = cell of element base+i
-  __shared__ uint64_t tmp[TB / WAVE + 1];
-  __shared__ uint64_t incl_max[TB];
-  __shared__ uint64_t rev_min[TB];
+  __shared__ uint32_t tmp[TB / WAVE + 1];
+  __shared__ uint32_t incl_max[TB];
+  __shared__ uint32_t rev_min[TB];
   __shared__ uint64_t first_start, last_end;
   const uint64_t N = a.N;
   const uint64_t base = (uint64_t)blockIdx.x * TILE;
@@ -453,11 +460,11 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
     // clamped, unconditional loads first, then the selects
     constexpr int CI = (TILE + 2 + TB - 1) / TB;
     uint32_t kc[CI];
+    const uint32_t first = base ? 0u : 1u;             // word 0 is element base - 1
+    const uint32_t *kp = skey + (base ? base - 1 : 0);
+    const uint32_t last = (uint32_t)min((uint64_t)TILE + 1, N - base) - first;
 #pragma unroll
-    for (int j = 0; j < CI; ++j) {
-      const int64_t e = (int64_t)base + j * TB + (int)threadIdx.x - 1;
-      kc[j] = skey[(uint64_t)min(max(e, (int64_t)0), (int64_t)N - 1)];
-    }
+    for (int j = 0; j < CI; ++j) kc[j] = kp[min((uint32_t)max(j * TB + (int)threadIdx.x, (int)first) - first, last)];
 #pragma unroll
     for (int j = 0; j < CI; ++j) {
       const int i = j * TB + (int)threadIdx.x;
@@ -517,7 +524,7 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
   // as li + 1 < tile_n, or tile_n for the tile's last run (which ends at
   // last_end).
   // run starts: thread-local running max
-  uint32_t st[ITEMS];
+  uint32_t se[ITEMS];                        // start | end << 16
   uint32_t runmax = 0;
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
@@ -525,12 +532,12 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
     const bool starts =
         (li == 0) ? (!has_prev || cell[dpad(0)] != cell[dpad(1)]) : (cell[dpad(li)] != cell[dpad(li + 1)]);
     if (li < (int)tile_n && starts) runmax = (uint32_t)li + 1;
-    st[i] = runmax;
+    se[i] = runmax;
   }
-  incl_max[threadIdx.x] = block_incl_scan_op<true>((uint64_t)runmax, tmp);
+  incl_max[threadIdx.x] = block_incl_scan_op<true>(runmax, tmp);
   // run ends: thread-local suffix min
-  uint32_t en[ITEMS];
-  uint32_t runmin = 0xFFFFFFFFu;
+  static_assert(TILE < 0xFFFF, "run starts and ends fit 16 bits");
+  uint32_t runmin = 0xFFFFu;
 #pragma unroll
   for (int i = ITEMS - 1; i >= 0; --i) {
     const int li = t0 + i;
@@ -538,20 +545,19 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
       if (li == (int)tile_n - 1) runmin = tile_n;
       else if (cell[dpad(li + 1)] != cell[dpad(li + 2)]) runmin = min(runmin, (uint32_t)li + 1);
     }
-    en[i] = runmin;
+    se[i] |= runmin << 16;
   }
   __syncthreads();
   // suffix over threads: thread t scans the value of thread TB-1-t
   rev_min[threadIdx.x] = runmin;
   __syncthreads();
-  const uint64_t mirrored = rev_min[TB - 1 - threadIdx.x];
+  const uint32_t mirrored = rev_min[TB - 1 - threadIdx.x];
   __syncthreads();
   rev_min[threadIdx.x] = block_incl_scan_op<false>(mirrored, tmp);
   __syncthreads();
-  const uint32_t prev_max = threadIdx.x ? (uint32_t)incl_max[threadIdx.x - 1] : 0u;
+  const uint32_t prev_max = threadIdx.x ? incl_max[threadIdx.x - 1] : 0u;
   // min over threads > t == reversed inclusive scan at position TB-2-t
-  const uint32_t next_min = (threadIdx.x < TB - 1) ? (uint32_t)min(rev_min[TB - 2 - threadIdx.x], 0xFFFFFFFFull)
-                                                   : 0xFFFFFFFFu;
+  const uint32_t next_min = (threadIdx.x < TB - 1) ? rev_min[TB - 2 - threadIdx.x] : 0xFFFFu;
   const uint64_t fs = first_start, le = last_end;
   // run lengths, blocked -> LDS, then striped (coalesced) keys, ids and outputs
   uint32_t *wl = (uint32_t *)cell;           // cell[] is no longer needed; reuse it
@@ -560,7 +566,7 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
   for (int i = 0; i < ITEMS; ++i) {
     const int li = t0 + i;
     if (li < (int)tile_n) {
-      const uint32_t sl = max(st[i], prev_max), el = min(en[i], next_min);
+      const uint32_t sl = max(se[i] & 0xFFFFu, prev_max), el = min(se[i] >> 16, next_min);
       const uint64_t sg = sl ? base + sl - 1 : fs;
       const uint64_t eg = (el == tile_n) ? le : base + el;
       wl[dpad(li)] = (uint32_t)(eg - sg);
@@ -569,36 +575,38 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
   __syncthreads();
   const int sdb = 3 * a.D;
   constexpr int DCH = 8;                     // ids loaded together
+  const uint32_t *ip = sidx + base, *sp = skey + base;
+  uint32_t *wp = w_out + base;
+  uint16_t *bp = kb_out + base;
 #pragma unroll
   for (int c = 0; c < ITEMS; c += DCH) {
     uint32_t ids[DCH], snaps[DCH];
 #pragma unroll
     for (int i = 0; i < DCH; ++i) {
-      ids[i] = sidx[min(base + (uint64_t)((c + i) * TB + threadIdx.x), N - 1)];
+      ids[i] = ip[min((uint32_t)((c + i) * TB + threadIdx.x), tile_n - 1)];
       snaps[i] = 0u;
     }
-    if (a.n_snap > 1) {
+    if (MULTI) {
 #pragma unroll
       for (int i = 0; i < DCH; ++i)
-        snaps[i] = (uint32_t)((uint64_t)skey[min(base + (uint64_t)((c + i) * TB + threadIdx.x), N - 1)] >> sdb);
+        snaps[i] = (uint32_t)((uint64_t)sp[min((uint32_t)((c + i) * TB + threadIdx.x), tile_n - 1)] >> sdb);
     }
     uint32_t exact = 0;                      // items whose bin needs the exact key (rare)
 #pragma unroll
     for (int i = 0; i < DCH; ++i) {
-      const int li = (c + i) * TB + threadIdx.x;
-      if (li < (int)tile_n) {
-        const uint64_t e = base + li;
+      const uint32_t li = (c + i) * TB + threadIdx.x;
+      if (li < tile_n) {
         const uint32_t w = wl[dpad(li)];
         // one snapshot: the counter's words 1-3 are zero, which folds the
         // first round's second product
-        const uint64_t U = a.n_snap > 1 ? particle_U(local_id(a, snaps[i], ids[i]), snaps[i], a.seed)
+        const uint64_t U = MULTI ? particle_U(local_id(a, snaps[i], ids[i]), snaps[i], a.seed)
                                         : (uint64_t)philox_word0(ids[i], 0u, 0u, 0u, (uint32_t)a.seed,
                                                                  (uint32_t)(a.seed >> 32)) + 1ull;
-        w_out[e] = w;
+        wp[li] = w;
         uint32_t bin;
         if (a.alpha <= 0) bin = kbin(selection_key(U, w, a.alpha));
         else if (!kbin_div_fast(U, w, bin)) exact |= 1u << i;
-        if (!((exact >> i) & 1u)) kb_out[e] = (uint16_t)bin;
+        if (!((exact >> i) & 1u)) bp[li] = (uint16_t)bin;
       }
     }
     // one copy of the exact path, entered by few lanes
@@ -607,7 +615,7 @@ __global__ __launch_bounds__(TB) void k_density(BuildArgs a, const uint32_t *__r
       exact &= exact - 1u;
       const int li = (c + i) * TB + threadIdx.x;
       const uint64_t e = base + li;
-      const uint32_t snap = a.n_snap > 1 ? (uint32_t)((uint64_t)skey[e] >> sdb) : 0u;
+      const uint32_t snap = MULTI ? (uint32_t)((uint64_t)skey[e] >> sdb) : 0u;
       const uint64_t U = particle_U(local_id(a, snap, sidx[e]), snap, a.seed);
       kb_out[e] = (uint16_t)kbin(div_u2p31(U, wl[dpad(li)]));
     }
@@ -2214,7 +2222,7 @@ lod_status launch_build(const lod_input &in, const lod_params &p, void *ws, cons
       return LOD_EDEVICE;
     dst = side->s;
   }
-  LOD_LAUNCH(k_density, dim3((unsigned)dtiles), dim3(TB), 0, dst, a, ks, is,
+  LOD_LAUNCH_NAMED("k_density", n_snap > 1 ? k_density<true> : k_density<false>, dim3((unsigned)dtiles), dim3(TB), 0, dst, a, ks, is,
              (uint32_t *)(W + L.w), (uint16_t *)(W + L.kb));
   if (side && hipEventRecord(side->join, side->s) != hipSuccess) return LOD_EDEVICE;
 

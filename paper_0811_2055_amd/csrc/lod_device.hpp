@@ -24,7 +24,9 @@ __device__ __forceinline__ uint32_t philox_word0(uint32_t c0, uint32_t c1, uint3
     if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
     // one 32 x 32 -> 64-bit multiply gives both halves of each product
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    // three-operand exclusive or (truth table 0x96)
+    const uint32_t n0 = (uint32_t)__builtin_amdgcn_bitop3_b32((int)(uint32_t)(p1 >> 32), (int)c1, (int)k0, 0x96);
+    const uint32_t n2 = (uint32_t)__builtin_amdgcn_bitop3_b32((int)(uint32_t)(p0 >> 32), (int)c3, (int)k1, 0x96);
     c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
   }
   return c0;
