@@ -230,7 +230,8 @@ lod_status splat_plan(uint64_t max_points, const lod_camera *cam, const splat_pa
 /* image[j*W + i] = sum_k m_k exp(-(ox^2+oy^2)/(2 s^2)) / (2 pi s^2) over
  * points whose truncated blob covers pixel (i,j); ox = fl(u - (i+1/2)),
  * oy = fl(v - (j+1/2)) in float32 from the pinned projection sequence
- * (no fused multiply-add); sums accumulated in float32 with compensation.
+ * (no fused multiply-add); products of 64 points summed in float32 on the matrix
+ * cores, everything beyond in float64, rounded once to float32.
  * x,y,z,m: device float32 [count]; image: device float32 [H*W], overwritten. */
 lod_status splat_render(const float *x, const float *y, const float *z, const float *m,
                         uint64_t count, const lod_camera *cam, const splat_params *sp,

@@ -12,9 +12,9 @@
 //   density    run lengths of equal depth-L cells (block max/min scans), then
 //              Philox U and the 12-bit bin of the integer selection key K per
 //              sorted position (on a second stream, beside the tree)
-//   tree       level by level: octant boundaries by binary search, then the
-//              next level emitted with one thread per (node, octant): counts,
-//              one scan, writes
+//   tree       the first levels by one block; then level by level: octant
+//              boundaries by a nine-way search of eight lanes per octant, and
+//              the next level written with one thread per (node, octant)
 //   leaves     float64 leaf masses; the per-level schedule copies the leaves'
 //              particles inside its selection launches
 //   selection  bottom up, per node holding > n: the node's float64 mass from
@@ -2044,12 +2044,6 @@ void fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t st) {
   if (!n) return;
   const unsigned g = (unsigned)std::min<uint64_t>(1024, (n + 255) / 256);
   LOD_LAUNCH(k_fill<uint64_t>, dim3(g), dim3(256), 0, st, p, n, v);
-}
-
-void fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st) {
-  if (!n) return;
-  const unsigned g = (unsigned)std::min<uint64_t>(1024, (n + 255) / 256);
-  LOD_LAUNCH(k_fill<uint32_t>, dim3(g), dim3(256), 0, st, p, n, v);
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }

@@ -119,6 +119,5 @@ lod_status launch_cut(const lod_tree &tree, const lod_camera &cam, float tau_px,
 
 // small utilities
 void fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t st);
-void fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st);
 
 }  // namespace lodh

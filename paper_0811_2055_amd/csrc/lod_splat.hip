@@ -5,14 +5,15 @@
 // Forward: points are binned to 16x16 pixel tiles by a stable counting sort
 // (per-wave units, a count pass and a fill pass, ballot ranks inside the
 // wave), so a tile's pair list depends on the input alone.  Each list is cut
-// into slices of at most 2048 points; one 256-thread block per slice adds the
-// separable blobs to its 16x16 tile as rank-64 products on the matrix cores
-// (MFMA 16x16x4, float32).  Each wave folds its products into compensated
-// (Neumaier) float32 sums of its own, and the four wave sums of a pixel are
-// folded in wave order at the end of the slice.  A final pass adds a tile's
-// slice partials in slice order, again compensated.  No floating-point atomics:
-// the image is bit-reproducible.  The LOD render feeds the binning straight
-// from the tree's 16-bit node-relative points, decoding them in registers.
+// into slices; one 256-thread block per slice adds the separable blobs to its
+// 16x16 tile as rank-64 products on the matrix cores (MFMA 16x16x4, float32).
+// Each wave adds its products to float64 sums of its own, the four wave sums
+// of a pixel are added in wave order at the end of the slice, and a final pass
+// adds a tile's slice partials in slice order.  The cubic blob, which is not
+// separable, is evaluated pixel by pixel (float64).  Every order of addition
+// is fixed: the image is bit-reproducible.  The LOD render feeds the binning
+// straight from the tree's 16-bit node-relative points, decoding them in
+// registers.
 //
 // The screen position and pixel offsets follow a fixed float32 sequence with
 // no contraction (this file is compiled with -ffp-contract=off) so that the
@@ -43,7 +44,6 @@ struct Cam {
   float inv2s2;     // 1 / (2 sigma^2)
   float norm;       // 1 / (2 pi sigma^2)
   float inv_s2;     // 1 / sigma^2
-  int win;          // candidate half-window, ceil(R) + 2
   int nin, nmax;    // pixels at most nin from the one that holds the point are covered, none beyond nmax is
   float cn[5];      // exp2(kexp2 n^2), n = 0 .. 4
   float cl[3];      // what float32 leaves of cn[0 .. 2]: the same rounding at every
@@ -53,7 +53,6 @@ struct Cam {
   uint32_t blob;    // LOD_BLOB_GAUSSIAN or LOD_BLOB_CUBIC
   float hpx;        // cubic: fixed pixel radius (when Fhw == 0)
   float Fhw;        // cubic, perspective world size: fl(F h_world), else 0
-  float hmax;       // largest pixel radius a blob can take (binning window)
 };
 
 Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayout *L) {
@@ -70,7 +69,6 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   k.inv2s2 = (float)(1.0 / (2.0 * s64 * s64));
   k.norm = (float)(1.0 / (2.0 * M_PI * s64 * s64));
   k.inv_s2 = (float)(1.0 / (s64 * s64));
-  k.win = (int)std::ceil((double)k.R) + 2;
   k.kexp2 = (float)(-1.4426950408889634 / (2.0 * s64 * s64));
   // the point lies within half a pixel of its pixel's centre; the binning admits
   // pixels 1/100 further out, and its float32 range and the
@@ -87,8 +85,6 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   k.blob = sp.blob;
   k.hpx = sp.h_px;
   k.Fhw = (sp.blob == LOD_BLOB_CUBIC && sp.h_world > 0.0f) ? c.F * sp.h_world : 0.0f;
-  k.hmax = lodh::blob_max_radius(sp);
-  if (sp.blob == LOD_BLOB_CUBIC) k.win = (int)std::ceil((double)k.hmax) + 2;
   return k;
 }
 
@@ -921,13 +917,6 @@ __global__ __launch_bounds__(BW) void k_bin_fill(Src src, Cam c, uint32_t units,
   } else {
     bin_unit<Src, true, RowTab, RecT>(src, c, units, u0, g, nbits, RowTab{row, tile_off, pre}, rec);
   }
-}
-
-__device__ __forceinline__ void neumaier(float &s, float &c, float x) {
-  const float t = s + x;
-  if (fabsf(s) >= fabsf(x)) c += (s - t) + x;
-  else c += (x - t) + s;
-  s = t;
 }
 
 // --- accumulation --------------------------------------------------------------
