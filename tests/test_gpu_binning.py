@@ -175,3 +175,14 @@ def test_splat_workspace_forms(size):
         lib.splat(*dev, lib.Camera.ortho(0, 80), workspace=ws, out=want)
     with pytest.raises(lib.LodError):
         lib.splat(*dev, cam, sigma=-1.0, workspace=ws)
+
+
+@pytest.mark.parametrize("W,H", [(512, 512), (513, 512)])
+@pytest.mark.parametrize("N", [30_000, 40_000, 520_000, 600_000])
+def test_chunk_scans_beside_the_tile_plan(W, H, N):
+    """1024 tiles (their chunk scans run in the plan's block) and 1056 (in a
+    launch of their own); one chunk of units, two, sixteen and nineteen."""
+    s = synth.uniform(N, 12)
+    img = lib.splat(*to_dev(s), lib.Camera.ortho(W, H)).cpu().numpy()
+    err, zeros_ok = image_rel_err(img, osplat.render(osplat.Camera(0, W, H), s.x, s.y, s.z, s.m))
+    assert zeros_ok and err <= 1e-5, (W, H, N, err)
