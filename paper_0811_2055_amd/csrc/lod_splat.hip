@@ -1526,7 +1526,9 @@ __global__ __launch_bounds__(PT) void k_backward_cubic(const float *__restrict__
     const bool have = k < count;
     float u = 0.0f, v = 0.0f, xc = 0.0f, yc = 0.0f, zc = 0.0f;
     const bool vis = have && project(c, x[k], y[k], z[k], u, v, xc, yc, zc);
-    const float h = vis ? cubic_radius(c, zc) : c.hpx;
+    // a culled point's pixel count is 0 and its sums stay 0: any finite radius
+    // (the camera's fixed one may be 0 beside a world radius)
+    const float h = vis ? cubic_radius(c, zc) : lodh::BLOB_H_MIN;
     bool dh_live = false;
     if (vis && radius) {
       const float hp = __fdiv_rn(c.Fhw, zc);
