@@ -43,11 +43,10 @@ struct Cam {
   float R;          // truncation half-width in pixels (float32)
   float inv2s2;     // 1 / (2 sigma^2)
   float norm;       // 1 / (2 pi sigma^2)
+  float wscale;     // the power of two below it: multiplies masses without rounding
+  double wnorm;     // 1 / (2 pi sigma^2) / wscale: multiplies a slice's float64 sums
   float inv_s2;     // 1 / sigma^2
   int nin, nmax;    // pixels at most nin from the one that holds the point are covered, none beyond nmax is
-  float cn[5];      // exp2(kexp2 n^2), n = 0 .. 4
-  float cl[3];      // what float32 leaves of cn[0 .. 2]: the same rounding at every
-  float norm_lo;    // point would not average out; and of norm
   float kexp2;      // -log2(e) / (2 sigma^2): Gaussian factor = exp2(o^2 kexp2)
   uint32_t tiles_x, tiles_y;
   uint32_t blob;    // LOD_BLOB_GAUSSIAN or LOD_BLOB_CUBIC
@@ -75,12 +74,10 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   // offsets are within 1/200 pixel of the exact ones
   k.nin = (int)std::floor((double)k.R - 0.52);
   k.nmax = (int)std::floor((double)k.R + 0.52);
-  for (int n = 0; n < 5; ++n) {
-    const double e = std::exp(-(double)(n * n) / (2.0 * s64 * s64));
-    k.cn[n] = (float)e;
-    if (n < 3) k.cl[n] = (float)(e - (double)k.cn[n]);
-  }
-  k.norm_lo = (float)(1.0 / (2.0 * M_PI * s64 * s64) - (double)k.norm);
+  const double norm = 1.0 / (2.0 * M_PI * s64 * s64);
+  const int e2 = std::min(std::ilogb(norm), 127);
+  k.wscale = std::ldexp(1.0f, e2);
+  k.wnorm = norm / std::ldexp(1.0, e2);
   if (L) { k.tiles_x = L->tiles_x; k.tiles_y = L->tiles_y; }
   k.blob = sp.blob;
   k.hpx = sp.h_px;
@@ -1022,13 +1019,14 @@ __device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
   (f(std::integral_constant<int, T>{}), ...);
 }
 
-// Narrow blobs: radius below 3.98 pixels, sigma at least 1/2.  The Gaussian of
-// the pixel n steps from the one that holds the point (offset d - n, |d| <=
-// 1/2) is exp2(k d^2) exp2(-2 k d)^n exp2(k n^2): three hardware exponentials
-// of small arguments per axis and a chain of products, where every pixel took
-// an exponential of its own (whose argument, up to 6.5, carried more rounding
-// than the products do).  Only the pixels between nin and nmax steps away need
-// the truncation test.
+// Narrow blobs: radius below 3.98 pixels.  A pixel's Gaussian is one hardware
+// exponential of its own offset; only the pixels between nin and nmax steps
+// away from the one that holds the point need the truncation test.  (A chain
+// of products from pixel to pixel, three exponentials per axis, draws 150 M
+// points in 1.89 ms where this takes 2.03, but carries a rounding of the
+// exponential per step: 1.2 to 1.4 times the error of an axis at sigma 0.5 to
+// 1, 2.1 times at 2 and 4.4 times at 8.)  The mass takes only the power of two
+// in the normalisation; the rest multiplies the float64 sums.
 //
 // A point's window of up to nine values goes to the same columns of its row,
 // 0 .. 2 nmax, with 16 zeros on either side that nothing overwrites, so
@@ -1039,11 +1037,12 @@ __device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
 // read before y rows overwrite them, which halves the LDS per wave.
 //
 // Bound by vector issue beside the matrix steps (a chunk of 64 points: about
-// 150 vector instructions and 16 matrix steps of 32 cycles).  150 M points
-// drawn at 1024^2, 285 M pairs: 2.31 -> 1.88 ms against a form that cleared and
-// wrote 8-wide windows at varying columns (LDS bank conflicts half of the LDS
-// time, 16 exponentials per point, four waves per SIMD; now six).  Error of
-// that image against float64 3.5e-8 -> 3.1e-8.
+// 170 vector instructions, 14 of them exponentials, and 16 matrix steps of 32
+// cycles).  150 M points drawn at 1024^2, 285 M pairs: 2.31 -> 2.03 ms against a
+// form that cleared and wrote 8-wide windows at varying columns (LDS bank
+// conflicts half of the LDS time, 16 exponentials per point, four waves per
+// SIMD; now six).  Error against float64 at sigma 1, radius 3, 16 points to a
+// pixel: 5.1e-8 -> 3.0e-8.
 constexpr int NPAD = TS;
 constexpr int NROW = 9 + TS;                  // odd: lane i's window starts on its own bank
 constexpr int NWAVE = TS + WAVE * NROW;       // a wave's rows: the zeros after one row precede the next
@@ -1083,19 +1082,14 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
       auto window = [&](float x, int t0, float w0) -> uint32_t {
         const float fc = floorf(x);
         const float d = x - (fc + 0.5f);
-        const float tw = -2.0f * c.kexp2 * d;
-        const float rp = __builtin_amdgcn_exp2f(tw), rm = __builtin_amdgcn_exp2f(-tw);
-        const float e0 = w0 * __builtin_amdgcn_exp2f((d * d) * c.kexp2);
         const float R = c.R;
-        float ep = e0, em = e0;
+        auto gauss = [&](float o) { return w0 * __builtin_amdgcn_exp2f((o * o) * c.kexp2); };
+        const float e0 = gauss(d);
         mine[nmax] = (nin >= 0 || fabsf(d) <= R) ? e0 : 0.0f;
 #pragma unroll
         for (int n = 1; n <= 4; ++n) {
           if (n > nmax) break;                                  // uniform
-          ep *= rp;
-          em *= rm;
-          float vp = n < 3 ? __builtin_fmaf(ep, c.cn[n], ep * c.cl[n < 3 ? n : 0]) : ep * c.cn[n];
-          float vm = n < 3 ? __builtin_fmaf(em, c.cn[n], em * c.cl[n < 3 ? n : 0]) : em * c.cn[n];
+          float vp = gauss(d - (float)n), vm = gauss(d + (float)n);
           if (n > nin) {
             vp = fabsf(x - ((fc + (float)n) + 0.5f)) <= R ? vp : 0.0f;
             vm = fabsf(x - ((fc - (float)n) + 0.5f)) <= R ? vm : 0.0f;
@@ -1113,7 +1107,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
       wave_sync_mem();
       for_16([&](auto st) { bv[st] = at_byte(row_bcast<st>(rx) + pxb); }, std::make_integer_sequence<int, 16>{});
       wave_sync_mem();
-      const uint32_t ry = window(v, ty0, __builtin_fmaf(m, c.norm, m * c.norm_lo));
+      const uint32_t ry = window(v, ty0, m * c.wscale);
       wave_sync_mem();
       for_16([&](auto st) { av[st] = at_byte(row_bcast<st>(ry) + pxb); }, std::make_integer_sequence<int, 16>{});
       wave_sync_mem();
@@ -1145,7 +1139,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
       double s = 0.0;
 #pragma unroll
       for (int g = 0; g < NW; ++g) s += reinterpret_cast<const double *>(rows[g])[threadIdx.x];
-      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s);
+      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s * c.wnorm);
       __syncthreads();
     }
 #pragma unroll
@@ -1186,7 +1180,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
       // A pixel is covered when its float32 offset fl(t - (i + 1/2)) lies in
       // [-R, R].  Pixels past the image edge are computed and dropped by the
       // final sum; lanes past the slice carry mass 0.
-      const float R = c.R, w0 = __builtin_fmaf(m, c.norm, m * c.norm_lo);
+      const float R = c.R, w0 = m * c.wscale;
       const float cx0 = (float)tx0 + 0.5f, cy0 = (float)ty0 + 0.5f;
 #pragma unroll
       for (int e = 0; e < TS; ++e) {
@@ -1228,7 +1222,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
       double s = 0.0;
 #pragma unroll
       for (int g = 0; g < NW; ++g) s += part[g][threadIdx.x];
-      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s);
+      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s * c.wnorm);
       __syncthreads();
     }
   }
@@ -2072,9 +2066,7 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
       LOD_LAUNCH(k_accumulate_cubic<RecT>, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
                  partial_aux, L.max_slices, L.max_pairs);
     } else {
-      // the narrow form's windows hold nine pixels; below sigma = 1/2 its
-      // products could overflow where the Gaussian itself underflows
-      const bool narrow = c.R < 3.98f && sp.sigma_px >= 0.5f;
+      const bool narrow = c.R < 3.98f;   // windows of nine pixels
       auto acc = [&](auto kernel) {
         LOD_LAUNCH_NAMED("k_accumulate", kernel, dim3(agrid), dim3(PT), 0, st, stab, soff, nt, rec, c, partial,
                          partial_aux, L.max_slices, L.max_pairs);
