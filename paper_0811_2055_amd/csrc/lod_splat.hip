@@ -1013,6 +1013,10 @@ __device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + FROM, 0xF, 0xF, true);
 }
 
+// A row value times its point's attribute; 0 where the blob does not reach the
+// row, also for an attribute that is infinite or NaN.
+__device__ __forceinline__ float times_attr(float row, float at) { return row != 0.0f ? row * at : 0.0f; }
+
 // Calls f(integral_constant<int, 0>) .. f(integral_constant<int, 15>).
 template <class F, int... T>
 __device__ __forceinline__ void for_16(F f, std::integer_sequence<int, T...>) {
@@ -1118,7 +1122,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
       for (int i = 0; i < 4; ++i) sum[0][i] += (double)acc[i];
       if constexpr (AUX) {
         // the second channel's rows are the first's times the point's attribute
-        for_16([&](auto st) { av[st] *= __uint_as_float(row_bcast<st>(__float_as_uint(at))); },
+        for_16([&](auto st) { av[st] = times_attr(av[st], __uint_as_float(row_bcast<st>(__float_as_uint(at)))); },
                std::make_integer_sequence<int, 16>{});
         float4v acc2 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -1205,7 +1209,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
 #pragma unroll
       for (int i = 0; i < 4; ++i) sum[0][i] += (double)acc[i];
       if constexpr (AUX) {
-        for_16([&](auto st) { av[st] *= __uint_as_float(row_bcast<st>(__float_as_uint(at))); },
+        for_16([&](auto st) { av[st] = times_attr(av[st], __uint_as_float(row_bcast<st>(__float_as_uint(at)))); },
                std::make_integer_sequence<int, 16>{});
         float4v acc2 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
