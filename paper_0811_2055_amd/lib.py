@@ -541,8 +541,13 @@ def splat(x, y, z, m, cam: Camera, sigma=1.0, radius_sigmas=3.0, workspace=None,
         # (before it enqueues anything) when it is not, and the plan's 10 us of
         # host time are spent only then
         img = out if out is not None else torch.empty((cam.H, cam.W), dtype=torch.float32, device=dev)
-        if lib.splat_render(_ptr(x), _ptr(y), _ptr(z), _ptr(m), N, C.byref(camc), C.byref(sp),
-                            _ptr(workspace), workspace.numel(), _ptr(img), _stream()) == LOD_OK:
+        code = lib.splat_render(_ptr(x), _ptr(y), _ptr(z), _ptr(m), N, C.byref(camc), C.byref(sp),
+                                _ptr(workspace), workspace.numel(), _ptr(img), _stream())
+        # too small or (empty, a small part of a larger one) not a workspace at all:
+        # planned and replaced below; anything else is final (the call that
+        # reports a device error clears it)
+        if code not in (LOD_ENOMEM, LOD_EINVAL):
+            _check(code, "splat_render")
             return img
     ws = splat_workspace_bytes(N, cam, sigma, radius_sigmas, blob)
     if workspace is None or workspace.numel() < ws:
