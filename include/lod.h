@@ -223,7 +223,9 @@ lod_status lod_select(const lod_tree *tree, const lod_camera *cam, float tau_px,
 /* ---- additive point splat (rendering paragraph) ----------------------- */
 
 /* Workspace bytes for splatting up to max_points points with cam/sp, by
- * splat_render or splat_render_aux. */
+ * splat_render or splat_render_aux.  No image depends on the size that its
+ * workspace was planned for, nor on max_points of the calls below (as long as
+ * every point is drawn). */
 lod_status splat_plan(uint64_t max_points, const lod_camera *cam, const splat_params *sp,
                       size_t *workspace_bytes);
 
@@ -370,19 +372,21 @@ lod_status splat_render_backward(const float *x, const float *y, const float *z,
 
 /* ---- allocation-free splat --------------------------------------------- */
 
-/* Bytes of the device array that splat_render_noalloc uses as its workspace
- * (one array per device, held until the process ends). */
+/* The size up to which splat_render_noalloc accepts a call: the binning table
+ * of units of 2048 points, the (point, tile) records and 1 KB per image tile and
+ * per 4096 records.  Its device array (one per device, held until the process
+ * ends) is 16 MiB larger. */
 #define LOD_NOALLOC_SCRATCH_BYTES (64u << 20)
 
 /* For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc): splat_render with
- * its workspace taken from a fixed 64 MiB device array inside the library
+ * its workspace taken from a fixed device array inside the library
  * instead of a caller buffer.  Same arguments, image and bits as
  * splat_render.  Allocates nothing (no hipMalloc, no library allocation);
  * the first call on a device looks up that device's array address.
- * LOD_ECAPACITY, with nothing enqueued, when splat_plan(count, cam, sp)
- * exceeds LOD_NOALLOC_SCRATCH_BYTES (about 1.2 M points at 1024x1024 with
- * the default blob).  All calls on one device share its array: calls that
+ * LOD_ECAPACITY, with nothing enqueued, when that size exceeds
+ * LOD_NOALLOC_SCRATCH_BYTES (at 1,086,475 points at 1024x1024 with the default
+ * blob).  All calls on one device share its array: calls that
  * overlap in time on one device (several streams or host threads) race and
  * must be serialised by the caller. */
 lod_status splat_render_noalloc(const float *x, const float *y, const float *z, const float *m,

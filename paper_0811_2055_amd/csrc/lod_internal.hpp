@@ -33,8 +33,6 @@ void *workspace_view(void *ws, const BuildLayout &L, uint32_t which, uint64_t N,
 struct SplatLayout {
   uint32_t tiles_x, tiles_y, n_tiles;
   uint32_t units, chunks;            // binning units (waves), 64 per chunk
-  uint32_t slice;                    // pairs per accumulation slice
-  bool wide;                         // slice partials in float64
   uint64_t max_points, max_pairs, max_slices;
   bool aux;                          // an attribute channel is drawn
   size_t tile_count, tile_off, ucount, pchunk, slice_off, counters;
@@ -44,7 +42,6 @@ struct SplatLayout {
 
 constexpr int SPLAT_TS = 16;           // tile edge in pixels
 constexpr uint32_t SPLAT_MAX_TILES = 8192;
-constexpr uint32_t SPLAT_SLICE = 4096; // pairs per accumulation slice of large renders
 constexpr uint32_t SPLAT_MAX_CHUNKS = 64;
 constexpr float BLOB_H_MIN = 1.0f;     // cubic blob: clamp of a projected world radius, pixels
 constexpr float BLOB_H_MAX = 16.0f;
@@ -57,6 +54,7 @@ inline float blob_max_radius(const splat_params &sp) {
 
 lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_params &sp,
                         SplatLayout &L, bool aux, bool few_units = false);
+size_t noalloc_size(uint64_t count, const splat_params &sp, const SplatLayout &L);
 lod_status launch_splat(const float *x, const float *y, const float *z, const float *m, const float *aux,
                         uint64_t count, const lod_camera &cam, const splat_params &sp, void *ws, const SplatLayout &L,
                         float *image, float *image_aux, hipStream_t st);

@@ -850,6 +850,33 @@ __global__ void k_bin_chunkscan(uint32_t *__restrict__ pchunk, uint32_t nt, uint
   if (t < nt) tile_count[t] = scan_chunks(pchunk, nt, chunks, t);
 }
 
+// log2 of the pairs of a slice (a block's share of a tile's list) when `pairs`
+// pairs are drawn: a function of the image's input alone, not of the sizes that
+// the workspace was planned for, because the order of the float64 sums depends
+// on it.
+// Long slices of dense tiles end last and leave CUs idle; short ones add
+// partial tiles and sums, and a cubic slice takes longer.  Accumulation and
+// final sums in us at slices of 512, 1024, 2048 and 4096:
+//   Gaussian, 256^2, clumps    2^19 pairs 17.5 19.2 22.2 25.9
+//             (1024^2)         2^20  23.5 22.4 26.6 32.6   (41.6 39.7 42.7 49.4)
+//                              2^22  56.3 49.0 49.2 56.0   (75.4 68.6 67.8 76.2)
+//                              2^23  100 86 80 83          (117 103 101 107)
+//                              2^25  346 291 278 265       (336 299 289 289)
+//                              2^27  1379 1190 1081 1048   (1262 1128 1060 1024)
+//   cubic, h = 2.5, 1024^2,    2^19  73 96 118 168         (68 66 67 66)
+//          clumps (uniform)    2^21  156 175 220 266       (144 138 138 139)
+//                              2^22  267 275 313 381       (263 248 245 245)
+//                              2^23  473 474 496 561       (493 476 457 458)
+//                              2^26  3409 3379 3360 3338   (3544 3455 3665 3668)
+__host__ __device__ inline uint32_t slice_bits(uint32_t pairs, bool cubic) {
+  if (cubic) return pairs <= 1u << 21 ? 9 : pairs <= 1u << 26 ? 10 : 12;
+  return pairs <= 1u << 19 ? 9 : pairs <= 1u << 22 ? 10 : pairs <= 1u << 25 ? 11 : 12;
+}
+
+__device__ __forceinline__ uint32_t slices_of(uint32_t pairs, uint32_t bits) {
+  return (pairs + (1u << bits) - 1u) >> bits;
+}
+
 // Offsets of the tiles' pair lists and of their slices (exclusive, with the
 // totals at [nt]), and a cleared status word: one block, since there are at
 // most 8192 tiles.  tile_count null: no points.  pchunk not null: at most PLAN_T
@@ -859,7 +886,7 @@ constexpr int PLAN_T = 1024;
 constexpr int PLAN_ITEMS = lodh::SPLAT_MAX_TILES / PLAN_T;
 __global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict__ tile_count,
                                                       uint32_t *__restrict__ pchunk, uint32_t chunks, uint32_t nt,
-                                                      uint32_t slice,
+                                                      int cubic,
                                                       uint32_t *__restrict__ tile_off,
                                                       uint32_t *__restrict__ slice_off, uint64_t *clear_status) {
   __shared__ uint32_t tmp[PLAN_T / WAVE + 1];
@@ -872,18 +899,18 @@ __global__ __launch_bounds__(PLAN_T) void k_tile_plan(const uint32_t *__restrict
     cnt[k] = pchunk ? (k ? 0u : scanned)
                     : (tile_count && (uint32_t)k < per && t0 + k < nt) ? tile_count[t0 + k] : 0u;
 #pragma unroll
-  for (int k = 0; k < PLAN_ITEMS; ++k) {
-    pairs += cnt[k];
-    slices += (cnt[k] + slice - 1) / slice;
-  }
+  for (int k = 0; k < PLAN_ITEMS; ++k) pairs += cnt[k];
   uint32_t tp, ts;
   uint32_t p = block_excl_scan<uint32_t>(pairs, tmp, tp);
+  const uint32_t bits = slice_bits(tp, cubic);
+#pragma unroll
+  for (int k = 0; k < PLAN_ITEMS; ++k) slices += slices_of(cnt[k], bits);
   uint32_t q = block_excl_scan<uint32_t>(slices, tmp, ts);
 #pragma unroll
   for (int k = 0; k < PLAN_ITEMS; ++k) {
     if ((uint32_t)k < per && t0 + k < nt) { tile_off[t0 + k] = p; slice_off[t0 + k] = q; }
     p += cnt[k];
-    q += (cnt[k] + slice - 1) / slice;
+    q += slices_of(cnt[k], bits);
   }
   if (threadIdx.x == 0) {
     tile_off[nt] = tp;
@@ -905,11 +932,12 @@ template <class Src, class RecT, bool LDS>
 __global__ __launch_bounds__(BW) void k_bin_fill(Src src, Cam c, uint32_t units, uint32_t g, int nbits,
                                                  uint32_t *ucount, const uint32_t *__restrict__ pchunk,
                                                  const uint32_t *__restrict__ tile_off,
-                                                 const uint32_t *__restrict__ slice_off, uint32_t slice,
+                                                 const uint32_t *__restrict__ slice_off,
                                                  uint2 *__restrict__ table, uint64_t max_slices, RecT *__restrict__ rec, uint64_t max_pairs,
                                                  uint64_t *status) {
   extern __shared__ uint32_t lc[];
   const uint32_t nt = c.tiles_x * c.tiles_y;
+  const uint32_t slice = 1u << slice_bits(tile_off[nt], RecInfo<RecT>::cubic);
   for (uint32_t t = blockIdx.x * BW + threadIdx.x; t < nt; t += gridDim.x * BW) {
     const uint32_t b = slice_off[t], e = slice_off[t + 1];
     const uint32_t p = tile_off[t], cnt = tile_off[t + 1] - p;
@@ -958,20 +986,6 @@ __device__ __forceinline__ void load_rec(const RecGA *r, uint64_t q, float &u, f
 }
 
 typedef float float4v __attribute__((ext_vector_type(4)));
-
-// Slice partials: float64 (rounded once, in the image), or float32 where the
-// workspace has to stay as small as it was.
-struct Partial {
-  void *p;
-  bool wide;
-  __device__ __forceinline__ void put(uint64_t i, double v) const {
-    if (wide) reinterpret_cast<double *>(p)[i] = v;
-    else reinterpret_cast<float *>(p)[i] = (float)v;
-  }
-  __device__ __forceinline__ double get(uint64_t i) const {
-    return wide ? reinterpret_cast<const double *>(p)[i] : (double)reinterpret_cast<const float *>(p)[i];
-  }
-};
 
 // The slices of a block and their records, loaded one chunk ahead across slice
 // boundaries (clamped indices: every load is issued unconditionally).  Pair
@@ -1055,7 +1069,7 @@ template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restrict__ table,
                                                           const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                           const RecT *__restrict__ rec, Cam c,
-                                                          Partial partial, Partial partial_aux, uint64_t max_slices,
+                                                          double *__restrict__ partial, double *__restrict__ partial_aux, uint64_t max_slices,
                                                           uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
@@ -1143,7 +1157,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_narrow(const uint2 *__restric
       double s = 0.0;
 #pragma unroll
       for (int g = 0; g < NW; ++g) s += reinterpret_cast<const double *>(rows[g])[threadIdx.x];
-      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s * c.wnorm);
+      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = s * c.wnorm;
       __syncthreads();
     }
 #pragma unroll
@@ -1159,7 +1173,7 @@ template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict__ table,
                                                         const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                         const RecT *__restrict__ rec, Cam c,
-                                                        Partial partial, Partial partial_aux,
+                                                        double *__restrict__ partial, double *__restrict__ partial_aux,
                                                         uint64_t max_slices, uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE, NCH = AUX ? 2 : 1;
@@ -1226,7 +1240,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
       double s = 0.0;
 #pragma unroll
       for (int g = 0; g < NW; ++g) s += part[g][threadIdx.x];
-      (ch ? partial_aux : partial).put((uint64_t)sw.sl * (TS * TS) + threadIdx.x, s * c.wnorm);
+      (ch ? partial_aux : partial)[(uint64_t)sw.sl * (TS * TS) + threadIdx.x] = s * c.wnorm;
       __syncthreads();
     }
   }
@@ -1238,7 +1252,7 @@ __global__ __launch_bounds__(PT) void k_accumulate_wide(const uint2 *__restrict_
 // clump has thousands of slices), and the shares are added in order.
 constexpr int FIN_G = 4;
 __global__ __launch_bounds__(FIN_G * PT) void k_finalize(const uint32_t *__restrict__ slice_off, uint32_t nt,
-                                                         Partial partial, Cam c,
+                                                         const double *__restrict__ partial, Cam c,
                                                          float *__restrict__ image, uint64_t max_slices) {
   __shared__ double share[FIN_G - 1][PT];
   const uint32_t g = threadIdx.x / PT, p = threadIdx.x % PT;
@@ -1250,7 +1264,7 @@ __global__ __launch_bounds__(FIN_G * PT) void k_finalize(const uint32_t *__restr
     for (uint32_t sl = b1; sl < e1; sl += 16) {
       double v[16];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = partial.get((uint64_t)min(sl + k, e1 - 1) * (TS * TS) + p);
+      for (int k = 0; k < 16; ++k) v[k] = partial[(uint64_t)min(sl + k, e1 - 1) * (TS * TS) + p];
 #pragma unroll
       for (int k = 0; k < 16; ++k)
         if (sl + k < e1) s += v[k];
@@ -1333,7 +1347,7 @@ template <class RecT>
 __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict__ table,
                                                          const uint32_t *__restrict__ slice_off, uint32_t nt,
                                                          const RecT *__restrict__ rec, Cam c,
-                                                         Partial partial, Partial partial_aux, uint64_t max_slices,
+                                                         double *__restrict__ partial, double *__restrict__ partial_aux, uint64_t max_slices,
                                                          uint64_t max_pairs) {
   constexpr bool AUX = RecInfo<RecT>::aux;
   constexpr int NW = PT / WAVE;
@@ -1472,8 +1486,8 @@ __global__ __launch_bounds__(PT) void k_accumulate_cubic(const uint2 *__restrict
 #pragma unroll
       for (int g = 0; g < NW * CSUM; ++g) s[ch] += sum[g / CSUM][g % CSUM][ch][o];
     }
-    partial.put((uint64_t)sl * (TS * TS) + threadIdx.x, s[0]);
-    if constexpr (AUX) partial_aux.put((uint64_t)sl * (TS * TS) + threadIdx.x, s[CH - 1]);
+    partial[(uint64_t)sl * (TS * TS) + threadIdx.x] = s[0];
+    if constexpr (AUX) partial_aux[(uint64_t)sl * (TS * TS) + threadIdx.x] = s[CH - 1];
     __syncthreads();
   }
 }
@@ -1954,46 +1968,38 @@ lod_status splat_layout(uint64_t max_points, const lod_camera &cam, const splat_
   L.chunks = (uint32_t)std::min<uint64_t>(SPLAT_MAX_CHUNKS,
                                           std::max<uint64_t>(1, (max_points + 64 * unit - 1) / (64 * unit)));
   L.units = 64 * L.chunks;
-  auto lay_out = [&](uint32_t units, uint32_t slice, bool wide, bool aux) {
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-    L.slice = slice;
-    L.wide = wide;
-    L.max_slices = nt + L.max_pairs / slice + 1;
-    L.tile_count = take(4 * (nt + 1));
-    L.tile_off = take(4 * (nt + 1));
-    L.ucount = take(4 * (size_t)units * nt);
-    L.pchunk = take(4 * (size_t)(units / 64) * nt);
-    L.slice_off = take(4 * (nt + 1));
-    L.counters = take(64);
-    L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
-    const size_t pb = (wide ? 8 : 4) * (size_t)TS * TS * L.max_slices;
-    L.partial = take(pb);
-    L.partial_aux = aux ? take(pb) : L.partial;
-    L.slice_table = take(8 * (size_t)L.max_slices);
-    return L.total = off;
-  };
-  // Slices: a block's share of a tile's pairs.  Long slices of dense tiles end
-  // last and leave CUs idle (a 262 k point frame is 256 tiles: 20.6 us of
-  // accumulation in slices of 4096, 9.3 in slices of 512; 16 k points 16.7 and
-  // 5.2; the cubic blob's slices take longer: 4 M points 447 us at 4096, 337 at
-  // 1024; 16.7 M at 1024^2, Gaussian 158 and 153 at 2048, cubic 388 and 345);
-  // 150 M points fill the chip either way.  Shorter slices take more
-  // workspace, as do float64 slice partials: near the size of the library's
-  // fixed one the slices stay at 4096 and the partials at float32, so that it
-  // holds the renders that it held.  The image depends on the slice
-  // length, so this depends on the points and the camera alone, not on the
-  // attribute channel or the form of the workspace.
+  // at most a slice per tile besides the full ones, of which the largest count
+  // over all numbers of pairs up to max_pairs: a plan covers fewer points
   const bool cubic = sp.blob == LOD_BLOB_CUBIC;
-  const uint32_t want = max_points <= (1u << 19)   ? 512u
-                        : max_points <= (1u << 25) ? (cubic ? 1024u : 2048u)
-                                                   : SPLAT_SLICE;
-  const uint32_t few = (uint32_t)std::min<uint64_t>(
-      SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (max_points + (64 * 2048) - 1) / (64 * 2048)));
-  const bool near_fixed = lay_out(64 * few, want, true, false) > (size_t)LOD_NOALLOC_SCRATCH_BYTES &&
-                          lay_out(64 * few, SPLAT_SLICE, false, false) <= (size_t)LOD_NOALLOC_SCRATCH_BYTES;
-  lay_out(L.units, near_fixed ? SPLAT_SLICE : want, !near_fixed, aux);
+  uint64_t full = 0;
+  for (int top = 19; top <= 32; ++top) {   // slice_bits steps at powers of two
+    const uint64_t pairs = std::min<uint64_t>(L.max_pairs, 1ull << top);
+    full = std::max(full, pairs >> slice_bits((uint32_t)std::min<uint64_t>(pairs, ~0u), cubic));
+  }
+  L.max_slices = nt + full + 1;
+  size_t off = 0;
+  auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
+  L.tile_count = take(4 * (nt + 1));
+  L.tile_off = take(4 * (nt + 1));
+  L.ucount = take(4 * (size_t)L.units * nt);
+  L.pchunk = take(4 * (size_t)L.chunks * nt);
+  L.slice_off = take(4 * (nt + 1));
+  L.counters = take(64);
+  L.rec = take(rec_bytes(sp, aux) * L.max_pairs);
+  L.partial = take(8 * (size_t)TS * TS * L.max_slices);
+  L.partial_aux = aux ? take(8 * (size_t)TS * TS * L.max_slices) : L.partial;
+  L.slice_table = take(8 * (size_t)L.max_slices);
+  L.total = off;
   return LOD_OK;
+}
+
+// The size by which the allocation-free render accepts a call: binning units of
+// 2048 points, the records, and a float32 tile per 4096 pairs and per tile.
+size_t noalloc_size(uint64_t count, const splat_params &sp, const SplatLayout &L) {
+  const uint64_t nt = L.n_tiles, slices = nt + L.max_pairs / 4096 + 1;
+  const uint64_t chunks = std::min<uint64_t>(SPLAT_MAX_CHUNKS, std::max<uint64_t>(1, (count + (1u << 17) - 1) >> 17));
+  return 3 * align256(4 * (nt + 1)) + align256(4 * 64 * chunks * nt) + align256(4 * chunks * nt) + align256(64) +
+         align256(rec_bytes(sp, false) * L.max_pairs) + align256(4 * TS * TS * slices) + align256(8 * slices);
 }
 
 // Binning, accumulation and the final slice sums for any point source and
@@ -2013,7 +2019,7 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
   uint64_t *ctr = (uint64_t *)(W + L.counters);
   uint64_t *status = status_word ? status_word : ctr;
   RecT *rec = (RecT *)(W + L.rec);
-  const Partial partial{W + L.partial, L.wide}, partial_aux{W + L.partial_aux, L.wide};
+  double *partial = (double *)(W + L.partial), *partial_aux = (double *)(W + L.partial_aux);
   uint2 *stab = (uint2 *)(W + L.slice_table);
   int nbits = 0;
   while ((1u << nbits) < nt) ++nbits;
@@ -2048,12 +2054,12 @@ static lod_status launch_splat_src(const Src &src, bool any, const lod_camera &c
       LOD_LAUNCH(k_bin_chunkscan, dim3((nt + 255) / 256), dim3(256), 0, st, pchunk, nt, L.chunks, tcount);
   }
   LOD_LAUNCH(k_tile_plan, dim3(1), dim3(PLAN_T), 0, st, any ? tcount : (uint32_t *)nullptr,
-             plan_scans ? pchunk : (uint32_t *)nullptr, L.chunks, nt, L.slice, toff, soff,
+             plan_scans ? pchunk : (uint32_t *)nullptr, L.chunks, nt, (int)RecInfo<RecT>::cubic, toff, soff,
              status_word ? (uint64_t *)nullptr : ctr);
   if (any) {
     auto fill = [&](auto kernel, uint32_t g, size_t bytes) {
       LOD_LAUNCH_NAMED("k_bin_fill", kernel, dim3(L.units / g), dim3(BW), bytes, st, src, c, L.units, g, nbits,
-                       ucount, pre, toff, soff, L.slice, stab, L.max_slices, rec, L.max_pairs, status);
+                       ucount, pre, toff, soff, stab, L.max_slices, rec, L.max_pairs, status);
     };
     // with cursors in LDS, blocks of two units when there are many (32-bit
     // cursors take twice the LDS of the 16-bit counts: fewer resident waves)

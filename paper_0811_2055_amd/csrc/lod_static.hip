@@ -19,7 +19,12 @@
 
 namespace {
 
-static __device__ __align__(256) unsigned char scratch[LOD_NOALLOC_SCRATCH_BYTES];
+// The limit is on a call's size as noalloc_size counts it, 1024 bytes for every
+// tile and every 4096 pairs.  The layout of a call takes 2048 bytes for every
+// tile and slice, of which there are up to 4096 besides one per tile at such
+// sizes: less than 16 MiB more, for 8192 tiles.
+constexpr size_t kScratchBytes = LOD_NOALLOC_SCRATCH_BYTES + (16u << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -55,10 +60,10 @@ lod_status splat_render_noalloc(const float *x, const float *y, const float *z, 
   lodh::SplatLayout L;
   lod_status s = lodh::splat_layout(count, *cam, *sp, L, false);
   if (s != LOD_OK) return s;
+  if (lodh::noalloc_size(count, *sp, L) > (size_t)LOD_NOALLOC_SCRATCH_BYTES) return LOD_ECAPACITY;
   // near the limit with fewer, larger binning units: the image is the same
-  if (L.total > (size_t)LOD_NOALLOC_SCRATCH_BYTES) s = lodh::splat_layout(count, *cam, *sp, L, false, true);
-  if (s != LOD_OK) return s;
-  if (L.total > (size_t)LOD_NOALLOC_SCRATCH_BYTES) return LOD_ECAPACITY;
+  if (L.total > kScratchBytes && (s = lodh::splat_layout(count, *cam, *sp, L, false, true)) != LOD_OK) return s;
+  if (L.total > kScratchBytes) return LOD_ECAPACITY;
   void *ws = nullptr;
   if ((s = scratch_for_current_device(&ws)) != LOD_OK) return s;
   return lodh::launch_splat(x, y, z, m, nullptr, count, *cam, *sp, ws, L, image, nullptr, (hipStream_t)stream);
