@@ -1506,6 +1506,57 @@ __device__ __forceinline__ double quad_sum(double v) {
   return v;
 }
 
+// One pixel's terms of the cubic blob's adjoint: (ox, oy) its offset, gf the
+// image's gradient there, rad = (h^2, 1 / h^2), fac the factors of the
+// position's and the radius' sums; s = sums of the mass, u, v and radius.
+__device__ __forceinline__ void adjoint_pixel(float ox, float oy, float gf, double2 rad, double2 fac, bool radius,
+                                              double (&s)[4]) {
+  const double ox64 = (double)ox, oy64 = (double)oy;
+  const double r2 = __builtin_fma(ox64, ox64, oy64 * oy64);   // exact squares, one rounding
+  const double q2 = fmax(r2 * rad.y, 1e-280);
+  const double yq = __builtin_amdgcn_rsq(q2), gq = q2 * yq;
+  const double nt = __builtin_fma(-gq, 0.5 * yq, 0.5);
+  const double q = __builtin_fma(gq, nt, gq), qi = __builtin_fma(yq, nt, yq);   // q and 1 / q
+  const double pq = 1.0 - q, pp = pq * pq;
+  const bool inner = q <= 0.5;
+  const double wq = inner ? __builtin_fma(-6.0 * q2, pq, 1.0) : pp * (pq + pq);
+  const double dwq = inner ? __builtin_fma(18.0, q, -12.0) : -6.0 * pp * qi;    // w'(q) / q
+  const double gp = (double)gf;
+  if (r2 < rad.x) {
+    const double t = fac.x * (dwq * gp);
+    s[0] += wq * gp;
+    s[1] += t * ox64;
+    s[2] += t * oy64;
+    if (radius) s[3] += fac.y * (__builtin_fma(-q2, dwq, -2.0 * wq) * gp);
+  }
+}
+
+// The gradients of a point from its four sums.
+__device__ __forceinline__ void adjoint_point(const Cam &c, bool vis, float xc, float yc, float zc, float h,
+                                              bool dh_live, double ih2, double am, double au, double av, double ah,
+                                              uint64_t k, float *gm, float *gx, float *gy, float *gz) {
+  double dx = 0.0, dy = 0.0, dz = 0.0;
+  if (vis) {
+    if (c.proj == 0) {
+      dx = au * (double)c.W;
+      dy = av * (double)c.H;
+    } else {
+      const double zz = (double)zc;
+      const double a = (double)c.F / zz;
+      const double bu = (double)c.F * (double)xc / (zz * zz);
+      const double bv = (double)c.F * (double)yc / (zz * zz);
+      const double dh = dh_live ? -(double)h / zz : 0.0;
+      dx = au * (a * c.rx - bu * c.fx) + av * (a * c.ux - bv * c.fx) + ah * dh * c.fx;
+      dy = au * (a * c.ry - bu * c.fy) + av * (a * c.uy - bv * c.fy) + ah * dh * c.fy;
+      dz = au * (a * c.rz - bu * c.fz) + av * (a * c.uz - bv * c.fz) + ah * dh * c.fz;
+    }
+  }
+  gm[k] = (float)(am * (kCubicNorm * ih2));
+  if (gx) gx[k] = (float)dx;
+  if (gy) gy[k] = (float)dy;
+  if (gz) gz[k] = (float)dz;
+}
+
 // Adjoint of the cubic blob over each point's own footprint (float64 sums):
 // dI/dm = W, dI/dox = m 40/(7 pi h^4) (w'(q)/q) ox, and with a world-space size
 // (radius not clamped) dI/dh = m 40/(7 pi h^3) (-2 w - q w'(q)) with
@@ -1574,68 +1625,51 @@ __global__ __launch_bounds__(PT) void k_backward_cubic(const float *__restrict__
       const int4 win = swin[w][p];
       const double2 rad = srad[w][p], fac = sfac[w][p];
       const int step = win.w & 0xFFFF, rows = win.w >> 16;
-      double am = 0.0, au = 0.0, av = 0.0, ah = 0.0;
+      double t[4] = {0.0, 0.0, 0.0, 0.0};
       int i = lane % Q, j = 0;
       while (i >= win.y && win.y > 0) { i -= win.y; ++j; }
       for (int e = lane % Q; e < win.z; e += Q) {
         const float gf = g[win.x + j * (int)c.W + i];
         // pixel centres are half-integers below 2^15: the sums are exact
-        const float ox = geo.x - (geo.z + (float)i), oy = geo.y - (geo.w + (float)j);
-        const double ox64 = (double)ox, oy64 = (double)oy;
-        const double r2 = __builtin_fma(ox64, ox64, oy64 * oy64);   // exact squares, one rounding
-        const double q2 = fmax(r2 * rad.y, 1e-280);
-        const double yq = __builtin_amdgcn_rsq(q2), gq = q2 * yq;
-        const double nt = __builtin_fma(-gq, 0.5 * yq, 0.5);
-        const double q = __builtin_fma(gq, nt, gq), qi = __builtin_fma(yq, nt, yq);   // q and 1 / q
-        const double pq = 1.0 - q, pp = pq * pq;
-        const bool inner = q <= 0.5;
-        const double wq = inner ? __builtin_fma(-6.0 * q2, pq, 1.0) : pp * (pq + pq);
-        const double dwq = inner ? __builtin_fma(18.0, q, -12.0) : -6.0 * pp * qi;    // w'(q) / q
-        const double gp = (double)gf;
-        if (r2 < rad.x) {
-          const double t = fac.x * (dwq * gp);
-          am += wq * gp;
-          au += t * ox64;
-          av += t * oy64;
-          if (radius) ah += fac.y * (__builtin_fma(-q2, dwq, -2.0 * wq) * gp);
-        }
+        adjoint_pixel(geo.x - (geo.z + (float)i), geo.y - (geo.w + (float)j), gf, rad, fac, radius, t);
         i += step;
         j += rows;
         if (i >= win.y) { i -= win.y; ++j; }
       }
-      am = quad_sum(am);
-      au = quad_sum(au);
-      av = quad_sum(av);
-      if (radius) ah = quad_sum(ah);
+      t[0] = quad_sum(t[0]);
+      t[1] = quad_sum(t[1]);
+      t[2] = quad_sum(t[2]);
+      if (radius) t[3] = quad_sum(t[3]);
       const int which = lane % Q;
-      ssum[w][which][p] = which == 0 ? am : which == 1 ? au : which == 2 ? av : ah;
+      ssum[w][which][p] = which == 0 ? t[0] : which == 1 ? t[1] : which == 2 ? t[2] : t[3];
     }
     wave_sync_mem();
-    if (have) {
-      const double am = ssum[w][0][slot] * (kCubicNorm * srad[w][slot].y), au = ssum[w][1][slot],
-                   av = ssum[w][2][slot], ah = ssum[w][3][slot];
-      double dx = 0.0, dy = 0.0, dz = 0.0;
-      if (vis) {
-        if (c.proj == 0) {
-          dx = au * (double)c.W;
-          dy = av * (double)c.H;
-        } else {
-          const double zz = (double)zc;
-          const double a = (double)c.F / zz;
-          const double bu = (double)c.F * (double)xc / (zz * zz);
-          const double bv = (double)c.F * (double)yc / (zz * zz);
-          const double dh = dh_live ? -(double)h / zz : 0.0;
-          dx = au * (a * c.rx - bu * c.fx) + av * (a * c.ux - bv * c.fx) + ah * dh * c.fx;
-          dy = au * (a * c.ry - bu * c.fy) + av * (a * c.uy - bv * c.fy) + ah * dh * c.fy;
-          dz = au * (a * c.rz - bu * c.fz) + av * (a * c.uz - bv * c.fz) + ah * dh * c.fz;
-        }
-      }
-      gm[k] = (float)am;
-      if (gx) gx[k] = (float)dx;
-      if (gy) gy[k] = (float)dy;
-      if (gz) gz[k] = (float)dz;
-    }
+    if (have)
+      adjoint_point(c, vis, xc, yc, zc, h, dh_live, srad[w][slot].y, ssum[w][0][slot], ssum[w][1][slot],
+                    ssum[w][2][slot], ssum[w][3][slot], k, gm, gx, gy, gz);
     wave_sync_mem();                         // the next points rewrite the rows
+  }
+}
+
+// The same with a thread per point: blobs of a fixed radius of a few pixels, for
+// which the exchange between the lanes costs more than it saves (see the launch).
+__global__ __launch_bounds__(PT) void k_backward_cubic_small(const float *__restrict__ x, const float *__restrict__ y,
+                                                             const float *__restrict__ z, const float *__restrict__ m,
+                                                             uint64_t count, Cam c, const float *__restrict__ g,
+                                                             float *__restrict__ gm, float *__restrict__ gx,
+                                                             float *__restrict__ gy, float *__restrict__ gz) {
+  for (uint64_t k = (uint64_t)blockIdx.x * PT + threadIdx.x; k < count; k += (uint64_t)gridDim.x * PT) {
+    float u, v, xc, yc, zc;
+    const bool vis = project(c, x[k], y[k], z[k], u, v, xc, yc, zc);
+    const double hh = (double)c.hpx * (double)c.hpx, ih2 = 1.0 / hh;
+    const double2 rad = make_double2(hh, ih2), fac = make_double2((double)m[k] * kCubicNorm * (ih2 * ih2), 0.0);
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    int i0, i1, j0, j1;
+    if (vis && cover_range(c.hpx, u, c.W, i0, i1) && cover_range(c.hpx, v, c.H, j0, j1))
+      for (int j = j0; j <= j1; ++j)
+        for (int i = i0; i <= i1; ++i)
+          adjoint_pixel(u - ((float)i + 0.5f), v - ((float)j + 0.5f), g[(uint64_t)j * c.W + i], rad, fac, false, t);
+    adjoint_point(c, vis, xc, yc, zc, c.hpx, false, ih2, t[0], t[1], t[2], 0.0, k, gm, gx, gy, gz);
   }
 }
 
@@ -2170,7 +2204,12 @@ lod_status launch_splat_backward(const float *x, const float *y, const float *z,
   if (!count) return LOD_OK;
   Cam c = make_cam(cam, sp, nullptr);
   const unsigned grid = (unsigned)std::min<uint64_t>(65535, (count + PT - 1) / PT);
-  if (sp.blob == LOD_BLOB_CUBIC)
+  // up to nine pixels: a thread a point (1 M and 3 M points, four lanes a point ->
+  // a thread: h = 0.6 25 -> 17 and 56 -> 38 us, 1 28 -> 24 and 63 -> 56, 1.25 36
+  // -> 33 and 84 -> 81; but 1.5 40 -> 42 and 93 -> 103, 2.5 67 -> 99)
+  if (sp.blob == LOD_BLOB_CUBIC && c.Fhw == 0.0f && c.hpx <= 1.25f)
+    LOD_LAUNCH(k_backward_cubic_small, dim3(grid), dim3(PT), 0, st, x, y, z, m, count, c, grad, gm, gx, gy, gz);
+  else if (sp.blob == LOD_BLOB_CUBIC)
     LOD_LAUNCH(k_backward_cubic, dim3(grid), dim3(PT), 0, st, x, y, z, m, count, c, grad, gm, gx, gy, gz);
   else
     LOD_LAUNCH(k_backward, dim3(grid), dim3(PT), 0, st, x, y, z, m, count, c, grad, gm, gx, gy, gz);

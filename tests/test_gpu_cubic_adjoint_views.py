@@ -15,7 +15,8 @@ from gpu_util import to_dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("h_px,h_world", [(0.0, 0.001), (0.0, 0.01), (0.0, 0.2), (2.2, 0.01), (2.2, 0.0), (16.0, 0.0)])
+@pytest.mark.parametrize("h_px,h_world", [(0.0, 0.001), (0.0, 0.01), (0.0, 0.2), (2.2, 0.01), (2.2, 0.0), (16.0, 0.0),
+                                          (0.3, 0.0), (1.25, 0.0), (1.2501, 0.0)])
 @pytest.mark.parametrize("n", [1, 65, 2000])
 def test_view_from_inside(n, h_px, h_world):
     import torch
