@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_build_init(BuildArgs a, uint32_t *__res
     zero[i] = 0u;
   if (blockIdx.x) return;
   if (threadIdx.x < 3) a.counts[threadIdx.x] = 0;
-  if (!a.snap_off || a.n_snap <= 1) return;
+  if (!a.snap_off || a.n_snap <= 1 || a.N == 0) return;   // no particles: no offsets are read
   __syncthreads();
   bool bad = false;
   for (uint32_t s = threadIdx.x; s < a.n_snap; s += blockDim.x) {
