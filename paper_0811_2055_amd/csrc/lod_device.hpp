@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lod.h"
 
 namespace lodk {
@@ -153,13 +155,12 @@ __device__ __forceinline__ uint16_t quant_at(uint32_t cD, uint32_t lo16, int D, 
 }
 
 // ---------------------------------------------------------------------------
-// Block-wide exclusive scan of one value per thread (LDS, any blockDim that
-// is a multiple of 64 and <= 1024).  `tmp` holds >= blockDim/64 + 1 entries.
-// Inclusive scan over the wave; 32-bit values on the lane-shift network (six
+// Inclusive scan over the wave; 32-bit integers on the lane-shift network (six
 // instructions) instead of six LDS permutes.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
   if constexpr (sizeof(T) == 4) {
+    static_assert(std::is_integral<T>::value, "the lane-shift form adds integers");
     uint32_t x = (uint32_t)v;
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
@@ -179,6 +180,8 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
   }
 }
 
+// Block-wide exclusive scan of one value per thread (LDS, any blockDim that
+// is a multiple of 64 and <= 1024).  `tmp` holds >= blockDim/64 + 1 entries.
 template <typename T>
 __device__ __forceinline__ T block_excl_scan(T v, T *tmp, T &total) {
   const int lane = threadIdx.x & (WAVE - 1);
@@ -217,16 +220,6 @@ __device__ __forceinline__ T block_reduce_sum(T v, T *tmp) {
   r = tmp[nw];
   __syncthreads();
   return r;
-}
-
-// lower_bound over a sorted uint32 array in [lo, hi) for the first element >= key.
-__device__ __forceinline__ uint64_t lower_bound_u32(const uint32_t *a, uint64_t lo, uint64_t hi,
-                                                    uint32_t key) {
-  while (lo < hi) {
-    uint64_t mid = lo + ((hi - lo) >> 1);
-    if (a[mid] < key) lo = mid + 1; else hi = mid;
-  }
-  return lo;
 }
 
 }  // namespace lodk
