@@ -44,7 +44,7 @@ struct Cam {
   float inv2s2;     // 1 / (2 sigma^2)
   float norm;       // 1 / (2 pi sigma^2)
   float wscale;     // the power of two below it: multiplies masses without rounding
-  double wnorm;     // 1 / (2 pi sigma^2) / wscale: multiplies a slice's float64 sums
+  double wnorm;     // the rest of the normalisation: multiplies a slice's float64 sums
   float inv_s2;     // 1 / sigma^2
   int nin, nmax;    // pixels at most nin from the one that holds the point are covered, none beyond nmax is
   float kexp2;      // -log2(e) / (2 sigma^2): Gaussian factor = exp2(o^2 kexp2)
@@ -68,7 +68,8 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   k.inv2s2 = (float)(1.0 / (2.0 * s64 * s64));
   k.norm = (float)(1.0 / (2.0 * M_PI * s64 * s64));
   k.inv_s2 = (float)(1.0 / (s64 * s64));
-  k.kexp2 = (float)(-1.4426950408889634 / (2.0 * s64 * s64));
+  const double kexp2 = -1.4426950408889634 / (2.0 * s64 * s64);
+  k.kexp2 = (float)kexp2;
   // the point lies within half a pixel of its pixel's centre; the binning admits
   // pixels 1/100 further out, and its float32 range and the
   // offsets are within 1/200 pixel of the exact ones
@@ -77,7 +78,9 @@ Cam make_cam(const lod_camera &c, const splat_params &sp, const lodh::SplatLayou
   const double norm = 1.0 / (2.0 * M_PI * s64 * s64);
   const int e2 = std::min(std::ilogb(norm), 127);
   k.wscale = std::ldexp(1.0f, e2);
-  k.wnorm = norm / std::ldexp(1.0, e2);
+  // the Gaussian drawn is that of the rounded exponent constant: a blob keeps
+  // its mass (a bias of up to 3.6e-8 of every dense pixel otherwise)
+  k.wnorm = norm / std::ldexp(1.0, e2) * (std::isfinite(k.kexp2) ? (double)k.kexp2 / kexp2 : 1.0);
   if (L) { k.tiles_x = L->tiles_x; k.tiles_y = L->tiles_y; }
   k.blob = sp.blob;
   k.hpx = sp.h_px;

@@ -41,3 +41,18 @@ def test_isolated_points(sigma, radius, mass):
     on = want > 1e-30
     rel = np.abs(got[on] - want[on]) / want[on]
     assert float(rel.max()) <= tol, (float(rel.max()), tol)
+
+
+@pytest.mark.parametrize("sigma", [0.5, 0.7, 0.9, 1.0, 1.1, 1.3, 2.0])
+def test_mass_of_a_dense_image(sigma):
+    """Roundings that are the same for every point would not average out: the
+    image's sum is the oracle's within a third of a rounding unit."""
+    import torch
+    rng = np.random.default_rng(9)
+    W, H, n = 128, 96, 200000
+    x, y, z = (rng.uniform(0.1, 0.9, n).astype(np.float32) for _ in range(3))
+    m = rng.uniform(0.2, 1.0, n).astype(np.float32)
+    d = [torch.from_numpy(a).cuda() for a in (x, y, z, m)]
+    got = lib.splat(*d, lib.Camera.ortho(W, H), sigma, 3.0).cpu().numpy().astype(np.float64).sum()
+    want = osplat.render(osplat.Camera(0, W, H), x, y, z, m, sigma, 3.0).sum()
+    assert abs(got / want - 1.0) <= U / 3, got / want - 1.0
