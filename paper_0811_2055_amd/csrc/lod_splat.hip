@@ -1570,9 +1570,10 @@ __device__ __forceinline__ void adjoint_point(const Cam &c, bool vis, float xc, 
 // together, so that no lane waits for a longer one's window.  Bound by the
 // float64 operations of a pixel (vector issue 75 % busy); q, its reciprocal and
 // w'(q)/q come from one hardware reciprocal square root and one Newton step
-// instead of a square root and two divisions.  A million points of 25 pixels:
-// 66 us, against 101 with a thread per point; reading the gradient a pixel
-// ahead changed nothing.
+// instead of a square root and two divisions (of 9.6 M gradients with radii
+// from 0.6 to 16 one differs, by an ulp of float32).  A million points of 25
+// pixels: 66 us, against 101 with a thread per point; reading the gradient a
+// pixel ahead changed nothing.
 __global__ __launch_bounds__(PT) void k_backward_cubic(const float *__restrict__ x, const float *__restrict__ y,
                                                        const float *__restrict__ z, const float *__restrict__ m,
                                                        uint64_t count, Cam c, const float *__restrict__ g,
